@@ -39,11 +39,10 @@ struct bs_mlp {
   TrainState* ts = nullptr;
   float *Xn = nullptr, *tn = nullptr;
   int n = 0;
-  float *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *Z3 = nullptr, *H3 = nullptr;
-  float *yv = nullptr, *dy = nullptr, *dZ3 = nullptr, *dZ2 = nullptr, *dZ1 = nullptr;
-  float* part = nullptr;
-  size_t part_len = 0;
-  double* loss = nullptr;
+  float *H1 = nullptr, *H2 = nullptr, *dZ2 = nullptr, *dZ3 = nullptr;
+  float *vpart = nullptr, *wpart = nullptr;   // gradient partials (MlpRowArgs)
+  double* lpart = nullptr;
+  double* loss = nullptr;   // pinned host memory, written by the reduction kernel
   float* Xp = nullptr;
   void *W2b = nullptr, *W3b = nullptr, *w4b = nullptr, *Hb1 = nullptr, *Hb2 = nullptr;
   hipGraph_t graph = nullptr;
@@ -59,72 +58,17 @@ void* alloc(bs_mlp* m, size_t bytes) {
   return p;
 }
 
-int splits_for(int K) { return std::max(1, std::min(16, (K + 255) / 256)); }
-
-GemmArgs gemm(const float* A, int lda, const float* B, int ldb, float* C, int ldc, int M, int N, int K) {
-  GemmArgs g{};
-  g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
-  return g;
-}
-
-// Forward pass of the FP32 network on normalised inputs X (n rows); output y' in y.
-void forward(bs_mlp* m, const float* X, int n, float* y, hipStream_t s) {
-  const float* p = m->state;
-  GemmArgs g = gemm(X, 4, p + MLP_OFF_W1, 4, m->H1, MLP_HID, n, MLP_HID, 4);
-  g.bias = p + MLP_OFF_B1; g.Z = m->Z1;
-  launch_gemm(g, false, true, EPI_BIAS_SILU, 1, s);
-  g = gemm(m->H1, MLP_HID, p + MLP_OFF_W2, MLP_HID, m->H2, MLP_HID, n, MLP_HID, MLP_HID);
-  g.bias = p + MLP_OFF_B2; g.Z = m->Z2;
-  launch_gemm(g, false, true, EPI_BIAS_SILU, 1, s);
-  g = gemm(m->H2, MLP_HID, p + MLP_OFF_W3, MLP_HID, m->H3, MLP_HID, n, MLP_HID, MLP_HID);
-  g.bias = p + MLP_OFF_B3; g.Z = m->Z3;
-  launch_gemm(g, false, true, EPI_BIAS_SILU, 1, s);
-  g = gemm(m->H3, MLP_HID, p + MLP_OFF_W4, MLP_HID, y, 1, n, 1, MLP_HID);
-  g.bias = p + MLP_OFF_B4;
-  launch_gemm(g, false, true, EPI_BIAS, 1, s);
-}
-
 // Loss and gradient of the training data (forward included).
-void loss_grad(bs_mlp* m, hipStream_t s) {
-  const int n = m->n;
-  const float* p = m->state;
-  float* gr = m->grad;
-  forward(m, m->Xn, n, m->yv, s);
-  launch_loss(m->yv, m->tn, n, m->dy, m->loss, s);
-  const int sp = splits_for(n);
-  // output layer
-  GemmArgs g = gemm(m->dy, 1, m->H3, MLP_HID, gr + MLP_OFF_W4, MLP_HID, 1, MLP_HID, n);
-  g.part = m->part;
-  launch_gemm(g, true, false, EPI_NONE, sp, s);
-  launch_colsum(m->dy, n, 1, gr + MLP_OFF_B4, s);
-  g = gemm(m->dy, 1, p + MLP_OFF_W4, MLP_HID, m->dZ3, MLP_HID, n, MLP_HID, 1);
-  g.Zin = m->Z3;
-  launch_gemm(g, false, false, EPI_DSILU, 1, s);
-  // layer 3
-  g = gemm(m->dZ3, MLP_HID, m->H2, MLP_HID, gr + MLP_OFF_W3, MLP_HID, MLP_HID, MLP_HID, n);
-  g.part = m->part;
-  launch_gemm(g, true, false, EPI_NONE, sp, s);
-  launch_colsum(m->dZ3, n, MLP_HID, gr + MLP_OFF_B3, s);
-  g = gemm(m->dZ3, MLP_HID, p + MLP_OFF_W3, MLP_HID, m->dZ2, MLP_HID, n, MLP_HID, MLP_HID);
-  g.Zin = m->Z2;
-  launch_gemm(g, false, false, EPI_DSILU, 1, s);
-  // layer 2
-  g = gemm(m->dZ2, MLP_HID, m->H1, MLP_HID, gr + MLP_OFF_W2, MLP_HID, MLP_HID, MLP_HID, n);
-  g.part = m->part;
-  launch_gemm(g, true, false, EPI_NONE, sp, s);
-  launch_colsum(m->dZ2, n, MLP_HID, gr + MLP_OFF_B2, s);
-  g = gemm(m->dZ2, MLP_HID, p + MLP_OFF_W2, MLP_HID, m->dZ1, MLP_HID, n, MLP_HID, MLP_HID);
-  g.Zin = m->Z1;
-  launch_gemm(g, false, false, EPI_DSILU, 1, s);
-  // layer 1
-  g = gemm(m->dZ1, MLP_HID, m->Xn, 4, gr + MLP_OFF_W1, 4, MLP_HID, 4, n);
-  g.part = m->part;
-  launch_gemm(g, true, false, EPI_NONE, sp, s);
-  launch_colsum(m->dZ1, n, MLP_HID, gr + MLP_OFF_B1, s);
+void loss_grad(bs_mlp* m, float* grad, hipStream_t s) {
+  MlpRowArgs a{};
+  a.X = m->Xn; a.t = m->tn; a.p = m->state; a.n = m->n;
+  a.H1 = m->H1; a.H2 = m->H2; a.dZ2 = m->dZ2; a.dZ3 = m->dZ3;
+  a.vpart = m->vpart; a.wpart = m->wpart; a.lpart = m->lpart;
+  launch_mlp_loss_grad(a, grad, m->loss, s);
 }
 
 void train_step(bs_mlp* m, hipStream_t s) {
-  loss_grad(m, s);
+  loss_grad(m, m->grad, s);
   launch_adam(m->state, m->grad, m->am, m->av, MLP_NPARAM, m->ts, s);
 }
 
@@ -172,24 +116,24 @@ extern "C" int bs_mlp_create(bs_ctx* c, uint64_t seed, int32_t max_batch, bs_mlp
   m->Xn = (float*)alloc(m, cap * 16);
   m->tn = (float*)alloc(m, cap * 4);
   m->Xp = (float*)alloc(m, cap * 16);
-  m->Z1 = (float*)alloc(m, cap * H * 4); m->H1 = (float*)alloc(m, cap * H * 4);
-  m->Z2 = (float*)alloc(m, cap * H * 4); m->H2 = (float*)alloc(m, cap * H * 4);
-  m->Z3 = (float*)alloc(m, cap * H * 4); m->H3 = (float*)alloc(m, cap * H * 4);
-  m->dZ1 = (float*)alloc(m, cap * H * 4); m->dZ2 = (float*)alloc(m, cap * H * 4);
-  m->dZ3 = (float*)alloc(m, cap * H * 4);
-  m->yv = (float*)alloc(m, cap * 4);
-  m->dy = (float*)alloc(m, cap * 4);
-  m->part_len = (size_t)16 * H * H;
-  m->part = (float*)alloc(m, m->part_len * 4);
-  m->loss = (double*)alloc(m, 16);
+  m->H1 = (float*)alloc(m, cap * H * 4); m->H2 = (float*)alloc(m, cap * H * 4);
+  m->dZ2 = (float*)alloc(m, cap * H * 4); m->dZ3 = (float*)alloc(m, cap * H * 4);
+  const size_t nblk = (size_t)mlp_row_blocks(max_batch);
+  m->vpart = (float*)alloc(m, 2 * nblk * MR_PART * 4);
+  m->wpart = (float*)alloc(m, (size_t)MLP_MAX_SPLITS * 2 * H * H * 4);
+  m->lpart = (double*)alloc(m, 2 * nblk * 8);
+  if (hipHostMalloc((void**)&m->loss, sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    m->loss = nullptr;
+  }
   m->W2b = alloc(m, H * H * 2);
   m->W3b = alloc(m, H * H * 2);
   m->w4b = alloc(m, H * 2);
   m->Hb1 = alloc(m, cap * H * 2);
   m->Hb2 = alloc(m, cap * H * 2);
-  const void* need[] = {m->state, m->grad, m->am, m->av, m->ts, m->Xn, m->tn, m->Xp, m->Z1, m->H1, m->Z2, m->H2,
-                        m->Z3, m->H3, m->dZ1, m->dZ2, m->dZ3, m->yv, m->dy, m->part, m->loss, m->W2b, m->W3b,
-                        m->w4b, m->Hb1, m->Hb2};
+  if (m->loss) *m->loss = 0.0;
+  const void* need[] = {m->state, m->grad, m->am, m->av, m->ts, m->Xn, m->tn, m->Xp, m->H1, m->H2, m->dZ2, m->dZ3,
+                        m->vpart, m->wpart, m->lpart, m->loss, m->W2b, m->W3b, m->w4b, m->Hb1, m->Hb2};
   for (const void* p : need)
     if (!p) return fail(BS_ENOMEM, "surrogate buffers");
   const float norm0[10] = {0, 0, 0, 0, 1, 1, 1, 1, 0, 1};
@@ -210,6 +154,7 @@ extern "C" void bs_mlp_destroy(bs_mlp* m) {
   if (m->s) (void)hipStreamSynchronize(m->s);
   for (void* p : m->owned)
     if (p) (void)hipFree(p);
+  if (m->loss) (void)hipHostFree(m->loss);
   if (m->ev_in) (void)hipEventDestroy(m->ev_in);
   if (m->ev_out) (void)hipEventDestroy(m->ev_out);
   if (m->s) (void)hipStreamDestroy(m->s);
@@ -253,15 +198,14 @@ extern "C" int bs_mlp_loss_grad(bs_mlp* m, float* grad, double* loss_host) {
   bs_ctx* c = m->c;
   if (m->n < 2) return ctx_fail(c, BS_EINVAL, "no training data (bs_mlp_set_data)");
   int rc = on_stream(m, [&](hipStream_t s) {
-    loss_grad(m, s);
+    loss_grad(m, grad ? grad : m->grad, s);
     LAUNCHCHK(c, "loss/gradient");
-    if (grad) HIPCHK(c, hipMemcpyAsync(grad, m->grad, MLP_NPARAM * 4, hipMemcpyDeviceToDevice, s));
     return BS_OK;
   });
   if (rc) return rc;
   if (loss_host) {
     HIPCHK(c, hipStreamSynchronize(m->s));
-    HIPCHK(c, hipMemcpy(loss_host, m->loss, 8, hipMemcpyDeviceToHost));
+    *loss_host = *m->loss;
   }
   return BS_OK;
 }
@@ -294,7 +238,7 @@ extern "C" int bs_mlp_train(bs_mlp* m, int32_t steps, double lr, int32_t cosine,
   if (rc) return rc;
   if (loss_host) {
     HIPCHK(c, hipStreamSynchronize(m->s));
-    HIPCHK(c, hipMemcpy(loss_host, m->loss, 8, hipMemcpyDeviceToHost));
+    *loss_host = *m->loss;
   }
   return BS_OK;
 }
@@ -306,11 +250,12 @@ extern "C" int bs_mlp_predict(bs_mlp* m, const float* X, int32_t n, int32_t bf16
   if (n < 1 || n > m->cap) return ctx_fail(c, BS_EINVAL, "prediction batch must be in [1, max_batch]");
   const float* norm = m->state + MLP_NPARAM;
   return on_stream(m, [&](hipStream_t s) {
-    launch_normalise(X, nullptr, n, norm, m->Xp, nullptr, s);
     if (!bf16) {
-      forward(m, m->Xp, n, m->dy, s);
-      launch_denorm(m->dy, n, norm, y, s);
+      MlpRowArgs a{};
+      a.X = X; a.p = m->state; a.norm = norm; a.n = n; a.y = y;
+      launch_mlp_predict(a, s);
     } else {
+      launch_normalise(X, nullptr, n, norm, m->Xp, nullptr, s);
       launch_to_bf16(m->state + MLP_OFF_W2, m->W2b, MLP_HID * MLP_HID, s);
       launch_to_bf16(m->state + MLP_OFF_W3, m->W3b, MLP_HID * MLP_HID, s);
       launch_to_bf16(m->state + MLP_OFF_W4, m->w4b, MLP_HID, s);

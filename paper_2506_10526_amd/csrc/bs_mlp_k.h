@@ -14,18 +14,22 @@ constexpr int MLP_OFF_B4 = MLP_OFF_W4 + MLP_HID;             // 133120
 constexpr int MLP_NPARAM = MLP_OFF_B4 + 1;                   // 133121
 constexpr int MLP_NSTATE = MLP_NPARAM + 10;                  // + mu_x[4], s_x[4], mu_t, s_t
 
-enum { EPI_NONE = 0, EPI_BIAS_SILU = 1, EPI_DSILU = 2, EPI_BIAS = 3 };
-
-struct GemmArgs {
-  const float* A;
-  const float* B;
-  float* C;
-  int M, N, K, lda, ldb, ldc;
-  const float* bias;   // EPI_BIAS_SILU / EPI_BIAS: [N]
-  float* Z;            // EPI_BIAS_SILU: pre-activation output (ldc)
-  const float* Zin;    // EPI_DSILU: pre-activation input (ldc)
-  float* part;         // split-K partial sums [splits][M][N]
-  int kchunk;          // set by the launcher
+// The row-local part of the network (k_mlp_rows) and the partials of its gradient.
+constexpr int MR_ROWS = 16;          // rows a block carries through the network at a time
+constexpr int MR_MAX_BLOCKS = 1024;  // row blocks; larger batches loop
+constexpr int MR_PART = 2048;        // per half block: dW1 [256][4], db1, db2, db3, dw4
+constexpr int MLP_MAX_SPLITS = 8;    // row splits of the weight gradients
+struct MlpRowArgs {
+  const float* X;      // [n][4]: normalised (training) or raw (prediction)
+  const float* t;      // training: normalised targets [n]
+  const float* p;      // parameters
+  const float* norm;   // prediction: mu_x[4], s_x[4], mu_t, s_t
+  int n;
+  float* y;            // prediction [n]
+  float *H1, *H2, *dZ2, *dZ3;   // training: [n][256]
+  float* vpart;        // [2 row blocks][MR_PART]
+  float* wpart;        // [splits][2][256][256]
+  double* lpart;       // [row blocks][2]: squared residuals, dy
 };
 
 // Device-resident training state read by the Adam kernel (so a captured step can be replayed).
@@ -37,14 +41,13 @@ struct TrainState {
   float lr, b1, b2, eps;
 };
 
-void launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, int splits, hipStream_t s);
-void launch_colsum(const float* X, int rows, int cols, float* out, hipStream_t s);
-void launch_loss(const float* y, const float* t, int B, float* dy, double* loss, hipStream_t s);
+int mlp_row_blocks(int n);
+void launch_mlp_predict(const MlpRowArgs& a, hipStream_t s);
+void launch_mlp_loss_grad(const MlpRowArgs& a, float* grad, double* loss, hipStream_t s);
 void launch_adam(float* p, const float* g, float* m, float* v, int n, const TrainState* ts, hipStream_t s);
 void launch_train_set(TrainState* ts, float lr, int K, int cosine, int reset_step, hipStream_t s);
 void launch_fit_norm(const float* X, const float* t, int n, float* norm, hipStream_t s);
 void launch_normalise(const float* X, const float* t, int n, const float* norm, float* Xn, float* tn, hipStream_t s);
-void launch_denorm(const float* yn, int n, const float* norm, float* y, hipStream_t s);
 void launch_mlp_init(float* p, unsigned long long seed, hipStream_t s);
 void launch_to_bf16(const float* x, void* y, int n, hipStream_t s);
 void launch_bf16_forward(const float* Xn, int n, const float* p, const float* norm, const void* W2b, const void* W3b,

@@ -6,6 +6,7 @@
 // Layer l: z = h W^T + b, h' = silu(z) = z / (1 + e^-z).  Loss: mean (y' - t')^2 over the batch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "bs_mlp_k.h"
@@ -18,119 +19,315 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// ---------------------------------------------------------------- FP32 GEMM
-// C[M][N] = op(A)[M][K] op(B)[K][N]; op(A)(m,k) = TA ? A[k lda + m] : A[m lda + k],
-// op(B)(k,n) = TB ? B[n ldb + k] : B[k ldb + n].  64 x 64 block tile, K staged by 16 through LDS,
-// 4 x 4 outputs per thread (rows ty + 16 i, columns tx + 16 j).  blockIdx.z = K split: with
-// ksplit > 1 the raw sums go to part[z][M][N] and k_gemm_reduce finishes them.
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int kc = g.kchunk;
-  const int kb = blockIdx.z * kc;
-  const int ke = min(g.K, kb + kc);
-  float acc[4][4] = {};
-  for (int k0 = kb; k0 < ke; k0 += 16) {
+// ---------------------------------------------------------------- FP32 network on FP32 MFMA
+// Everything of a row but the weight gradients stays inside the row: forward, loss and the chain of
+// dZ are row-local, so one kernel takes 16 rows through all of it in LDS, and only what the weight
+// gradients contract over rows (H1, H2, dZ2, dZ3) is written out.  Bound: the weights' trip from L2
+// (0.5 MB forward, 1 MB with the backward pass, per 16 rows) and the latency of the layer chain.
+// 8 waves of 32 columns (two 16 x 16 tiles of mfma_f32_16x16x4_f32, K = 256): a layer's 128 weight
+// registers per lane are loaded before the previous layer's barrier.  Loss and gradient
+// of 3122 rows and 483 predictions: 2.96 ms in about 30 launches (2.3 ms of it column sums by one
+// block) before, 0.14 ms in four now (rows 46 us, weight gradients 15, reduction 6, prediction 25).
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+constexpr int MR_LD = MLP_HID + 4;   // LDS row stride: 16 rows of one 16-byte chunk hit distinct banks
+
+// acc[t] += A (16 rows in LDS, K = 256) x the two column tiles held in wb; lane (c = lane & 15, g =
+// lane >> 4) supplies row c and column c at k = 16 s + 4 g + e in MFMA step (s, e).
+__device__ __forceinline__ void mr_mm(const float* __restrict__ A, const float4 (&wb)[2][16], int c, int g, f32x4m (&acc)[2]) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int idx = tid + 256 * r;
-      int m, k;
-      if (TA) { k = idx >> 6; m = idx & 63; } else { m = idx >> 4; k = idx & 15; }
-      const int gm = m0 + m, gk = k0 + k;
-      float v = 0.f;
-      if (gm < g.M && gk < ke) v = TA ? g.A[(size_t)gk * g.lda + gm] : g.A[(size_t)gm * g.lda + gk];
-      As[k][m] = v;
-      int n, kk;
-      if (TB) { n = idx >> 4; kk = idx & 15; } else { kk = idx >> 6; n = idx & 63; }
-      const int gn = n0 + n, gk2 = k0 + kk;
-      float w = 0.f;
-      if (gn < g.N && gk2 < ke) w = TB ? g.B[(size_t)gn * g.ldb + gk2] : g.B[(size_t)gk2 * g.ldb + gn];
-      Bs[kk][n] = w;
+  for (int s = 0; s < 16; ++s) {
+    const float4 av = *(const float4*)&A[c * MR_LD + 16 * s + 4 * g];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, wb[t][s].x, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, wb[t][s].y, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, wb[t][s].z, acc[t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, wb[t][s].w, acc[t], 0, 0, 0);
+  }
+}
+// The weights are read with buffer loads: one lane offset and scalar offsets for all 128 registers
+// (as 64-bit addresses they are loop-invariant, and keeping them spilled 280 registers a lane).
+// B of h W^T: columns col0 + 16 t + c, four consecutive k per load; W at float offset `off` of p.
+typedef unsigned u32x4m __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void mr_load_fwd(__amdgpu_buffer_rsrc_t p, int off, int col0, int c, int g, float4 (&wb)[2][16]) {
+  const int v = 4 * ((col0 + c) * MLP_HID + 4 * g);
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const u32x4m x = __builtin_amdgcn_raw_buffer_load_b128(p, v, 4 * (off + 16 * t * MLP_HID) + 64 * s, 0);
+      wb[t][s] = __builtin_bit_cast(float4, x);
+    }
+}
+// B of dZ W: columns col0 + 2 c + t (one 8-byte load serves both tiles at one k)
+__device__ __forceinline__ void mr_load_bwd(__amdgpu_buffer_rsrc_t p, int off, int col0, int c, int g, float4 (&wb)[2][16]) {
+  const int v = 4 * (4 * g * MLP_HID + col0 + 2 * c);
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    float2 x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      x[e] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(p, v, 4 * (off + (16 * s + e) * MLP_HID), 0));
+    wb[0][s] = make_float4(x[0].x, x[1].x, x[2].x, x[3].x);
+    wb[1][s] = make_float4(x[0].y, x[1].y, x[2].y, x[3].y);
+  }
+}
+
+// TRAIN: loss, row-local gradients and their column sums over the block's rows.  Otherwise the
+// de-normalised prediction from raw inputs.
+template <bool TRAIN>
+__global__ __launch_bounds__(512) void k_mlp_rows(MlpRowArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float mr_sh[];
+  float* HA = mr_sh;
+  float* HB = HA + MR_ROWS * MR_LD;
+  float* D1 = HB + MR_ROWS * MR_LD;      // TRAIN only: silu'(z) of the three layers
+  float* D2 = D1 + MR_ROWS * MR_LD;
+  float* D3 = D2 + MR_ROWS * MR_LD;
+  __shared__ float Xs[MR_ROWS][4], ys[MR_ROWS], dys[MR_ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int col0 = 32 * w, tc = tid & 255, half = tid >> 8;   // MFMA columns; column and row parity of the elementwise steps
+  const float* __restrict__ p = a.p;
+  const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, MLP_NPARAM * 4, 0x00020000);
+  const float4 w1 = *(const float4*)&p[MLP_OFF_W1 + 4 * tc];
+  const float b1 = p[MLP_OFF_B1 + tc], w4 = p[MLP_OFF_W4 + tc];
+  float s_b1 = 0.f, s_b2 = 0.f, s_b3 = 0.f, s_w4 = 0.f, s_w1[4] = {0.f, 0.f, 0.f, 0.f}, s_dy = 0.f;
+  double s_loss = 0.0;
+  const int ngroups = (a.n + MR_ROWS - 1) / MR_ROWS;
+  for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+    const int r0 = grp * MR_ROWS;
+    float4 wb[2][16];
+    mr_load_fwd(pr, MLP_OFF_W2, col0, c, g, wb);
+    if (tid < 4 * MR_ROWS) {
+      const int r = r0 + (tid >> 2), k = tid & 3;
+      float x = r < a.n ? a.X[(size_t)r * 4 + k] : 0.f;
+      if (!TRAIN) x = (x - a.norm[k]) / a.norm[4 + k];
+      Xs[tid >> 2][k] = x;
     }
     __syncthreads();
+    // layer 1
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
+    for (int i = 0; i < MR_ROWS / 2; ++i) {
+      const int r = half + 2 * i;
+      const float z = fmaf(Xs[r][3], w1.w, fmaf(Xs[r][2], w1.z, fmaf(Xs[r][1], w1.y, Xs[r][0] * w1.x))) + b1;
+      const float h = silu(z);
+      HA[r * MR_LD + tc] = h;
+      if (TRAIN) {
+        D1[r * MR_LD + tc] = dsilu(z);
+        if (r0 + r < a.n) a.H1[(size_t)(r0 + r) * MLP_HID + tc] = h;
+      }
+    }
+    __syncthreads();
+    // layers 2 (HA -> HB) and 3 (HB -> HA)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty + 16 * i];
+    for (int l = 0; l < 2; ++l) {
+      f32x4m acc[2] = {};
+      mr_mm(l ? HB : HA, wb, c, g, acc);
+      __builtin_amdgcn_sched_barrier(0);   // the next layer's weights reuse these registers
+      if (l == 0) mr_load_fwd(pr, MLP_OFF_W3, col0, c, g, wb);
+      else if (TRAIN) mr_load_bwd(pr, MLP_OFF_W3, col0, c, g, wb);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx + 16 * j];
+      for (int t = 0; t < 2; ++t) {
+        const int col = col0 + 16 * t + c;
+        const float b = p[(l ? MLP_OFF_B3 : MLP_OFF_B2) + col];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = 4 * g + i;
+          const float z = acc[t][i] + b;
+          const float h = silu(z);
+          (l ? HA : HB)[r * MR_LD + col] = h;
+          if (TRAIN) {
+            (l ? D3 : D2)[r * MR_LD + col] = dsilu(z);
+            if (l == 0 && r0 + r < a.n) a.H2[(size_t)(r0 + r) * MLP_HID + col] = h;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    // output: wave w sums rows 2 w and 2 w + 1
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * w + i;
+      const float4 h = *(const float4*)&HA[r * MR_LD + 4 * lane], v = *(const float4*)&p[MLP_OFF_W4 + 4 * lane];
+      float s = fmaf(h.w, v.w, fmaf(h.z, v.z, fmaf(h.y, v.y, h.x * v.x)));
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      const float y = s + p[MLP_OFF_B4];
+      if (lane == 0) {
+        if (TRAIN) {
+          const float d = r0 + r < a.n ? y - a.t[r0 + r] : 0.f;
+          ys[r] = d;
+          dys[r] = 2.0f * d / (float)a.n;
+        } else if (r0 + r < a.n) {
+          a.y[r0 + r] = a.norm[8] + a.norm[9] * y;
+        }
+      }
+    }
+    __syncthreads();
+    if constexpr (!TRAIN) continue;
+    // dZ3 = dy w4 silu'(z3) into HB; sums of dy H3, dy and the squared residuals
+#pragma unroll
+    for (int i = 0; i < MR_ROWS / 2; ++i) {
+      const int r = half + 2 * i;
+      const float dy = dys[r], dz = dy * w4 * D3[r * MR_LD + tc];
+      s_w4 = fmaf(dy, HA[r * MR_LD + tc], s_w4);
+      s_b3 += dz;
+      HB[r * MR_LD + tc] = dz;
+      if (r0 + r < a.n) a.dZ3[(size_t)(r0 + r) * MLP_HID + tc] = dz;
+    }
+    if (tid == 0)
+      for (int r = 0; r < MR_ROWS; ++r) {
+        s_loss += (double)ys[r] * ys[r];
+        s_dy += dys[r];
+      }
+    __syncthreads();
+    // dZ2 = (dZ3 W3) silu'(z2) into HA, dZ1 = (dZ2 W2) silu'(z1) into HB
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+      f32x4m acc[2] = {};
+      mr_mm(l ? HA : HB, wb, c, g, acc);
+      __builtin_amdgcn_sched_barrier(0);
+      if (l == 0) mr_load_bwd(pr, MLP_OFF_W2, col0, c, g, wb);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 4 * g + i, col = col0 + 2 * c;
+        const float2 d = *(const float2*)&(l ? D1 : D2)[r * MR_LD + col];
+        const float2 dz = make_float2(acc[0][i] * d.x, acc[1][i] * d.y);
+        *(float2*)&(l ? HB : HA)[r * MR_LD + col] = dz;
+        if (l == 0 && r0 + r < a.n) *(float2*)&a.dZ2[(size_t)(r0 + r) * MLP_HID + col] = dz;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < MR_ROWS / 2; ++i) {
+        const int r = half + 2 * i;
+        const float dz = (l ? HB : HA)[r * MR_LD + tc];
+        if (l == 0) {
+          s_b2 += dz;
+        } else {
+          s_b1 += dz;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) s_w1[k] = fmaf(dz, Xs[r][k], s_w1[k]);
+        }
+      }
+    }
+    __syncthreads();   // Xs and the LDS rows are free for the next group
+  }
+  if constexpr (TRAIN) {
+    float* q = a.vpart + (size_t)(2 * blockIdx.x + half) * MR_PART;
+    *(float4*)&q[4 * tc] = make_float4(s_w1[0], s_w1[1], s_w1[2], s_w1[3]);
+    q[1024 + tc] = s_b1;
+    q[1280 + tc] = s_b2;
+    q[1536 + tc] = s_b3;
+    q[1792 + tc] = s_w4;
+    if (tid == 0) {
+      a.lpart[2 * blockIdx.x] = s_loss;
+      a.lpart[2 * blockIdx.x + 1] = (double)s_dy;
+    }
+  }
+}
+
+// Weight gradients dW3 = dZ3^T H2 (blockIdx.y = 1) and dW2 = dZ2^T H1 (0): 64 x 64 block tiles
+// (blockIdx.x), rows split over blockIdx.z and, four at a time, over the block's waves, each of
+// which forms the whole tile (one 16-byte load of either operand serves four 16-wide tiles, 16 MFMAs
+// per load pair); the waves' tiles are added through LDS.
+__global__ __launch_bounds__(256) void k_mlp_wgrad(MlpRowArgs a, int chunk) {
+  __shared__ __attribute__((aligned(16))) float red[4][64 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int i0 = (blockIdx.x & 3) * 64, j0 = (blockIdx.x >> 2) * 64;
+  const float* __restrict__ Z = (blockIdx.y ? a.dZ3 : a.dZ2) + i0 + 4 * c;
+  const float* __restrict__ H = (blockIdx.y ? a.H2 : a.H1) + j0 + 4 * c;
+  const int kb = blockIdx.z * chunk, ke = min(a.n, kb + chunk);
+  f32x4m acc[4][4] = {};
+  constexpr int U = 4;   // steps of 16 rows in flight
+  for (int k0 = kb + 4 * w + g; k0 - g < ke; k0 += 16 * U) {
+    float4 x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = k0 + 16 * u;
+      x[u] = y[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < ke) {
+        x[u] = *(const float4*)&Z[(size_t)r * MLP_HID];
+        y[u] = *(const float4*)&H[(size_t)r * MLP_HID];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float av[4] = {x[u].x, x[u].y, x[u].z, x[u].w}, bv[4] = {y[u].x, y[u].y, y[u].z, y[u].w};
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty + 16 * i;
-    if (m >= g.M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      if (n >= g.N) continue;
-      float v = acc[i][j];
-      if (gridDim.z > 1) {
-        g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
-        continue;
-      }
-      const size_t o = (size_t)m * g.ldc + n;
-      if (EPI == EPI_BIAS_SILU) {
-        const float z = v + g.bias[n];
-        g.Z[o] = z;
-        g.C[o] = silu(z);
-      } else if (EPI == EPI_DSILU) {
-        g.C[o] = v * dsilu(g.Zin[o]);
-      } else if (EPI == EPI_BIAS) {
-        g.C[o] = v + g.bias[n];
-      } else {
-        g.C[o] = v;
-      }
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
     }
   }
-}
-
-// C[m][n] = sum over splits of part[s][m][n] (fixed order).
-__global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs g, int splits) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long tot = (long long)g.M * g.N;
-  if (e >= tot) return;
-  float s = 0.f;
-  for (int z = 0; z < splits; ++z) s += g.part[(size_t)z * tot + e];
-  const int m = (int)(e / g.N), n = (int)(e - (long long)m * g.N);
-  g.C[(size_t)m * g.ldc + n] = s;
-}
-
-// out[c] = sum_r X[r][c] for each column (bias gradients).
-__global__ __launch_bounds__(256) void k_colsum(const float* __restrict__ X, int rows, int cols, float* __restrict__ out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += X[(size_t)r * cols + c];
-  out[c] = s;
-}
-
-// dy = 2 (y - t) / B, loss = mean (y - t)^2 (FP64 sum, one block).
-__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const float* __restrict__ t, int B,
-                                              float* __restrict__ dy, double* __restrict__ loss) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < B; i += 256) {
-    const float r = y[i] - t[i];
-    dy[i] = 2.0f * r / (float)B;
-    s += (double)r * r;
-  }
-  red[threadIdx.x] = s;
+  // tile (i, j) element q of the lane: row 4 (4 g + q) + i, column 4 c + j
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *(float4*)&red[w][(4 * (4 * g + q) + i) * 64 + 4 * c] = make_float4(acc[i][0][q], acc[i][1][q], acc[i][2][q], acc[i][3][q]);
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+  float* out = a.wpart + ((size_t)blockIdx.z * 2 + blockIdx.y) * MLP_HID * MLP_HID;
+  for (int e = tid; e < 64 * 16; e += 256) {
+    const int r = e >> 4, q = (e & 15) * 4;
+    float4 s = *(const float4*)&red[0][r * 64 + q];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      const float4 v = *(const float4*)&red[k][r * 64 + q];
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    *(float4*)&out[(size_t)(i0 + r) * MLP_HID + j0 + q] = s;
   }
-  if (threadIdx.x == 0) *loss = red[0] / (double)B;
+}
+
+// The gradient from the partials, each in a fixed order: W2 and W3 over the row splits (blocks 0 ..
+// 511, an element a thread), W1, b1, b2, b3 and w4 over the row blocks' halves (64 blocks of 32
+// elements, eight interleaved runs each), b4 and the loss in the last block.
+__global__ __launch_bounds__(256) void k_mlp_reduce(MlpRowArgs a, int splits, int nblk, float* __restrict__ grad,
+                                                    double* __restrict__ loss) {
+  const int b = blockIdx.x, tid = threadIdx.x;
+  if (b < 512) {
+    const int e = b * 256 + tid;   // W2 then W3
+    float v[MLP_MAX_SPLITS], s = 0.f;   // every split's load in flight
+#pragma unroll
+    for (int z = 0; z < MLP_MAX_SPLITS; ++z) v[z] = z < splits ? a.wpart[(size_t)z * 2 * MLP_HID * MLP_HID + e] : 0.f;
+#pragma unroll
+    for (int z = 0; z < MLP_MAX_SPLITS; ++z) s += v[z];
+    grad[e < MLP_HID * MLP_HID ? MLP_OFF_W2 + e : MLP_OFF_W3 + e - MLP_HID * MLP_HID] = s;
+  } else if (b < 576) {
+    __shared__ float red[8][32];
+    const int e = (b - 512) * 32 + (tid & 31), q = tid >> 5;
+    float s = 0.f;
+    for (int k = q; k < 2 * nblk; k += 64) {   // eight loads in flight
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = k + 8 * u < 2 * nblk ? a.vpart[(size_t)(k + 8 * u) * MR_PART + e] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    red[q][tid & 31] = s;
+    __syncthreads();
+    if (q == 0) {
+      for (int k = 1; k < 8; ++k) s += red[k][tid];
+      const int o = e < 1280 ? e : e < 1536 ? MLP_OFF_B2 + e - 1280 : e < 1792 ? MLP_OFF_B3 + e - 1536 : MLP_OFF_W4 + e - 1792;
+      grad[o] = s;   // W1 and b1 lie first in both layouts
+    }
+  } else {
+    __shared__ double rl[256], rd[256];
+    double l = 0.0, d = 0.0;
+    for (int k = tid; k < nblk; k += 256) { l += a.lpart[2 * k]; d += a.lpart[2 * k + 1]; }
+    rl[tid] = l;
+    rd[tid] = d;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (tid < w) { rl[tid] += rl[tid + w]; rd[tid] += rd[tid + w]; }
+      __syncthreads();
+    }
+    if (tid == 0) {
+      *loss = rl[0] / (double)a.n;
+      grad[MLP_OFF_B4] = (float)rd[0];
+    }
+  }
 }
 
 // Adam with bias correction at step k = ts->step + 1 and learning rate
@@ -218,13 +415,6 @@ __global__ __launch_bounds__(256) void k_normalise(const float* __restrict__ X, 
 #pragma unroll
   for (int c = 0; c < 4; ++c) Xn[(size_t)i * 4 + c] = (X[(size_t)i * 4 + c] - norm[c]) / norm[4 + c];
   if (t && tn) tn[i] = (t[i] - norm[8]) / norm[9];
-}
-
-// y = mu_t + s_t y'
-__global__ __launch_bounds__(256) void k_denorm(const float* __restrict__ yn, int n, const float* __restrict__ norm,
-                                                float* __restrict__ y) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) y[i] = norm[8] + norm[9] * yn[i];
 }
 
 // theta_j = a_j (2 u_j - 1), u_j the 24-bit uniform of word j % 4 of Philox4x64-10 block j / 4 under
@@ -365,32 +555,21 @@ __global__ __launch_bounds__(256) void k_var_cube(int n, int nh, int nc, int sma
 }  // namespace
 
 // ---------------------------------------------------------------- launchers
-void launch_gemm(const GemmArgs& g0, bool ta, bool tb, int epi, int splits, hipStream_t s) {
-  GemmArgs g = g0;
-  if (splits < 1) splits = 1;
-  g.kchunk = ((g.K + splits - 1) / splits + 15) / 16 * 16;
-  splits = (g.K + g.kchunk - 1) / g.kchunk;
-  if (splits < 1) splits = 1;
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, splits);
-#define GEMM_CASE(TA_, TB_, E_) \
-  if (ta == TA_ && tb == TB_ && epi == E_) { hipLaunchKernelGGL((k_gemm<TA_, TB_, E_>), grid, dim3(256), 0, s, g); }
-  GEMM_CASE(false, true, EPI_BIAS_SILU)
-  GEMM_CASE(false, true, EPI_BIAS)
-  GEMM_CASE(false, false, EPI_DSILU)
-  GEMM_CASE(true, false, EPI_NONE)
-  GEMM_CASE(false, true, EPI_NONE)
-#undef GEMM_CASE
-  if (splits > 1) {
-    const long long tot = (long long)g.M * g.N;
-    hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, g, splits);
-  }
+// LDS of k_mlp_rows: two activation buffers, and the three of silu' when training
+static size_t mr_lds(bool train) { return (train ? 5 : 2) * (size_t)MR_ROWS * MR_LD * sizeof(float); }
+int mlp_row_blocks(int n) { return std::min((n + MR_ROWS - 1) / MR_ROWS, MR_MAX_BLOCKS); }
+void launch_mlp_predict(const MlpRowArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(k_mlp_rows<false>, dim3(mlp_row_blocks(a.n)), dim3(512), mr_lds(false), s, a);
 }
-
-void launch_colsum(const float* X, int rows, int cols, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_colsum, dim3((cols + 255) / 256), dim3(256), 0, s, X, rows, cols, out);
-}
-void launch_loss(const float* y, const float* t, int B, float* dy, double* loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, s, y, t, B, dy, loss);
+void launch_mlp_loss_grad(const MlpRowArgs& a, float* grad, double* loss, hipStream_t s) {
+  const int nblk = mlp_row_blocks(a.n);
+  (void)hipFuncSetAttribute((const void*)k_mlp_rows<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mr_lds(true));
+  hipLaunchKernelGGL(k_mlp_rows<true>, dim3(nblk), dim3(512), mr_lds(true), s, a);
+  // 32 tiles: enough row splits for one block a CU, at least 64 rows each
+  const int want = std::max(1, std::min(MLP_MAX_SPLITS, (a.n + 63) / 64));
+  const int chunk = ((a.n + want - 1) / want + 15) / 16 * 16, splits = (a.n + chunk - 1) / chunk;
+  hipLaunchKernelGGL(k_mlp_wgrad, dim3(16, 2, splits), dim3(256), 0, s, a, chunk);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(577), dim3(256), 0, s, a, splits, nblk, grad, loss);
 }
 void launch_adam(float* p, const float* g, float* m, float* v, int n, const TrainState* ts, hipStream_t s) {
   hipLaunchKernelGGL(k_adam, dim3((n + 255) / 256), dim3(256), 0, s, p, g, m, v, n, ts);
@@ -404,9 +583,6 @@ void launch_fit_norm(const float* X, const float* t, int n, float* norm, hipStre
 }
 void launch_normalise(const float* X, const float* t, int n, const float* norm, float* Xn, float* tn, hipStream_t s) {
   hipLaunchKernelGGL(k_normalise, dim3((n + 255) / 256), dim3(256), 0, s, X, t, n, norm, Xn, tn);
-}
-void launch_denorm(const float* yn, int n, const float* norm, float* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_denorm, dim3((n + 255) / 256), dim3(256), 0, s, yn, n, norm, y);
 }
 void launch_mlp_init(float* p, unsigned long long seed, hipStream_t s) {
   const int nblk = (MLP_NPARAM + 3) / 4;
