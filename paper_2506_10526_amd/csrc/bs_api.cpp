@@ -986,33 +986,37 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
   HIPCHK(c, hipMemcpyAsync(d_nu1, nu1.data(), nu1.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
   const long long nrows = (long long)n_nu1 * nc;
   const size_t per_tri = (size_t)nrows * nc * 8;
-  // number of pixel chunks: enough blocks to fill the chip, chunks of >= 1024 pixels
-  const int tm = fp64 ? 64 : 128, tn = fp64 ? 64 : 128;
-  long long tiles_per_tri = ((nrows + tm - 1) / tm) * ((nc + tn - 1) / tn);
+  // number of pixel chunks: enough blocks to fill the chip, chunks of at least `least` pixels
+  auto pixel_chunks = [&](long long blocks, int least) {
+    int k = 1;
+    while (blocks * k < 2048 && Ppix / (k * 2) >= least && (Ppix / (k * 2)) % 32 == 0) k *= 2;
+    // BS_MABS_KCHUNKS (tests): a fixed pixel-chunk count, so that small GEMMs run the long chunks of
+    // large ones (used only if it splits the pixels into multiples of 32)
+    if (const char* ek = getenv("BS_MABS_KCHUNKS")) {
+      const int e = atoi(ek);
+      if (e >= 1 && Ppix % e == 0 && (Ppix / e) % 32 == 0) k = e;
+    }
+    return k;
+  };
   const size_t budget = (size_t)8 << 30;
   int tb = (int)std::max<size_t>(1, std::min<size_t>(ntri, budget / std::max<size_t>(per_tri, 1)));
-  long long blocks_batch = tiles_per_tri * tb;
-  int kchunks = 1;
-  while (blocks_batch * kchunks < 2048 && Ppix / (kchunks * 2) >= 1024 && (Ppix / (kchunks * 2)) % 32 == 0) kchunks *= 2;
-  // BS_MABS_KCHUNKS (tests): a fixed pixel-chunk count, so that small GEMMs run the long chunks of
-  // large ones (used only if it splits the pixels into multiples of 32)
-  if (const char* ek = getenv("BS_MABS_KCHUNKS")) {
-    const int k = atoi(ek);
-    if (k >= 1 && Ppix % k == 0 && (Ppix / k) % 32 == 0) kchunks = k;
-  }
-  int kchunk = Ppix / kchunks;
+  MabsGemmArgs shape{};
+  shape.nc = nc; shape.n_nu1 = n_nu1; shape.ntri = tb;
+  const int kchunks64 = pixel_chunks(mabs_f64_blocks(shape), 512);
+  const int kchunks = fp64 ? kchunks64 : pixel_chunks(((nrows + 127) / 128) * ((nc + 127) / 128) * tb, 1024);
+  const int kchunk = Ppix / kchunks, kchunk64 = Ppix / kchunks64;
   if (!separable) {
     // per-channel count fields, FP64 GEMM: chains of kchunk products, then the chunk sums
-    c->last_count_bound = ring_count_bound(P, tri, (double)kchunk + (double)kchunks + 4.0);
+    c->last_count_bound = ring_count_bound(P, tri, (double)kchunk64 + (double)kchunks64 + 4.0);
     if (!(c->last_count_bound < 0.5))
       return ctx_fail(c, BS_ECOUNT, "triangle counts cannot be certified at this size (FP64 error bound " +
                                         std::to_string(c->last_count_bound) + " >= 1/2)");
   }
   // the batch must hold kchunks partial copies
-  tb = (int)std::max<size_t>(1, std::min<size_t>(ntri, budget / std::max<size_t>(per_tri * kchunks, 1)));
+  tb = (int)std::max<size_t>(1, std::min<size_t>(ntri, budget / std::max<size_t>(per_tri * std::max(kchunks, separable ? 1 : kchunks64), 1)));
   double* S = (double*)ctx_ws(c, "mabs_S", per_tri * kchunks * tb);
   double* Sc = nullptr;
-  if (!separable) Sc = (double*)ctx_ws(c, "mabs_Sc", per_tri * kchunks * tb);
+  if (!separable) Sc = (double*)ctx_ws(c, "mabs_Sc", per_tri * kchunks64 * tb);
   if (!S || (!separable && !Sc)) return ctx_fail(c, BS_ENOMEM, "workspace (partial sums)");
   const int D = collapse == 1 ? 2 * nc - 1 : nc;
   const size_t out_per_tri = collapse ? (size_t)D * D : (size_t)nrows * nc;
@@ -1041,13 +1045,14 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
       gc.F = nullptr; gc.Fh = gc.Fl = nullptr;
       gc.F64 = I64;
       gc.S = Sc;
+      gc.kchunk = kchunk64; gc.kchunks = kchunks64;
       launch_mabs_gemm_f64(gc, c->stream);
       LAUNCHCHK(c, "count contraction kernel");
     }
     if (!collapse) {
       MabsFinalArgs f{};
       f.S = S; f.kchunks = kchunks;
-      f.Sc = Sc; f.kchunks_c = kchunks;
+      f.Sc = Sc; f.kchunks_c = kchunks64;
       f.Tperp = d_tperp ? d_tperp + t0 : nullptr;
       f.chw = separable && w ? w->chan_w : nullptr;
       f.nu1 = d_nu1;
@@ -1061,7 +1066,7 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
     } else {
       MabsCollapseArgs f{};
       f.S = S; f.kchunks = kchunks;
-      f.Sc = Sc; f.kchunks_c = kchunks;
+      f.Sc = Sc; f.kchunks_c = kchunks64;
       f.Tperp = d_tperp ? d_tperp + t0 : nullptr;
       f.chw = separable && w ? w->chan_w : nullptr;
       f.nc = nc; f.ntri = nt; f.circular = collapse == 2;

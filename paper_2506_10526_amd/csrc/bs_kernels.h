@@ -100,6 +100,7 @@ int mabs_split_blocks(const MabsGemmArgs& a);
 void launch_mabs_gemm_split_grouped(const MabsGemmArgs* groups_dev, const int* offs_dev, int ngroups, int nblocks,
                                     hipStream_t s);
 void launch_mabs_gemm_f64(const MabsGemmArgs& a, hipStream_t s);
+long long mabs_f64_blocks(const MabsGemmArgs& a);   // blocks of that launch with one pixel chunk
 // Persistent split-BF16 contraction over ngroups GEMMs of one tile kind (0: 128 x 256 tiles,
 // 1: 256 x 192 tiles over nu1 x nu2 row blocks of tile_m1 x 256/tile_m1).  qoff[x][g] (x < 8, g <=
 // ngroups) is the prefix over groups of the tiles that queue x holds: per = tiles/8 of group g,

@@ -1310,65 +1310,111 @@ __global__ void k_zero_i32(int* p, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// FP64 contraction on the vector ALUs (data in BS_FP64 mode, counts for per-cell N_g).
-// 64 x 64 tile, 256 threads, 4 x 4 outputs per thread (strided by 16), K staged by 16.
+// FP64 contraction (data in BS_FP64 mode, counts for per-cell N_g) on FP64 MFMA, whose peak is the
+// vector FP64 peak: what it buys is operand traffic.  A wave owns TI nu1 x 16 nu2 rows by 16 CT nu3
+// columns (TI x CT tiles of mfma_f64_16x16x4); the four waves lie WI x 4/WI along (nu1, nu2).  Only the
+// raw field rows (TI WI of F_b1, 64 / WI of F_b2, 16 CT of F_b3, at most 130) are staged in LDS, 16
+// pixels a stage, two stages, the next one's loads in flight under the MFMAs; F1 F2 is one product
+// per lane at the fragment read, F1 being a broadcast.  Lane group g takes pixels 4 g .. 4 g + 3 of a
+// stage, one per MFMA step, on both operands; rows of 18 doubles put 16 rows' 16-byte reads on distinct
+// banks.  Bound: FP64 issue.  Measured against 64 x 64 tiles with both A rows loaded per element: counts
+// of 96^2 x 48 channels, 6 rings 3825 -> 1487 us (55 TFLOP/s; a large FP64 matrix product reaches 73 on this
+// card); 64^2 x 16, 8 rings, whose 16 columns filled a quarter of a tile, 420 -> 71 us.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_mabs_gemm_f64(MabsGemmArgs a) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ double sA[BK][BM + 1];
-  __shared__ double sB[BK][BN + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int nrows = a.n_nu1 * a.nc;
-  const int col0 = blockIdx.x * BN, row0 = blockIdx.y * BM;
-  const int t = blockIdx.z / a.kchunks;
-  const int kc = blockIdx.z - t * a.kchunks;
-  const int b1 = a.tri[3 * t], b2 = a.tri[3 * t + 1], b3 = a.tri[3 * t + 2];
-  const int kbeg = kc * a.kchunk;
-  const int kend = min(a.P, kbeg + a.kchunk);
-  double acc[4][4];
+typedef double f64x4m __attribute__((ext_vector_type(4)));
+constexpr int G64_K = 16, G64_LD = G64_K + 2;
+
+template <int TI, int CT>
+__global__ __launch_bounds__(256) void k_mabs_gemm_f64(MabsGemmArgs a, int WI) {
+  constexpr int MAXROWS = (TI == 2 ? 66 : 65) + 16 * CT, PASSES = (MAXROWS + 31) / 32;
+  __shared__ __attribute__((aligned(16))) double sh[2][MAXROWS * G64_LD];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int WJ = 4 / WI, wi = w & (WI - 1), wj = w / WI;
+  const int NI = TI * WI, NJ = 16 * WJ, NR = NI + NJ + 16 * CT;
+  const int ni = (a.n_nu1 + NI - 1) / NI, nj = (a.nc + NJ - 1) / NJ, nct = (a.nc + 16 * CT - 1) / (16 * CT);
+  // column tiles fastest, then nu2, nu1, pixel chunk, triangle: one XCD's run shares its raw rows
+  int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int c0 = (b % nct) * 16 * CT; b /= nct;
+  const int j0 = (b % nj) * NJ; b /= nj;
+  const int i0 = (b % ni) * NI; b /= ni;
+  const int kc = b % a.kchunks, t = b / a.kchunks;
+  const int kbeg = kc * a.kchunk, kend = min(a.P, kbeg + a.kchunk);
+  // staging: eight threads a row, two pixels each, 32 rows a pass; rows past the channels are zero
+  const int kk = (tid & 7) * 2;
+  const double* src[PASSES];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    for (int e = tid; e < BM * BK; e += 256) {
-      int r = e / BK, k = e - r * BK;
-      int R = row0 + r;
-      double v = 0.0;
-      if (R < nrows && k0 + k < kend) {
-        int i = R / a.nc, nu2 = R - i * a.nc;
-        v = a.F64[(size_t)b1 * a.bin_stride + (size_t)a.nu1[i] * a.P + k0 + k] *
-            a.F64[(size_t)b2 * a.bin_stride + (size_t)nu2 * a.P + k0 + k];
-      }
-      sA[k][r] = v;
-      int c = r, nu3 = col0 + c;
-      double w = 0.0;
-      if (nu3 < a.nc && k0 + k < kend) w = a.F64[(size_t)b3 * a.bin_stride + (size_t)nu3 * a.P + k0 + k];
-      sB[k][c] = w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k) {
-      double av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = sA[k][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = sB[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
+  for (int q = 0; q < PASSES; ++q) {
+    const int r = (tid >> 3) + 32 * q;
+    src[q] = nullptr;
+    int bin = -1, ch = 0;
+    if (r < NI) { if (i0 + r < a.n_nu1) { bin = a.tri[3 * t]; ch = a.nu1[i0 + r]; } }
+    else if (r < NI + NJ) { if (j0 + r - NI < a.nc) { bin = a.tri[3 * t + 1]; ch = j0 + r - NI; } }
+    else if (r < NR) { if (c0 + r - NI - NJ < a.nc) { bin = a.tri[3 * t + 2]; ch = c0 + r - NI - NJ; } }
+    if (bin >= 0) src[q] = a.F64 + (size_t)bin * a.bin_stride + (size_t)ch * a.P + kk;
   }
+  double2 v[PASSES];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {   // the pixel count is even, so a pair is in or out whole
+      v[q] = make_double2(0.0, 0.0);
+      if (src[q] && k0 + kk < kend) v[q] = *(const double2*)(src[q] + k0);
+    }
+  };
+  auto store = [&](double* buf) {
+#pragma unroll
+    for (int q = 0; q < PASSES; ++q) {
+      const int r = (tid >> 3) + 32 * q;
+      if (r < NR) *(double2*)&buf[r * G64_LD + kk] = v[q];
+    }
+  };
+  f64x4m acc[TI][CT] = {};
+  load(kbeg);
+  store(sh[0]);
+  __syncthreads();
+  int cur = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += G64_K) {
+    const bool more = k0 + G64_K < kend;
+    if (more) load(k0 + G64_K);
+    const double* buf = sh[cur];
+    double f1[TI][4], f2[4], f3[CT][4];
+    auto frag = [&](int row, double (&f)[4]) {
+      const double2 x = *(const double2*)&buf[row * G64_LD + 4 * g], y = *(const double2*)&buf[row * G64_LD + 4 * g + 2];
+      f[0] = x.x; f[1] = x.y; f[2] = y.x; f[3] = y.y;
+    };
+#pragma unroll
+    for (int i = 0; i < TI; ++i) frag(TI * wi + i, f1[i]);
+    frag(NI + 16 * wj + c, f2);
+#pragma unroll
+    for (int j = 0; j < CT; ++j) frag(NI + NJ + 16 * j + c, f3[j]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const double av = f1[i][e] * f2[e];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, f3[j][e], acc[i][j], 0, 0, 0);
+      }
+    if (more) {
+      store(sh[cur ^ 1]);
+      __syncthreads();
+      cur ^= 1;
+    }
+  }
+  const int nrows = a.n_nu1 * a.nc;
   double* S = a.S + ((size_t)kc * a.ntri + t) * (size_t)nrows * a.nc;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TI; ++i) {
+    const int r1 = i0 + TI * wi + i;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int row = row0 + ty + 16 * i, col = col0 + tx + 16 * j;
-      if (row < nrows && col < a.nc) S[(size_t)row * a.nc + col] = acc[i][j];
+    for (int q = 0; q < 4; ++q) {   // element q of a lane: row g + 4 q
+      const int r2 = j0 + 16 * wj + g + 4 * q;
+#pragma unroll
+      for (int j = 0; j < CT; ++j) {
+        const int col = c0 + 16 * j + c;
+        if (r1 < a.n_nu1 && r2 < a.nc && col < a.nc) S[((size_t)r1 * a.nc + r2) * a.nc + col] = acc[i][j][q];
+      }
     }
+  }
 }
 
 // Few entries (n_nu1 nc x nc <= 64, e.g. one channel): a 64 x 64 tile would be almost all padding,
@@ -1617,12 +1663,45 @@ void launch_mabs_gemm_f32(const MabsGemmArgs& a, hipStream_t s) {
   }
   hipLaunchKernelGGL(k_mabs_gemm<1>, gemm_grid(a, TM, TN), dim3(256), 0, s, a);
 }
+// Tile of the FP64 contraction.  Column tiles of 16 CT: the CT in 1..4 with the least padded work, a
+// tile of few columns counted dearer for its staging per MFMA.  Two nu1 a wave where there are two, and as
+// many of the four waves along nu1 as have rows (the others take further nu2 rows).
+static void f64_tile(const MabsGemmArgs& a, int& ti, int& wi, int& ct) {
+  const int n16 = (a.nc + 15) / 16;
+  double best = 0.0;
+  ct = 0;
+  for (int k = 4; k >= 1; --k) {
+    const double cost = (double)((n16 + k - 1) / k * k) * (1.0 + 0.3 / k);
+    if (!ct || cost < best) { ct = k; best = cost; }
+  }
+  ti = a.n_nu1 >= 2 ? 2 : 1;
+  wi = a.n_nu1 >= 5 ? 4 : a.n_nu1 >= 3 ? 2 : 1;
+}
+long long mabs_f64_blocks(const MabsGemmArgs& a) {
+  if ((long long)a.n_nu1 * a.nc * a.nc <= 64) return (long long)a.n_nu1 * a.nc * a.nc * a.ntri;
+  int ti, wi, ct;
+  f64_tile(a, ti, wi, ct);
+  return (long long)((a.n_nu1 + ti * wi - 1) / (ti * wi)) * ((a.nc + 64 / wi - 1) / (64 / wi)) *
+         ((a.nc + 16 * ct - 1) / (16 * ct)) * a.ntri;
+}
+template <int TI>
+static void launch_gemm_f64_ct(const MabsGemmArgs& a, int wi, int ct, unsigned nb, hipStream_t s) {
+  if (ct == 1) hipLaunchKernelGGL((k_mabs_gemm_f64<TI, 1>), dim3(nb), dim3(256), 0, s, a, wi);
+  else if (ct == 2) hipLaunchKernelGGL((k_mabs_gemm_f64<TI, 2>), dim3(nb), dim3(256), 0, s, a, wi);
+  else if (ct == 3) hipLaunchKernelGGL((k_mabs_gemm_f64<TI, 3>), dim3(nb), dim3(256), 0, s, a, wi);
+  else hipLaunchKernelGGL((k_mabs_gemm_f64<TI, 4>), dim3(nb), dim3(256), 0, s, a, wi);
+}
 void launch_mabs_gemm_f64(const MabsGemmArgs& a, hipStream_t s) {
   const long long ents = (long long)a.n_nu1 * a.nc * a.nc;
-  if (ents <= 64)
+  if (ents <= 64) {
     hipLaunchKernelGGL(k_mabs_dot_f64, dim3((unsigned)ents, 1, a.ntri * a.kchunks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_mabs_gemm_f64, gemm_grid(a, 64, 64), dim3(256), 0, s, a);
+    return;
+  }
+  int ti, wi, ct;
+  f64_tile(a, ti, wi, ct);
+  const unsigned nb = (unsigned)(mabs_f64_blocks(a) * a.kchunks);
+  if (ti == 2) launch_gemm_f64_ct<2>(a, wi, ct, nb, s);
+  else launch_gemm_f64_ct<1>(a, wi, ct, nb, s);
 }
 void launch_tperp(const double* I, const int* tri, int ntri, int P, double npix2, double* Tsum, hipStream_t s) {
   if (ntri > 0) hipLaunchKernelGGL(k_tperp, dim3(ntri), dim3(256), 0, s, I, tri, P, npix2, Tsum);
