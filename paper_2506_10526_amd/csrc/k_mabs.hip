@@ -1464,20 +1464,29 @@ __global__ __launch_bounds__(256) void k_tperp(const double* __restrict__ I, con
   if (threadIdx.x == 0) Tsum[t] = npix2 * red[0];
 }
 
-// Rounds an FP64 triangle count and records |x - rint(x)| in *maxdev (bit pattern of a
-// non-negative double, so integer max == floating max; NaN maps above every finite value).
-__device__ __forceinline__ int64_t round_count(double x, unsigned long long* maxdev) {
+// Rounds an FP64 triangle count and keeps the largest |x - rint(x)| in dev (NaN counts as infinite).
+__device__ __forceinline__ int64_t round_count(double x, double& dev) {
   double r = rint(x);
   double d = fabs(x - r);
   if (d != d) d = __builtin_inf();
-  atomicMax(maxdev, (unsigned long long)__double_as_longlong(d));
+  dev = fmax(dev, d);
   return (int64_t)r;
+}
+// *maxdev = max(*maxdev, dev) over the threads (bit patterns of non-negative doubles, so integer
+// max == floating max).  One atomic a wave: an atomic per count, all on one address, was most of the
+// time of the kernels that round counts (each count is one subtraction and a rounding).
+__device__ __forceinline__ void record_dev(double dev, unsigned long long* maxdev) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) dev = fmax(dev, __shfl_xor(dev, o));
+  if ((threadIdx.x & 63) == 0) atomicMax(maxdev, (unsigned long long)__double_as_longlong(dev));
 }
 
 __global__ void k_round_counts(const double* __restrict__ x, int n, int64_t* __restrict__ out,
                                unsigned long long* bad) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = round_count(x[i], bad);
+  double dev = 0.0;
+  if (i < n) out[i] = round_count(x[i], dev);
+  record_dev(dev, bad);
 }
 
 __device__ __forceinline__ double sum_chunks(const double* S, int kchunks, size_t chunk_stride, size_t idx) {
@@ -1489,14 +1498,14 @@ __device__ __forceinline__ double sum_chunks(const double* S, int kchunks, size_
 __device__ __forceinline__ void mabs_entry(const double* S, int kchunks, const double* Sc, int kchunks_c,
                                            const int64_t* Tperp, const float* chw, int ntri, int nrows, int nc,
                                            int t, int R, int n1, int n2, int n3, double npix, double norm,
-                                           unsigned long long* bad, double& Bo, int64_t& No) {
+                                           double& dev, double& Bo, int64_t& No) {
   size_t chunk_stride = (size_t)ntri * nrows * nc;
   size_t idx = ((size_t)t * nrows + R) * nc + n3;
   double s = sum_chunks(S, kchunks, chunk_stride, idx);
   int64_t cnt;
   if (Sc) {
     double sc = sum_chunks(Sc, kchunks_c, chunk_stride, idx);
-    cnt = round_count(npix * npix * sc, bad);
+    cnt = round_count(npix * npix * sc, dev);
   } else {
     bool on = !chw || (chw[n1] > 0.f && chw[n2] > 0.f && chw[n3] > 0.f);
     cnt = on ? Tperp[t] : 0;
@@ -1508,6 +1517,7 @@ __device__ __forceinline__ void mabs_entry(const double* S, int kchunks, const d
 __global__ __launch_bounds__(256) void k_mabs_finalize(MabsFinalArgs a) {
   const int nrows = a.n_nu1 * a.nc;
   const size_t total = (size_t)a.ntri * nrows * a.nc;
+  double dev = 0.0;
   for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
     int n3 = (int)(e % a.nc);
     size_t rest = e / a.nc;
@@ -1517,10 +1527,11 @@ __global__ __launch_bounds__(256) void k_mabs_finalize(MabsFinalArgs a) {
     double b;
     int64_t c;
     mabs_entry(a.S, a.kchunks, a.Sc, a.kchunks_c, a.Tperp, a.chw, a.ntri, nrows, a.nc, t, R, a.nu1[i], n2, n3,
-               a.npix, a.norm, a.bad, b, c);
+               a.npix, a.norm, dev, b, c);
     a.B[e] = b;
     a.N[e] = c;
   }
+  if (a.Sc) record_dev(dev, a.bad);
 }
 
 // Ergodic collapse over a nu1 subset (unit channel weights): Bbar[t][d1'][d2'] is the mean of
@@ -1553,35 +1564,84 @@ __global__ __launch_bounds__(256) void k_mabs_collapse_subset(MabsSubsetArgs a) 
 }
 
 // Ergodic collapse: mean over valid nu3 of B(nu3 + d1, nu3 + d2, nu3) (rows R = nu1*nc + nu2).
+// Bound: the partial sums' one trip from HBM.  Outputs (d1, d2) of one d2 - d1 meet, at one nu1, on one
+// row (nu1, nu2 = nu1 + d2 - d1) and take consecutive nu3 = nu1 - d1, so threads run along d1 at fixed d2 -
+// d1 and the whole wave walks the same nu1: every read is a contiguous run (with d2 along the threads each
+// read was a row apart; 96^2 x 48 with per-cell counts, 6 rings: 1700 us that way with an atomic per count,
+// 190 us).  Order of a sum: nu1, which for the non-circular collapse is nu3 ascending.
+constexpr int COLL_U = 4;   // nu1 in flight
 __global__ __launch_bounds__(256) void k_mabs_collapse(MabsCollapseArgs a) {
   const int nc = a.nc;
   const int D = a.circular ? nc : 2 * nc - 1;
   const int nrows = nc * nc;
-  const size_t total = (size_t)a.ntri * D * D;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
-    int j2 = (int)(e % D);
-    size_t rest = e / D;
-    int j1 = (int)(rest % D);
-    int t = (int)(rest / D);
-    int d1 = a.circular ? j1 : j1 - (nc - 1);
-    int d2 = a.circular ? j2 : j2 - (nc - 1);
+  const size_t total = (size_t)a.ntri * D * D, cs = (size_t)a.ntri * nrows * nc;
+  double dev = 0.0;
+  // whole waves stay in the loop (the wave walks a common nu1 range)
+  for (size_t e0 = (size_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); e0 < total; e0 += (size_t)gridDim.x * blockDim.x) {
+    const size_t e = e0 + (threadIdx.x & 63);
+    const bool in = e < total;
+    const int j1 = (int)(e % D);
+    const size_t rest = e / D;
+    const int t = (int)(rest / D);
+    int j2 = j1 + (int)(rest % D);
+    if (j2 >= D) j2 -= D;
+    const int d1 = a.circular ? j1 : j1 - (nc - 1);
+    const int dd = a.circular ? j2 - j1 : j2 - (nc - 1) - d1;   // nu2 - nu1 (mod nc when circular)
+    int lo = 0, hi = in ? nc - 1 : -1;
+    if (in && !a.circular) {
+      lo = max(0, max(d1, -dd));
+      hi = min(nc - 1, min(nc - 1 + d1, nc - 1 - dd));
+    }
+    int wlo = lo <= hi ? lo : nc, whi = lo <= hi ? hi : -1;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      wlo = min(wlo, __shfl_xor(wlo, o));
+      whi = max(whi, __shfl_xor(whi, o));
+    }
     double acc = 0.0;
     int cnt = 0;
     int64_t tot = 0;
-    for (int n3 = 0; n3 < nc; ++n3) {
-      int n1 = n3 + d1, n2 = n3 + d2;
-      if (a.circular) { n1 %= nc; n2 %= nc; }
-      else if (n1 < 0 || n1 >= nc || n2 < 0 || n2 >= nc) continue;
-      double b;
-      int64_t c;
-      mabs_entry(a.S, a.kchunks, a.Sc, a.kchunks_c, a.Tperp, a.chw, a.ntri, nrows, nc, t, n1 * nc + n2, n1, n2,
-                 n3, a.npix, a.norm, a.bad, b, c);
-      if (c > 0) { acc += b; ++cnt; tot += c; }
+    for (int nb = wlo; nb <= whi; nb += COLL_U) {
+      double s[COLL_U], sc[COLL_U];
+      int m2[COLL_U], m3[COLL_U];
+#pragma unroll
+      for (int u = 0; u < COLL_U; ++u) {
+        const int n1 = nb + u;
+        int n2 = n1 + dd, n3 = n1 - d1;
+        if (a.circular) {
+          if (n2 < 0) n2 += nc;
+          if (n2 >= nc) n2 -= nc;
+          if (n3 < 0) n3 += nc;
+        }
+        m2[u] = n2;
+        m3[u] = n1 >= lo && n1 <= hi ? n3 : -1;
+        s[u] = sc[u] = 0.0;
+        if (m3[u] >= 0) {
+          const size_t idx = ((size_t)t * nrows + (size_t)n1 * nc + n2) * nc + n3;
+          s[u] = sum_chunks(a.S, a.kchunks, cs, idx);
+          if (a.Sc) sc[u] = sum_chunks(a.Sc, a.kchunks_c, cs, idx);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < COLL_U; ++u) {
+        if (m3[u] < 0) continue;
+        int64_t c;
+        if (a.Sc) c = round_count(a.npix * a.npix * sc[u], dev);
+        else c = !a.chw || (a.chw[nb + u] > 0.f && a.chw[m2[u]] > 0.f && a.chw[m3[u]] > 0.f) ? a.Tperp[t] : 0;
+        if (c > 0) {
+          acc += a.norm * a.npix * s[u] / (double)c;
+          ++cnt;
+          tot += c;
+        }
+      }
     }
-    a.B[e] = cnt ? acc / cnt : __builtin_nan("");
-    a.N[e] = tot;
-    a.Nnu[e] = cnt;
+    if (!in) continue;
+    const size_t o = ((size_t)t * D + j1) * D + j2;
+    a.B[o] = cnt ? acc / cnt : __builtin_nan("");
+    a.N[o] = tot;
+    a.Nnu[o] = cnt;
   }
+  if (a.Sc) record_dev(dev, a.bad);
 }
 
 }  // namespace
