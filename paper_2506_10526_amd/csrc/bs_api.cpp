@@ -226,56 +226,61 @@ extern "C" void bs_free_bins(bs_bins* b) {
 // ------------------------------------------------------------------ ring fields
 namespace {
 
-struct RingFieldLaunch {
-  int G, CB, RB;
-  size_t lds;
-};
-
-RingFieldLaunch ring_field_geometry(int n, int vmax, size_t esz) {
+// Fold of the FP32 column transform: the smallest G for which vmax + 1 columns of n / G values and two
+// 2048-value work buffers stay within 128 KB (1 up to n = 192 with the default support, 2 at 256).  It
+// splits a column over G blocks; what it fixes is the order of the FP32 roundings, which every FP32
+// and split-BF16 MABS inherits.  FP64 fields take G = 1: folding reads every cell G times.
+int ring_fold_f32(int n, int vmax) {
   const int ncols = vmax + 1, M = n / 2;
-  RingFieldLaunch r{};
+  int fold = 1;
   for (int G = 1; G <= n / 4; G *= 2) {
     if (n % G) break;
-    int Lc = n / G;
-    int CB = std::max(1, std::min(ncols, 2048 / Lc));
-    int RB = std::max(1, std::min(Lc, 2048 / M));
-    size_t work = std::max((size_t)CB * Lc, (size_t)RB * M);
-    size_t lds = esz * ((size_t)ncols * Lc + 2 * work);
-    r = {G, CB, RB, lds};
-    if (lds <= 128 * 1024) return r;
+    const int Lc = n / G;
+    const int CB = std::max(1, std::min(ncols, 2048 / Lc));
+    const int RB = std::max(1, std::min(Lc, 2048 / M));
+    fold = G;
+    if (8 * ((size_t)ncols * Lc + 2 * std::max((size_t)CB * Lc, (size_t)RB * M)) <= 128 * 1024) break;
   }
-  return r;
+  return fold;
 }
 
 }  // namespace
 
-// Arguments of the ring-field kernel for ring ids already on the device (no upload, no launch).
+// Arguments of the ring-field kernels for ring ids already on the device (no upload, no launch).
 int ring_fields_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, bool fp64, bool count_mode,
-                        bool ignore_chan, const int* d_bins, void* out, long long bin_stride, MabsFieldArgs& a,
-                        size_t& lds) {
+                        bool ignore_chan, const int* d_bins, void* out, long long bin_stride, MabsFieldArgs& a) {
   const auto& P = b->P;
   const int n = P.n;
   const void* tw = ctx_twiddle(c, n, fp64);
   if (!tw) return ctx_fail(c, BS_ENOMEM, "twiddle table");
-  RingFieldLaunch g = ring_field_geometry(n, P.vmax, fp64 ? 16 : 8);
-  if (g.lds > 160 * 1024) return ctx_fail(c, BS_EUNSUPPORTED, "ring field transform does not fit in LDS");
   a = MabsFieldArgs{};
   a.vis = nullptr;
   a.ng = w ? w->ng : nullptr;
   a.uvm = w ? w->uv_mask : nullptr;
   a.chw = w ? w->chan_w : nullptr;
-  a.lut = b->d_lut;
-  a.smax = P.smax;
   a.bins = d_bins;
+  // |U| grows with s, so a ring's cells are one range of s
+  for (int j = 0; j < 120; ++j) { a.ring_lo[j] = 1; a.ring_hi[j] = 0; a.ring_v[j] = -1; }
+  for (int s = 1; s <= P.smax; ++s) {
+    const int j = P.lut[s];
+    if (j < 0) continue;
+    if (a.ring_hi[j] < a.ring_lo[j]) a.ring_lo[j] = s;
+    a.ring_hi[j] = s;
+  }
+  for (int j = 0; j < P.nbins; ++j)
+    while (a.ring_v[j] < P.vmax && (a.ring_v[j] + 1) * (a.ring_v[j] + 1) <= a.ring_hi[j]) ++a.ring_v[j];
   a.n = n; a.nh = P.nh; a.nc = P.nc; a.vmax = P.vmax;
-  a.G = g.G; a.CB = g.CB; a.RB = g.RB;
+  a.G = fp64 ? 1 : ring_fold_f32(n, P.vmax);
+  // at most 2048 values a block: the in-place FFT's four butterflies a thread
+  a.CB = std::max(1, std::min(P.vmax + 1, 2048 / (n / a.G)));
+  a.RB = std::max(1, std::min(n, 2048 / (n / 2)));
   a.count_mode = count_mode ? 1 : 0;
   a.ignore_chan = ignore_chan ? 1 : 0;
   a.out = out;
   a.plane_stride = (long long)n * n;
   a.bin_stride = bin_stride;
   a.tw_n = tw;
-  a.pcol = make_fft_plan(n / g.G);
+  a.pcol = make_fft_plan(n / a.G);
   a.prow = make_fft_plan(n / 2);
   // smallest radices first (first-pass LDS writes spread over more banks; the same DFT)
   if (!getenv("BS_MABS_RADIX_DESC")) {
@@ -283,17 +288,16 @@ int ring_fields_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, bool f
     std::reverse(a.prow.rad, a.prow.rad + a.prow.nr);
   }
   a.scale = 1.0 / ((double)n * (double)n);
-  lds = g.lds;
   return BS_OK;
 }
 
-// Launches the ring-field kernel over `nblocks` rings and channels [0, nch) (grid.y <= 65535 each).
-void ring_fields_launch(MabsFieldArgs a, bool fp64, int nblocks, int nch, size_t lds, hipStream_t s) {
+// Launches the ring-field kernels over `nblocks` rings and channels [0, nch) (grid.y <= 65535 each).
+void ring_fields_launch(MabsFieldArgs a, bool fp64, int nblocks, int nch, hipStream_t s) {
   for (int c0 = 0; c0 < nch; c0 += 65535) {
     a.chan_offset = c0;
     int cn = std::min(65535, nch - c0);
-    if (fp64) launch_mabs_fields_f64(a, nblocks, cn, lds, s);
-    else launch_mabs_fields_f32(a, nblocks, cn, lds, s);
+    if (fp64) launch_mabs_fields_f64(a, nblocks, cn, s);
+    else launch_mabs_fields_f32(a, nblocks, cn, s);
   }
 }
 
@@ -308,11 +312,10 @@ int run_ring_fields(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weigh
   if (!d_bins) return ctx_fail(c, BS_ENOMEM, "workspace (ring ids)");
   HIPCHK(c, hipMemcpyAsync(d_bins, blocks.data(), blocks.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
   MabsFieldArgs a;
-  size_t lds = 0;
-  int rc = ring_fields_prepare(c, b, w, fp64, count_mode, ignore_chan, d_bins, out, bin_stride, a, lds);
+  int rc = ring_fields_prepare(c, b, w, fp64, count_mode, ignore_chan, d_bins, out, bin_stride, a);
   if (rc) return rc;
   a.vis = vis;
-  ring_fields_launch(a, fp64, (int)blocks.size(), nch, lds, c->stream);
+  ring_fields_launch(a, fp64, (int)blocks.size(), nch, c->stream);
   LAUNCHCHK(c, "ring field kernel");
   return BS_OK;
 }

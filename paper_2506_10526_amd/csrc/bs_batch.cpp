@@ -49,7 +49,6 @@ struct BCube {
   std::vector<int64_t> tperp;
   GenArgs ga{};
   MabsFieldArgs fa{};
-  size_t flds = 0;
   size_t off_vis = 0, off_g = 0, off_F = 0, off_Fh = 0, off_Fl = 0, off_S = 0;   // arena offsets
   double* Bbar = nullptr;
   int32_t* Nnu = nullptr;
@@ -165,7 +164,7 @@ void enqueue_front(const BCube& q, char* arena, hipStream_t s) {
   MabsFieldArgs fa = q.fa;
   fa.vis = arena + q.off_vis;
   fa.out = arena + q.off_F;
-  ring_fields_launch(fa, false, q.nbu, q.nc, q.flds, s);
+  ring_fields_launch(fa, false, q.nbu, q.nc, s);
   launch_split_bf16((const float*)(arena + q.off_F), (uint16_t*)(arena + q.off_Fh), (uint16_t*)(arena + q.off_Fl),
                     (long long)q.bytes_fields(), s);
 }
@@ -368,7 +367,7 @@ extern "C" int bs_batch_create(bs_ctx* c, const bs_batch_cube* cubes, int32_t nc
     launch_gen_amp(q.ga, c->stream);
     // ring-field kernel arguments (data), unit weights
     rc = ring_fields_prepare(c, q.bins, nullptr, false, false, false, q.d_blocks, nullptr, (long long)q.nc * q.n * q.n,
-                             q.fa, q.flds);
+                             q.fa);
     if (rc) return restore_fail(rc);
     // channel-independent counts T_perp = n^4 sum_p I1 I2 I3, certified like the MABS counts
     const double bound = ring_count_bound(q.bins->P, q.tri, (double)((q.n * q.n + 255) / 256) + 8.0);
@@ -382,10 +381,9 @@ extern "C" int bs_batch_create(bs_ctx* c, const bs_batch_cube* cubes, int32_t nc
       return restore_fail(ctx_fail(c, BS_ENOMEM, "count workspace"));
     }
     MabsFieldArgs ca;
-    size_t clds = 0;
-    rc = ring_fields_prepare(c, q.bins, nullptr, true, true, true, q.d_blocks, Ic, (long long)q.n * q.n, ca, clds);
+    rc = ring_fields_prepare(c, q.bins, nullptr, true, true, true, q.d_blocks, Ic, (long long)q.n * q.n, ca);
     if (!rc) {
-      ring_fields_launch(ca, true, q.nbu, 1, clds, c->stream);
+      ring_fields_launch(ca, true, q.nbu, 1, c->stream);
       const double P2 = (double)q.n * q.n * (double)q.n * q.n;
       launch_tperp(Ic, q.d_tri, q.ntri, q.n * q.n, P2, Ts, c->stream);
       q.d_tperp = (int64_t*)balloc(b, (size_t)q.ntri * 8);

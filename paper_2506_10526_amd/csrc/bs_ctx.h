@@ -76,6 +76,5 @@ bool fft_ip_fits(const FftPlan& p, int nl, int threads, int bmax);
 bool fft_len_ok(int L);
 struct MabsFieldArgs;
 int ring_fields_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, bool fp64, bool count_mode,
-                        bool ignore_chan, const int* d_bins, void* out, long long bin_stride, MabsFieldArgs& a,
-                        size_t& lds);
-void ring_fields_launch(MabsFieldArgs a, bool fp64, int nblocks, int nch, size_t lds, hipStream_t s);
+                        bool ignore_chan, const int* d_bins, void* out, long long bin_stride, MabsFieldArgs& a);
+void ring_fields_launch(MabsFieldArgs a, bool fp64, int nblocks, int nch, hipStream_t s);

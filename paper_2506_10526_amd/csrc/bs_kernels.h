@@ -16,10 +16,14 @@ struct MabsFieldArgs {
   const uint16_t* ng;       // per-cell counts or NULL
   const uint8_t* uvm;       // separable occupancy or NULL
   const float* chw;         // separable channel weights or NULL
-  const int8_t* lut;        // ring of s = qu^2 + qv^2, s <= smax
-  int smax;
   const int* bins;          // ring id per z block
-  int n, nh, nc, vmax, G, CB, RB;
+  // per ring id: its cells are the range lo <= s <= hi of s = qu^2 + qv^2 (empty: lo > hi) and reach
+  // column v (-1 when empty); by value, read as uniform scalars
+  int ring_lo[120], ring_hi[120];
+  short ring_v[120];
+  int n, nh, nc, vmax;
+  int G;                    // fold of the column transform: length n / G, G blocks per column tile
+  int CB, RB;               // columns, rows per block
   int count_mode;           // 0: W V, 1: unit indicator [N_g > 0]
   int chan_offset;          // first channel of this launch (grid.y indexes channels from here)
   int ignore_chan;          // count mode, separable: channel-independent indicator
@@ -89,8 +93,8 @@ struct MabsSubsetArgs {
 };
 void launch_mabs_collapse_subset(const MabsSubsetArgs& a, hipStream_t s);
 
-void launch_mabs_fields_f32(const MabsFieldArgs& a, int nbins, int nchan, size_t lds, hipStream_t s);
-void launch_mabs_fields_f64(const MabsFieldArgs& a, int nbins, int nchan, size_t lds, hipStream_t s);
+void launch_mabs_fields_f32(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s);
+void launch_mabs_fields_f64(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s);
 void launch_split_bf16(const float* F, uint16_t* hi, uint16_t* lo, long long n, hipStream_t s);
 void launch_mabs_gemm_split(const MabsGemmArgs& a, hipStream_t s);
 void launch_mabs_gemm_f32(const MabsGemmArgs& a, hipStream_t s);

@@ -14,22 +14,25 @@ namespace {
 __device__ __forceinline__ int signed_idx(int i, int n) { return i < (n + 1) / 2 ? i : i - n; }
 
 // ---------------------------------------------------------------------------
-// Ring-filtered field of one (ring, channel) plane.
+// Ring-filtered fields.
 //
-// X(u, v) = 1_ring(U) W(U, nu) V(U, nu) (or the unit indicator in count mode) on the
-// half plane is inverse-transformed to the real n x n field: a C2C pass along u for every
-// column v <= vmax that can hold support, then a C2R pass along v for every output row.
-// A block computes the output rows x_u = G m + g (m < n/G) of its plane; the u pass is
-// folded to length n/G so the columns fit in LDS:
-//   Y_v[u'] = sum_q X(u' + q n/G, v) e^{+2 pi i (u' + q n/G) g / n},  G_v[m] = IDFT_{n/G}(Y_v)[m].
+// X(u, v) = 1_ring(U) W(U, nu) V(U, nu) (or the unit indicator in count mode) on the half plane is
+// inverse-transformed to the real n x n field in two passes, as many small blocks each:
+//   columns (k_ring_cols): C2C along u of the columns v <= v_b that the ring reaches (v_b its radius;
+//     a tenth of the columns for the inner rings), folded to length n / G,
+//       Y_v[u'] = sum_q X(u' + q n/G, v) e^{+2 pi i (u' + q n/G) g / n},  G_v[m] = IDFT_{n/G}(Y_v)[m],
+//     x_u = G m + g; value (x_u, v) goes to complex element v of the field's own row x_u, which always
+//     holds v_b + 1 <= n / 2 of them, so the pass needs no workspace;
+//   rows (k_ring_rows): C2R along v, each row read into LDS and written over itself.
+// Bound: HBM, the rows' 4 n^2 bytes (FP32).  One block per (ring, channel, g) with the whole plane's columns in
+// LDS ran one block a CU: 10 rings x 192 channels x 256^2 FP32 1690 us, now 113 + 289; 768 channels 6720 us, now 435 + 1158.
 // ---------------------------------------------------------------------------
 template <typename T>
-__device__ __forceinline__ Cx<T> ring_cell(const MabsFieldArgs& a, int bin, int nu, int iu, int v) {
+__device__ __forceinline__ Cx<T> ring_cell(const MabsFieldArgs& a, int s_lo, int s_hi, int nu, int iu, int v) {
   const int n = a.n;
   int qu = signed_idx(iu, n);
   int s = qu * qu + v * v;
-  if (s == 0 || s > a.smax || qu == -n / 2) return cmk(T(0), T(0));
-  if (a.lut[s] != bin) return cmk(T(0), T(0));
+  if (s < s_lo || s > s_hi || qu == -n / 2) return cmk(T(0), T(0));
   size_t cell = ((size_t)nu * n + iu) * a.nh + v;
   size_t cell_uv = (size_t)iu * a.nh + v;
   T w;
@@ -51,76 +54,87 @@ __device__ __forceinline__ Cx<T> ring_cell(const MabsFieldArgs& a, int bin, int 
 }
 
 template <typename T>
-__device__ __forceinline__ Cx<T> ring_input(const MabsFieldArgs& a, int bin, int nu, int iu, int v) {
-  Cx<T> x = ring_cell<T>(a, bin, nu, iu, v);
+__device__ __forceinline__ Cx<T> ring_input(const MabsFieldArgs& a, int s_lo, int s_hi, int nu, int iu, int v) {
+  Cx<T> x = ring_cell<T>(a, s_lo, s_hi, nu, iu, v);
   if (v == 0) {  // self-conjugate column: (X(u) + conj X(-u)) / 2
     int ineg = (a.n - iu) % a.n;
-    Cx<T> y = ring_cell<T>(a, bin, nu, ineg, 0);
+    Cx<T> y = ring_cell<T>(a, s_lo, s_hi, nu, ineg, 0);
     x = cscale(cadd(x, cconj(y)), T(0.5));
   }
   return x;
 }
 
+// blockIdx.x = g + G (column tile), y = channel, z = ring
 template <typename T>
-__global__ __launch_bounds__(256) void k_mabs_fields(MabsFieldArgs a) {
+__global__ __launch_bounds__(256) void k_ring_cols(MabsFieldArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int g = blockIdx.x;
-  const int nu = a.chan_offset + blockIdx.y;
-  const int bi = blockIdx.z;
-  const int bin = a.bins[bi];
-  const int n = a.n, G = a.G, Lc = n / G, M = n / 2, ncols = a.vmax + 1;
-  const int tid = threadIdx.x;
-  const int work = (a.CB * Lc > a.RB * M) ? a.CB * Lc : a.RB * M;
-  Cx<T>* Rg = (Cx<T>*)smem_raw;
-  Cx<T>* wa = Rg + (size_t)ncols * Lc;
-  Cx<T>* wb = wa + work;
-  const Cx<T>* tw = (const Cx<T>*)a.tw_n;
-
-  // Phase 1: folded u pass over the columns v = 0..vmax.
-  for (int c0 = 0; c0 < ncols; c0 += a.CB) {
-    const int nb = min(a.CB, ncols - c0);
-    for (int e = tid; e < nb * Lc; e += blockDim.x) {
-      int cl = e / Lc, up = e - cl * Lc, v = c0 + cl;
-      Cx<T> acc = cmk(T(0), T(0));
-      for (int q = 0; q < G; ++q) {
-        int iu = up + q * Lc;
-        Cx<T> x = ring_input<T>(a, bin, nu, iu, v);
-        if (g) {
-          Cx<T> w = tw[(iu * g) % n];
-          w.y = -w.y;
-          x = cmul(x, w);
-        }
-        acc = cadd(acc, x);
+  const int n = a.n, G = a.G, Lc = n / G, ld = Lc + 1;
+  const int g = blockIdx.x % G, c0 = (blockIdx.x / G) * a.CB;
+  const int nu = a.chan_offset + blockIdx.y, bi = blockIdx.z, bin = a.bins[bi];
+  const int nb = min(a.CB, a.ring_v[bin] + 1 - c0);
+  if (nb <= 0) return;
+  const int s_lo = a.ring_lo[bin], s_hi = a.ring_hi[bin];
+  Cx<T>* A = (Cx<T>*)smem_raw;
+  Cx<T>* tw = A + (size_t)a.CB * ld;
+  for (int e = threadIdx.x; e < n; e += blockDim.x) tw[e] = ((const Cx<T>*)a.tw_n)[e];
+  if (G > 1) __syncthreads();   // the fold reads the table
+  // consecutive threads take consecutive v of one row
+  const float rnb = 1.0f / (float)nb;
+  for (int e = threadIdx.x; e < nb * Lc; e += blockDim.x) {
+    int up, cl;
+    fdivmod(e, nb, rnb, up, cl);
+    Cx<T> acc = cmk(T(0), T(0));
+    for (int q = 0; q < G; ++q) {
+      const int iu = up + q * Lc;
+      Cx<T> x = ring_input<T>(a, s_lo, s_hi, nu, iu, c0 + cl);
+      if (g) {
+        Cx<T> w = tw[(iu * g) % n];
+        w.y = -w.y;
+        x = cmul(x, w);
       }
-      wa[e] = acc;
+      acc = cadd(acc, x);
     }
-    __syncthreads();
-    Cx<T>* r = lds_fft<+1, T>(wa, wb, a.pcol, nb, tw, G);
-    for (int e = tid; e < nb * Lc; e += blockDim.x) Rg[(size_t)c0 * Lc + e] = r[e];
-    __syncthreads();
+    A[(size_t)cl * ld + up] = acc;
   }
-
-  // Phase 2: C2R along v for output rows x_u = G m + g.
+  __syncthreads();
+  lds_fft_ip<+1, T, 4>(A, a.pcol, nb, tw, G, ld);
   T* out = (T*)a.out + (size_t)bi * a.bin_stride + (size_t)nu * a.plane_stride;
+  for (int e = threadIdx.x; e < nb * Lc; e += blockDim.x) {
+    int m, cl;
+    fdivmod(e, nb, rnb, m, cl);
+    ((Cx<T>*)(out + (size_t)(G * m + g) * n))[c0 + cl] = A[(size_t)cl * ld + m];
+  }
+}
+
+// blockIdx.x = tile of RB rows, y = channel, z = ring
+template <typename T>
+__global__ __launch_bounds__(256) void k_ring_rows(MabsFieldArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int n = a.n, M = n / 2, ld = M + 1;
+  const int nu = a.chan_offset + blockIdx.y, bi = blockIdx.z;
+  const int r0 = blockIdx.x * a.RB, nb = min(a.RB, n - r0);
+  const int vmax = a.ring_v[a.bins[bi]];
+  Cx<T>* A = (Cx<T>*)smem_raw;
+  Cx<T>* tw = A + (size_t)a.RB * ld;
+  for (int e = threadIdx.x; e < n; e += blockDim.x) tw[e] = ((const Cx<T>*)a.tw_n)[e];
+  __syncthreads();
+  T* out = (T*)a.out + (size_t)bi * a.bin_stride + (size_t)nu * a.plane_stride + (size_t)r0 * n;
+  const float rM = 1.0f / (float)M;
+  for (int e = threadIdx.x; e < nb * M; e += blockDim.x) {
+    int rl, k;
+    fdivmod(e, M, rM, rl, k);
+    const Cx<T>* row = (const Cx<T>*)(out + (size_t)rl * n);
+    auto get = [&](int v) -> Cx<T> { return v <= vmax ? row[v] : cmk(T(0), T(0)); };
+    A[(size_t)rl * ld + k] = c2r_pack<T>(k, M, get, tw, 1);
+  }
+  __syncthreads();
+  lds_fft_ip<+1, T, 4>(A, a.prow, nb, tw, 2, ld);
   const T sc = T(a.scale);
-  const int vmax = a.vmax;
-  for (int m0 = 0; m0 < Lc; m0 += a.RB) {
-    const int nb = min(a.RB, Lc - m0);
-    for (int e = tid; e < nb * M; e += blockDim.x) {
-      int rl = e / M, k = e - rl * M, m = m0 + rl;
-      auto get = [&](int v) -> Cx<T> { return v <= vmax ? Rg[(size_t)v * Lc + m] : cmk(T(0), T(0)); };
-      wa[e] = c2r_pack<T>(k, M, get, tw, 1);
-    }
-    __syncthreads();
-    Cx<T>* r = lds_fft<+1, T>(wa, wb, a.prow, nb, tw, 2);
-    for (int e = tid; e < nb * M; e += blockDim.x) {
-      int rl = e / M, k = e - rl * M;
-      int xu = G * (m0 + rl) + g;
-      Cx<T> z = r[e];
-      Cx<T>* o = (Cx<T>*)(out + (size_t)xu * n);
-      o[k] = cmk(z.x * sc, z.y * sc);
-    }
-    __syncthreads();
+  for (int e = threadIdx.x; e < nb * M; e += blockDim.x) {
+    int rl, k;
+    fdivmod(e, M, rM, rl, k);
+    const Cx<T> z = A[(size_t)rl * ld + k];
+    ((Cx<T>*)(out + (size_t)rl * n))[k] = cmk(z.x * sc, z.y * sc);
   }
 }
 
@@ -1647,13 +1661,17 @@ __global__ __launch_bounds__(256) void k_mabs_collapse(MabsCollapseArgs a) {
 }  // namespace
 
 // ----------------------------------------------------------------- launchers
-void launch_mabs_fields_f32(const MabsFieldArgs& a, int nbins, int nchan, size_t lds, hipStream_t s) {
-  (void)hipFuncSetAttribute((const void*)k_mabs_fields<float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_mabs_fields<float>, dim3(a.G, nchan, nbins), dim3(256), lds, s, a);
+template <typename T>
+static void launch_mabs_fields(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
+  const size_t lc = ((size_t)a.CB * (a.n / a.G + 1) + a.n) * sizeof(Cx<T>), lr = ((size_t)a.RB * (a.n / 2 + 1) + a.n) * sizeof(Cx<T>);
+  hipLaunchKernelGGL(k_ring_cols<T>, dim3(a.G * ((a.vmax + a.CB) / a.CB), nchan, nbins), dim3(256), lc, s, a);
+  hipLaunchKernelGGL(k_ring_rows<T>, dim3((a.n + a.RB - 1) / a.RB, nchan, nbins), dim3(256), lr, s, a);
 }
-void launch_mabs_fields_f64(const MabsFieldArgs& a, int nbins, int nchan, size_t lds, hipStream_t s) {
-  (void)hipFuncSetAttribute((const void*)k_mabs_fields<double>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_mabs_fields<double>, dim3(a.G, nchan, nbins), dim3(256), lds, s, a);
+void launch_mabs_fields_f32(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
+  launch_mabs_fields<float>(a, nbins, nchan, s);
+}
+void launch_mabs_fields_f64(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
+  launch_mabs_fields<double>(a, nbins, nchan, s);
 }
 void launch_split_bf16(const float* F, uint16_t* hi, uint16_t* lo, long long n, hipStream_t s) {
   long long blocks = (n + 255) / 256;
