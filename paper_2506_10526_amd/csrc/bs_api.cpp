@@ -271,9 +271,9 @@ int ring_fields_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, bool f
     while (a.ring_v[j] < P.vmax && (a.ring_v[j] + 1) * (a.ring_v[j] + 1) <= a.ring_hi[j]) ++a.ring_v[j];
   a.n = n; a.nh = P.nh; a.nc = P.nc; a.vmax = P.vmax;
   a.G = fp64 ? 1 : ring_fold_f32(n, P.vmax);
-  // at most 2048 values a block: the in-place FFT's four butterflies a thread
-  a.CB = std::max(1, std::min(P.vmax + 1, 2048 / (n / a.G)));
-  a.RB = std::max(1, std::min(n, 2048 / (n / 2)));
+  // at most RING_BLOCK values a block: the in-place FFT's four butterflies a thread
+  a.CB = std::max(1, std::min(P.vmax + 1, RING_BLOCK / (n / a.G)));
+  a.RB = std::max(1, std::min(n, RING_BLOCK / (n / 2)));
   a.count_mode = count_mode ? 1 : 0;
   a.ignore_chan = ignore_chan ? 1 : 0;
   a.out = out;

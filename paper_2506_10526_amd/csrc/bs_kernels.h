@@ -11,6 +11,7 @@
 constexpr int kReduceGroup = 32;
 
 // ---------------------------------------------------------------- ring fields
+constexpr int RING_BLOCK = 2048;   // values a block transforms at a time (the in-place FFT's bound)
 struct MabsFieldArgs {
   const void* vis;          // complex64 (T=float) or complex128 (T=double), [nc][n][nh]
   const uint16_t* ng;       // per-cell counts or NULL

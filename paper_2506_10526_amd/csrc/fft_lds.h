@@ -222,6 +222,73 @@ __device__ void lds_fft_ip(Cx<T>* a, const FftPlan& p, int nl, const Cx<T>* __re
   }
 }
 
+// The in-place transform with its length, line stride and block size known at compile time.  The plan is
+// the smallest-radix-first one (3s, then a 2 or 4, then 8s) and every butterfly does the operations of
+// stockham_pass_ip in the same order, so the results are the same bits; what goes is the index
+// arithmetic, which was about half of the vector instructions of the passes that run these transforms
+// (LDS addresses become one base with constant offsets, the divisions shifts or constant products).
+constexpr int fft_ct_radix(int rem) {   // next radix when the product `rem` of radices is left
+  if (rem % 3 == 0) return 3;
+  int p = 0;
+  while ((1 << p) < rem) ++p;
+  return p % 3 == 1 ? 2 : p % 3 == 2 ? 4 : 8;
+}
+// whether a run-time plan is the one lds_fft_ct<L> runs
+inline bool fft_ct_plan(const FftPlan& p, int L) {
+  int rem = p.L;
+  if (rem != L) return false;
+  for (int s = 0; s < p.nr; ++s) {
+    if (p.rad[s] != fft_ct_radix(rem)) return false;
+    rem /= p.rad[s];
+  }
+  return rem == 1;
+}
+
+template <int SIGN, typename T, int L, int NLMAX, int TH, int LD, int Ns = 1>
+__device__ __forceinline__ void lds_fft_ct(Cx<T>* __restrict__ buf, int nl, const Cx<T>* __restrict__ tw, int tws) {
+  if constexpr (Ns < L) {
+    constexpr int R = fft_ct_radix(L / Ns), NBF = L / R, BM = (NLMAX * NBF + TH - 1) / TH;
+    const unsigned total = (unsigned)(nl * NBF);
+    const int tstep = (L / (Ns * R)) * tws;
+    Cx<T> v[BM][R];
+    int o[BM];
+#pragma unroll
+    for (int b = 0; b < BM; ++b) {
+      const unsigned t = threadIdx.x + b * TH;
+      o[b] = -1;
+      if (t < total) {
+        const unsigned line = t / NBF, j = t % NBF, k = j % Ns;
+        const Cx<T>* in = buf + line * LD + j;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[b][r] = in[r * NBF];
+        if constexpr (Ns > 1) {
+#pragma unroll
+          for (int r = 1; r < R; ++r) {
+            Cx<T> w = tw[(int)k * r * tstep];
+            if (SIGN > 0) w.y = -w.y;
+            v[b][r] = cmul(v[b][r], w);
+          }
+        }
+        if constexpr (R == 2) dft2<SIGN>(v[b]);
+        else if constexpr (R == 3) dft3<SIGN>(v[b]);
+        else if constexpr (R == 4) dft4<SIGN>(v[b]);
+        else dft8<SIGN>(v[b]);
+        o[b] = (int)(line * LD + (j / Ns) * (Ns * R) + k);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < BM; ++b) {
+      if (o[b] >= 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) buf[o[b] + r * Ns] = v[b][r];
+      }
+    }
+    __syncthreads();
+    lds_fft_ct<SIGN, T, L, NLMAX, TH, LD, Ns * R>(buf, nl, tw, tws);
+  }
+}
+
 // Transform nl lines held in `a` (line i at a + i*ld, ld >= L; ld = L when omitted).
 // `b` is scratch of the same size.  Returns the buffer holding the result (a or b).
 // Ends with a barrier.  PAD: intermediate passes use the padded layout fft_pad() (input and

@@ -25,7 +25,8 @@ __device__ __forceinline__ int signed_idx(int i, int n) { return i < (n + 1) / 2
 //     holds v_b + 1 <= n / 2 of them, so the pass needs no workspace;
 //   rows (k_ring_rows): C2R along v, each row read into LDS and written over itself.
 // Bound: HBM, the rows' 4 n^2 bytes (FP32).  One block per (ring, channel, g) with the whole plane's columns in
-// LDS ran one block a CU: 10 rings x 192 channels x 256^2 FP32 1690 us, now 113 + 289; 768 channels 6720 us, now 435 + 1158.
+// LDS ran one block a CU: 10 rings x 192 channels x 256^2 FP32 1690 us, now 91 + 178 (113 + 289 with run-time FFT
+// plans); loading all of a thread's cells before the first is used made the column pass 127 us.
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ Cx<T> ring_cell(const MabsFieldArgs& a, int s_lo, int s_hi, int nu, int iu, int v) {
@@ -65,10 +66,11 @@ __device__ __forceinline__ Cx<T> ring_input(const MabsFieldArgs& a, int s_lo, in
 }
 
 // blockIdx.x = g + G (column tile), y = channel, z = ring
-template <typename T>
+// L: the column length n / G when lds_fft_ct runs it, 0 for the run-time plan
+template <typename T, int L>
 __global__ __launch_bounds__(256) void k_ring_cols(MabsFieldArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int n = a.n, G = a.G, Lc = n / G, ld = Lc + 1;
+  const int G = a.G, Lc = L ? L : a.n / G, n = L ? L * G : a.n, ld = Lc + 1;
   const int g = blockIdx.x % G, c0 = (blockIdx.x / G) * a.CB;
   const int nu = a.chan_offset + blockIdx.y, bi = blockIdx.z, bin = a.bins[bi];
   const int nb = min(a.CB, a.ring_v[bin] + 1 - c0);
@@ -97,7 +99,8 @@ __global__ __launch_bounds__(256) void k_ring_cols(MabsFieldArgs a) {
     A[(size_t)cl * ld + up] = acc;
   }
   __syncthreads();
-  lds_fft_ip<+1, T, 4>(A, a.pcol, nb, tw, G, ld);
+  if constexpr (L > 0) lds_fft_ct<+1, T, L, RING_BLOCK / L, 256, L + 1>(A, nb, tw, G);
+  else lds_fft_ip<+1, T, 4>(A, a.pcol, nb, tw, G, ld);
   T* out = (T*)a.out + (size_t)bi * a.bin_stride + (size_t)nu * a.plane_stride;
   for (int e = threadIdx.x; e < nb * Lc; e += blockDim.x) {
     int m, cl;
@@ -107,32 +110,56 @@ __global__ __launch_bounds__(256) void k_ring_cols(MabsFieldArgs a) {
 }
 
 // blockIdx.x = tile of RB rows, y = channel, z = ring
-template <typename T>
+// L: the row transform's length n / 2 when lds_fft_ct runs it, 0 for the run-time plan
+template <typename T, int L>
 __global__ __launch_bounds__(256) void k_ring_rows(MabsFieldArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int n = a.n, M = n / 2, ld = M + 1;
+  const int M = L ? L : a.n / 2, n = 2 * M, ld = M + 1;
   const int nu = a.chan_offset + blockIdx.y, bi = blockIdx.z;
   const int r0 = blockIdx.x * a.RB, nb = min(a.RB, n - r0);
   const int vmax = a.ring_v[a.bins[bi]];
   Cx<T>* A = (Cx<T>*)smem_raw;
   Cx<T>* tw = A + (size_t)a.RB * ld;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) tw[e] = ((const Cx<T>*)a.tw_n)[e];
-  __syncthreads();
   T* out = (T*)a.out + (size_t)bi * a.bin_stride + (size_t)nu * a.plane_stride + (size_t)r0 * n;
   const float rM = 1.0f / (float)M;
-  for (int e = threadIdx.x; e < nb * M; e += blockDim.x) {
+  auto split = [&](int e, int& rl, int& k) {
+    if constexpr (L > 0) { rl = (int)((unsigned)e / L); k = (int)((unsigned)e % L); }
+    else fdivmod(e, M, rM, rl, k);
+  };
+  // both spectrum entries of all of a thread's elements are in flight before the first is used
+  constexpr int U = RING_BLOCK / 256;
+  Cx<T> hk[U], hm[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = threadIdx.x + 256 * u;
     int rl, k;
-    fdivmod(e, M, rM, rl, k);
+    split(e, rl, k);
     const Cx<T>* row = (const Cx<T>*)(out + (size_t)rl * n);
-    auto get = [&](int v) -> Cx<T> { return v <= vmax ? row[v] : cmk(T(0), T(0)); };
-    A[(size_t)rl * ld + k] = c2r_pack<T>(k, M, get, tw, 1);
+    hk[u] = hm[u] = cmk(T(0), T(0));
+    if (e < nb * M) {
+      if (k <= vmax) hk[u] = row[k];
+      if (M - k <= vmax) hm[u] = row[M - k];
+    }
+  }
+  for (int e = threadIdx.x; e < n; e += blockDim.x) tw[e] = ((const Cx<T>*)a.tw_n)[e];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = threadIdx.x + 256 * u;
+    int rl, k;
+    split(e, rl, k);
+    if (e < nb * M) A[(size_t)rl * ld + k] = c2r_pack<T>(k, M, [&](int v) { return v == k ? hk[u] : hm[u]; }, tw, 1);
   }
   __syncthreads();
-  lds_fft_ip<+1, T, 4>(A, a.prow, nb, tw, 2, ld);
+  if constexpr (L > 0) lds_fft_ct<+1, T, L, RING_BLOCK / L, 256, L + 1>(A, nb, tw, 2);
+  else lds_fft_ip<+1, T, 4>(A, a.prow, nb, tw, 2, ld);
   const T sc = T(a.scale);
-  for (int e = threadIdx.x; e < nb * M; e += blockDim.x) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = threadIdx.x + 256 * u;
+    if (e >= nb * M) break;
     int rl, k;
-    fdivmod(e, M, rM, rl, k);
+    split(e, rl, k);
     const Cx<T> z = A[(size_t)rl * ld + k];
     ((Cx<T>*)(out + (size_t)rl * n))[k] = cmk(z.x * sc, z.y * sc);
   }
@@ -1661,11 +1688,38 @@ __global__ __launch_bounds__(256) void k_mabs_collapse(MabsCollapseArgs a) {
 }  // namespace
 
 // ----------------------------------------------------------------- launchers
+template <typename T, int L>
+static void launch_ring_cols(const MabsFieldArgs& a, dim3 grid, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((k_ring_cols<T, L>), grid, dim3(256), lds, s, a);
+}
+template <typename T, int L>
+static void launch_ring_rows(const MabsFieldArgs& a, dim3 grid, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((k_ring_rows<T, L>), grid, dim3(256), lds, s, a);
+}
+// lengths with a compile-time transform: those of the uv grids in use (48 to 256, folded or not)
 template <typename T>
 static void launch_mabs_fields(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
-  const size_t lc = ((size_t)a.CB * (a.n / a.G + 1) + a.n) * sizeof(Cx<T>), lr = ((size_t)a.RB * (a.n / 2 + 1) + a.n) * sizeof(Cx<T>);
-  hipLaunchKernelGGL(k_ring_cols<T>, dim3(a.G * ((a.vmax + a.CB) / a.CB), nchan, nbins), dim3(256), lc, s, a);
-  hipLaunchKernelGGL(k_ring_rows<T>, dim3((a.n + a.RB - 1) / a.RB, nchan, nbins), dim3(256), lr, s, a);
+  const int lc = a.n / a.G, lr = a.n / 2;
+  const dim3 gc(a.G * ((a.vmax + a.CB) / a.CB), nchan, nbins), gr((a.n + a.RB - 1) / a.RB, nchan, nbins);
+  const size_t bc = ((size_t)a.CB * (lc + 1) + a.n) * sizeof(Cx<T>), br = ((size_t)a.RB * (lr + 1) + a.n) * sizeof(Cx<T>);
+  switch (fft_ct_plan(a.pcol, lc) ? lc : 0) {
+    case 48: launch_ring_cols<T, 48>(a, gc, bc, s); break;
+    case 64: launch_ring_cols<T, 64>(a, gc, bc, s); break;
+    case 96: launch_ring_cols<T, 96>(a, gc, bc, s); break;
+    case 128: launch_ring_cols<T, 128>(a, gc, bc, s); break;
+    case 192: launch_ring_cols<T, 192>(a, gc, bc, s); break;
+    case 256: launch_ring_cols<T, 256>(a, gc, bc, s); break;
+    default: launch_ring_cols<T, 0>(a, gc, bc, s);
+  }
+  switch (fft_ct_plan(a.prow, lr) ? lr : 0) {
+    case 24: launch_ring_rows<T, 24>(a, gr, br, s); break;
+    case 32: launch_ring_rows<T, 32>(a, gr, br, s); break;
+    case 48: launch_ring_rows<T, 48>(a, gr, br, s); break;
+    case 64: launch_ring_rows<T, 64>(a, gr, br, s); break;
+    case 96: launch_ring_rows<T, 96>(a, gr, br, s); break;
+    case 128: launch_ring_rows<T, 128>(a, gr, br, s); break;
+    default: launch_ring_rows<T, 0>(a, gr, br, s);
+  }
 }
 void launch_mabs_fields_f32(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
   launch_mabs_fields<float>(a, nbins, nchan, s);

@@ -23,7 +23,7 @@ def ctx():
     c.close()
 
 
-@pytest.mark.parametrize("n,nc,umax", [(8, 3, 3.0), (16, 2, 0.0), (18, 3, 8.0), (54, 2, 26.0), (64, 3, 31.0), (192, 1, 0.0),
+@pytest.mark.parametrize("n,nc,umax", [(8, 3, 3.0), (16, 2, 0.0), (18, 3, 8.0), (48, 1, 0.0), (54, 2, 26.0), (64, 3, 31.0), (96, 1, 40.0), (128, 1, 0.0), (192, 1, 0.0),
                                        (256, 2, 0.0), (256, 1, 127.0)])
 @pytest.mark.parametrize("precision", [bs.BS_FP64, bs.BS_FP32])
 @pytest.mark.parametrize("weights", ["unit", "flags", "counts"])
