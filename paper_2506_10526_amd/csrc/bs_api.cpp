@@ -149,6 +149,11 @@ extern "C" int bs_last_count_bound(const bs_ctx* c, double* bound) {
 
 extern "C" int bs_set_stream(bs_ctx* c, void* s) {
   if (!c) return BS_EINVAL;
+  // tables uploaded on the old stream are uploaded again on the new one
+  if ((hipStream_t)s != c->stream) {
+    for (auto& kv : c->ws) kv.second.mirror.clear();
+    ++c->ws_gen;
+  }
   c->stream = (hipStream_t)s;
   return BS_OK;
 }
@@ -308,11 +313,11 @@ int run_ring_fields(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weigh
                     bool count_mode, bool ignore_chan, int nch, const std::vector<int>& blocks,
                     void* out, long long bin_stride) {
   if (blocks.empty()) return BS_OK;
-  int* d_bins = (int*)ctx_ws(c, count_mode ? "ring_bins_c" : "ring_bins_d", blocks.size() * sizeof(int));
-  if (!d_bins) return ctx_fail(c, BS_ENOMEM, "workspace (ring ids)");
-  HIPCHK(c, hipMemcpyAsync(d_bins, blocks.data(), blocks.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
+  int rc = BS_OK;
+  int* d_bins = upload(c, count_mode ? "ring_bins_c" : "ring_bins_d", blocks, rc);
+  if (rc) return rc;
   MabsFieldArgs a;
-  int rc = ring_fields_prepare(c, b, w, fp64, count_mode, ignore_chan, d_bins, out, bin_stride, a);
+  rc = ring_fields_prepare(c, b, w, fp64, count_mode, ignore_chan, d_bins, out, bin_stride, a);
   if (rc) return rc;
   a.vis = vis;
   ring_fields_launch(a, fp64, (int)blocks.size(), nch, c->stream);
@@ -919,12 +924,10 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
 
   unsigned long long* bad = (unsigned long long*)ctx_ws(c, "count_dev", 256);
   if (!bad) return ctx_fail(c, BS_ENOMEM, "workspace (flag)");
-  HIPCHK(c, hipMemsetAsync(bad, 0, sizeof(unsigned long long), c->stream));
 
   // ---- counts ----
-  int* d_tri = (int*)ctx_ws(c, "mabs_tri", tri_blk.size() * sizeof(int) + 16);
-  if (!d_tri) return ctx_fail(c, BS_ENOMEM, "workspace (triangles)");
-  HIPCHK(c, hipMemcpyAsync(d_tri, tri_blk.data(), tri_blk.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
+  int* d_tri = upload(c, "mabs_tri", tri_blk, rc);
+  if (rc) return rc;
   int64_t* d_tperp = nullptr;
   double* I64 = nullptr;
   if (separable) {
@@ -958,6 +961,7 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
       CountCache cc;
       cc.tri.assign(tri.begin(), tri.end());
       if (hipMalloc(&cc.d_counts, (size_t)ntri * 8) != hipSuccess) { (void)hipGetLastError(); return ctx_fail(c, BS_ENOMEM, "count cache"); }
+      HIPCHK(c, hipMemsetAsync(bad, 0, sizeof(unsigned long long), c->stream));
       launch_round_counts(Ts, ntri, cc.d_counts, bad, c->stream);
       LAUNCHCHK(c, "count rounding");
       double dev = 0.0;
@@ -977,6 +981,7 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
     c->last_count_dev = it->second.dev;
     c->last_count_bound = it->second.bound;
   } else {
+    HIPCHK(c, hipMemsetAsync(bad, 0, sizeof(unsigned long long), c->stream));
     I64 = (double*)ctx_ws(c, "mabs_I64", (size_t)nbu * bstride * 8);
     if (!I64) return ctx_fail(c, BS_ENOMEM, "workspace (count fields)");
     rc = run_ring_fields(c, b, nullptr, w, true, true, false, nc, blocks, I64, bstride);
@@ -984,9 +989,8 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
   }
 
   // ---- contraction + finalisation, batched over triangles to bound the workspace ----
-  int* d_nu1 = (int*)ctx_ws(c, "mabs_nu1", nu1.size() * sizeof(int) + 16);
-  if (!d_nu1) return ctx_fail(c, BS_ENOMEM, "workspace (nu1)");
-  HIPCHK(c, hipMemcpyAsync(d_nu1, nu1.data(), nu1.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
+  int* d_nu1 = upload(c, "mabs_nu1", nu1, rc);
+  if (rc) return rc;
   const long long nrows = (long long)n_nu1 * nc;
   const size_t per_tri = (size_t)nrows * nc * 8;
   // number of pixel chunks: enough blocks to fill the chip, chunks of at least `least` pixels

@@ -68,29 +68,6 @@ void build_plan3(const bsplan::Plan& P, const std::vector<int>& blocks, bool fp6
 
 namespace {
 
-// Host table -> named device workspace.  A table equal to what the workspace already holds is not
-// copied again: a copy from pageable memory would hold the host until the stream reaches it, so
-// repeated calls could no longer be queued ahead of the running kernels.
-template <typename X>
-X* upload(bs_ctx* c, const std::string& name, const std::vector<X>& v, int& rc) {
-  X* d = (X*)ctx_ws(c, name.c_str(), std::max<size_t>(v.size() * sizeof(X), 16));
-  if (!d) { rc = ctx_fail(c, BS_ENOMEM, "workspace " + name); return nullptr; }
-  DevBuf& wb = c->ws[name];
-  const size_t nb = v.size() * sizeof(X);
-  const unsigned char* hv = (const unsigned char*)v.data();
-  if (nb > 0 && !(wb.mirror.size() == nb && std::memcmp(wb.mirror.data(), hv, nb) == 0)) {
-    if (hipMemcpyAsync(d, v.data(), nb, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
-      wb.mirror.clear();
-      rc = ctx_fail(c, BS_EHIP, "upload " + name);
-      return nullptr;
-    }
-    wb.mirror.assign(hv, hv + nb);
-    ++c->ws_gen;
-  }
-  rc = BS_OK;
-  return d;
-}
-
 // Twiddle table of the eta synthesis x(t) = sum_q a_q (Re G_q cos(2 pi q t / M) - Im G_q sin(2 pi q t / M)):
 // entry m holds (cos, sin) of 2 pi m / M in FP32.  Cached per M.
 const void* ctx_dft_twiddle(bs_ctx* c, int M) {
@@ -530,7 +507,7 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
 // Launches one estimate of the prepared plan on `vis` (no allocation, copy or synchronisation,
 // so it may be captured into a graph).
 int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights* w, Est3& e, double norm, double* B,
-                 int64_t* N_tri, double* N_eff) {
+                 int64_t* N_tri, double* N_eff, const float* rho3_w) {
   if (e.ntri == 0) return BS_OK;
   int rc;
   int nparts = (int)e.nblk;
@@ -561,11 +538,10 @@ int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights*
   Fin3Args f{};
   f.partial = e.partial; f.nparts = nparts; f.tri_pair = e.d_tp; f.tri_col = e.d_tc; f.ntri = e.ntri;
   if (e.fused && e.dft) { f.pstride = DFT_WAVES; f.nent = (e.npairs + 15) / 16 * 16 * 32; }
-  f.T3D = e.d_counts; f.rho3 = e.rho3; f.nvox = (double)e.nvox; f.norm = norm; f.sfac = e.sfac;
+  f.T3D = e.d_counts; f.rho3 = e.rho3; f.rho3_w = rho3_w; f.nc = b->P.nc; f.nvox = (double)e.nvox; f.norm = norm; f.sfac = e.sfac;
   f.B = B; f.N = N_tri; f.Neff = N_eff;
   launch_fin3(f, e.reduced, c->stream);
   LAUNCHCHK(c, "finalize");
-  (void)b;
   return BS_OK;
 }
 
@@ -578,35 +554,41 @@ extern "C" int bs_estimate_3d(bs_ctx* c, const bs_bins* b, const void* vis, cons
   if (!vis || !B || !N_tri) return ctx_fail(c, BS_EINVAL, "vis, B and N_tri must be non-NULL");
   if (precision < 0 || precision > 2) return ctx_fail(c, BS_EINVAL, "bad precision");
   if (c->timing) { (void)hipEventRecord(c->ev[0], c->stream); (void)hipEventRecord(c->ev[4], c->stream); }
-  // Unweighted calls reuse the last prepared estimate (pair cover, work lists, uploaded tables) as
-  // long as the bins, precision and path switches are the same and no workspace has changed since.
-  // With weights the mask and channel weights are read back on every call.
-  const bool cacheable = !w || (!w->ng && !w->uv_mask && !w->chan_w);
-  std::string key;
-  if (cacheable) {
-    key = std::to_string((uintptr_t)b) + ":" + std::to_string((uintptr_t)b->d_lut) + ":" + std::to_string(b->P.hash) +
-          ":" + std::to_string(precision);
-    for (const char* k : {"BS_3D_FULLGRID", "BS_3D_UNFUSED", "BS_3D_ALLFFT", "BS_3D_FFT", "BS_3D_DFT_BLOCKS",
-                          "BS_3D_DFT_FLUSH", "BS_FORCE_ENOMEM"}) {
-      const char* v = getenv(k);
-      key += std::string(":") + (v ? v : "-");
-    }
+  // Calls reuse the last prepared estimate (pair cover, work lists, uploaded tables: 1.3 ms of host work
+  // on the 256^2 x 768 cube) as long as the bins, the uv mask's contents, precision and path switches
+  // are the same and no workspace has changed since.  The channel weights do not enter it: the kernels
+  // read them, rho3 included.
+  const bs_weights wm{nullptr, w ? w->uv_mask : nullptr, nullptr};
+  uint64_t mask = 0;
+  if (wm.uv_mask) {
+    std::vector<uint8_t> hm((size_t)b->P.n * b->P.nh);
+    HIPCHK(c, hipMemcpyAsync(hm.data(), wm.uv_mask, hm.size(), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    mask = hash_bytes3(b->P.hash, hm.data(), hm.size());
+  }
+  std::string key = std::to_string((uintptr_t)b) + ":" + std::to_string((uintptr_t)b->d_lut) + ":" +
+                    std::to_string(b->P.hash) + ":" + std::to_string(precision) + (wm.uv_mask ? ":m" : ":") + std::to_string(mask);
+  for (const char* k : {"BS_3D_FULLGRID", "BS_3D_UNFUSED", "BS_3D_ALLFFT", "BS_3D_FFT", "BS_3D_DFT_BLOCKS",
+                        "BS_3D_DFT_FLUSH", "BS_FORCE_ENOMEM"}) {
+    const char* v = getenv(k);
+    key += std::string(":") + (v ? v : "-");
   }
   std::shared_ptr<Est3> held;
-  if (cacheable && c->est3 && c->est3_key == key && c->est3_gen == c->ws_gen) {
+  if (c->est3 && c->est3_key == key && c->est3_gen == c->ws_gen) {
     held = c->est3;
   } else {
     held = std::make_shared<Est3>();
-    rc = est3_prepare(c, b, w, precision, "c3", *held);
+    rc = est3_prepare(c, b, &wm, precision, "c3", *held);
     if (rc) return rc;
-    if (cacheable) { c->est3 = held; c->est3_key = key; c->est3_gen = c->ws_gen; }
-    else c->est3.reset();
+    c->est3 = held;
+    c->est3_key = key;
+    c->est3_gen = c->ws_gen;
   }
   Est3& e = *held;
   if (e.ntri == 0) return BS_OK;
   c->last_count_dev = e.count_dev;
   c->last_count_bound = e.count_bound;
-  rc = est3_enqueue(c, b, vis, w, e, norm, B, N_tri, N_eff);
+  rc = est3_enqueue(c, b, vis, w, e, norm, B, N_tri, N_eff, w ? w->chan_w : nullptr);
   if (rc) return rc;
   c->last_grid_M = e.M;
   c->last_flops_vox = 0.0;

@@ -2,7 +2,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <map>
 #include <memory>
 #include <string>
@@ -69,6 +71,28 @@ double ring_count_bound(const bsplan::Plan& P, const std::vector<int>& tri, doub
 int ctx_fail(bs_ctx* c, int code, const std::string& msg);
 void* ctx_ws(bs_ctx* c, const char* name, size_t bytes);       // grow-only; NULL on failure
 const void* ctx_twiddle(bs_ctx* c, int L, bool fp64);          // NULL on failure
+// Host table -> named device workspace.  A table equal to what the workspace already holds is not
+// copied again: a copy from pageable memory would hold the host until the stream reaches it, so
+// repeated calls could no longer be queued ahead of the running kernels.
+template <typename X>
+inline X* upload(bs_ctx* c, const std::string& name, const std::vector<X>& v, int& rc) {
+  X* d = (X*)ctx_ws(c, name.c_str(), std::max<size_t>(v.size() * sizeof(X), 16));
+  if (!d) { rc = ctx_fail(c, BS_ENOMEM, "workspace " + name); return nullptr; }
+  DevBuf& wb = c->ws[name];
+  const size_t nb = v.size() * sizeof(X);
+  const unsigned char* hv = (const unsigned char*)v.data();
+  if (nb > 0 && !(wb.mirror.size() == nb && std::memcmp(wb.mirror.data(), hv, nb) == 0)) {
+    if (hipMemcpyAsync(d, v.data(), nb, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
+      wb.mirror.clear();
+      rc = ctx_fail(c, BS_EHIP, "upload " + name);
+      return nullptr;
+    }
+    wb.mirror.assign(hv, hv + nb);
+    ++c->ws_gen;
+  }
+  rc = BS_OK;
+  return d;
+}
 FftPlan make_fft_plan(int L);
 // true when every pass of `p` over nl lines fits the in-place LDS FFT with `threads` threads and
 // at most bmax butterflies per thread (bmax / 2 in radix-8 passes)

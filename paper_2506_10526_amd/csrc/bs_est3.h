@@ -79,5 +79,6 @@ struct Est3 {
 void build_plan3(const bsplan::Plan& P, const std::vector<int>& blocks, bool fp64, Plan3& p);
 int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t precision, const std::string& tag,
                  Est3& e);
+// rho3_w: channel weights whose rho3 replaces e.rho3 (summed on the device), or NULL
 int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights* w, Est3& e, double norm, double* B,
-                 int64_t* N_tri, double* N_eff);
+                 int64_t* N_tri, double* N_eff, const float* rho3_w = nullptr);

@@ -194,6 +194,7 @@ struct Fin3Args {
   const int64_t* T3D;          // counts (NULL when computing counts)
   double* Ssum;                // [ntri] output sums (count pass) or NULL
   double rho3, nvox, norm, sfac;
+  const float* rho3_w; int nc;  // rho3 = (1/nc) sum of rho3_w^3 instead, when given
   double* B; int64_t* N; double* Neff;
 };
 

@@ -950,7 +950,24 @@ __global__ void k3_reduce_parts(const double* __restrict__ partial, int nparts, 
 }
 
 // --------------------------------------------------------------- finalisation
-__global__ void k3_fin(Fin3Args a) {
+constexpr int FIN3_THREADS = 128;
+__global__ __launch_bounds__(FIN3_THREADS) void k3_fin(Fin3Args a) {
+  double rho3 = a.rho3;
+  if (a.rho3_w) {   // every block sums the channel weights itself, in one order
+    __shared__ double red[FIN3_THREADS];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < a.nc; i += FIN3_THREADS) {
+      const double x = (double)a.rho3_w[i];
+      s += x * x * x;
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = FIN3_THREADS / 2; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    rho3 = red[0] / a.nc;
+  }
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= a.ntri) return;
   int idx = a.tri_pair[t] * 32 + a.tri_col[t];
@@ -960,7 +977,7 @@ __global__ void k3_fin(Fin3Args a) {
     return;
   }
   int64_t T = a.T3D[t];
-  double neff = (double)T * a.rho3;
+  double neff = (double)T * rho3;
   a.N[t] = T;
   if (a.Neff) a.Neff[t] = neff;
   a.B[t] = (T > 0 && neff > 0) ? a.norm * a.nvox * s / neff : __builtin_nan("");
@@ -1029,7 +1046,7 @@ void launch_fin3(const Fin3Args& a, double* reduced, hipStream_t s) {
                      reduced);
   Fin3Args b = a;
   b.partial = reduced;
-  if (a.ntri > 0) hipLaunchKernelGGL(k3_fin, dim3((a.ntri + 127) / 128), dim3(128), 0, s, b);
+  if (a.ntri > 0) hipLaunchKernelGGL(k3_fin, dim3((a.ntri + FIN3_THREADS - 1) / FIN3_THREADS), dim3(FIN3_THREADS), 0, s, b);
 }
 template <int RTN>
 static void launch_dft3_rt(const Dft3Args& a, int nblocks, size_t lds, hipStream_t s) {
