@@ -54,11 +54,15 @@ __device__ __forceinline__ void dft_split2(float x, float y, uint32_t& hp, uint3
 // --------------------------------------------------------------- delay transform
 // Vt(eta, U) = sum_nu w(nu) m(U) V(U, nu) e^{-2 pi i eta nu / nc}, with the v = 0 column
 // symmetrised per channel.  Block: NL consecutive qv of one qu row, all channels.
-template <typename T, int IP>   // IP: in-place FFT butterflies per thread (2 or 4), 0 = two buffers
+// IP: in-place FFT butterflies per thread (2 or 4), 0 = two buffers.  L: the length of an in-place
+// transform that lds_fft_ct runs (then a.NL is the lines constant below), 0 for the run-time plan.
+template <typename T>
+constexpr int delay_lines(int L) { return L > 512 ? 4 : (sizeof(T) == 8 ? 8 : 16); }
+template <typename T, int IP, int L>
 __global__ __launch_bounds__(256) void k3_delay(Delay3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Shell3Geom& g = a.g;
-  const int nc = g.nc, n = g.n, nh = g.nh;
+  const int nc = L ? L : g.nc, n = g.n, nh = g.nh;
   // logical block (ub, v-block), v-blocks of one uv row consecutive on one XCD: the NL-column
   // reads of neighbouring blocks fill the same cache lines
   const int nvblk = (g.nvb + a.NL - 1) / a.NL;
@@ -110,7 +114,8 @@ __global__ __launch_bounds__(256) void k3_delay(Delay3Args a) {
   }
   __syncthreads();
   Cx<T>* r = A;
-  if constexpr (IP > 0) lds_fft_ip<-1, T, IP>(A, a.plan, nl, twl, 1, ld);
+  if constexpr (L > 0) lds_fft_ct<-1, T, L, delay_lines<T>(L), 256, L + 1>(A, nl, twl, 1);
+  else if constexpr (IP > 0) lds_fft_ip<-1, T, IP>(A, a.plan, nl, twl, 1, ld);
   else r = lds_fft<-1, T>(A, Bf, a.plan, nl, twl, 1, ld);
   Cx<T>* out = (Cx<T>*)a.out;
   const int ne = 2 * g.H + 1;
@@ -149,14 +154,15 @@ __device__ __forceinline__ Cx<T> shell_data(const Pass3Args& a, int eta, int qu,
   return cconj(D[((size_t)(g.H - eta) * g.nub + (-qu + g.vmax)) * g.nvb + (-qv)]);
 }
 
-template <typename T, int IP>
+constexpr int PASS3_LINES = 8;   // lines of a v- or u-pass block when lds_fft_ct transforms them
+template <typename T, int IP, int L>
 __global__ __launch_bounds__(256) void k3_vpass(Pass3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Shell3Geom& g = a.g;
   // consecutive work items (neighbouring qu blocks, whose output rows share cache lines) on one XCD
   const Work3 w = a.work[xcd_block(blockIdx.x, gridDim.x)];
   const int shell = a.shell_of_block[w.j];
-  const int n = g.n, ld = n + 1;
+  const int n = L ? L : g.n, ld = n + 1;
   const int nl = min(a.NL, g.nub - w.start);
   Cx<T>* A = (Cx<T>*)smem_raw;
   Cx<T>* Bf = A + (size_t)a.NL * ld;
@@ -183,7 +189,8 @@ __global__ __launch_bounds__(256) void k3_vpass(Pass3Args a) {
   }
   __syncthreads();
   Cx<T>* r = A;
-  if constexpr (IP > 0) lds_fft_ip<+1, T, IP>(A, a.plan, nl, twl, 1, ld);
+  if constexpr (L > 0) lds_fft_ct<+1, T, L, PASS3_LINES, 256, L + 1>(A, nl, twl, 1);
+  else if constexpr (IP > 0) lds_fft_ip<+1, T, IP>(A, a.plan, nl, twl, 1, ld);
   else r = lds_fft<+1, T>(A, Bf, a.plan, nl, twl, 1, ld);
   // T_j[x_v][eta][qu]: consecutive threads write consecutive qu rows of one x_v
   const int hp1 = a.hj[w.j] + 1;
@@ -199,12 +206,12 @@ __global__ __launch_bounds__(256) void k3_vpass(Pass3Args a) {
 // --------------------------------------------------------------- u pass
 // Work item (j, x_v = w.start, eta0 = w.eta): the delay planes eta0.. of one x_v column.
 // Output G_j[line = x_u n + x_v][eta] keeps each line's delay spectrum contiguous.
-template <typename T, int IP>
+template <typename T, int IP, int L>
 __global__ __launch_bounds__(256) void k3_upass(Pass3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const Shell3Geom& g = a.g;
   const Work3 w = a.work[blockIdx.x];
-  const int n = g.n, ld = n + 1;
+  const int n = L ? L : g.n, ld = n + 1;
   const int hp1 = a.hj[w.j] + 1;
   const int xv = w.start, e0 = w.eta;
   const int nl = min(a.NL, hp1 - e0);
@@ -230,7 +237,8 @@ __global__ __launch_bounds__(256) void k3_upass(Pass3Args a) {
   }
   __syncthreads();
   Cx<T>* r = A;
-  if constexpr (IP > 0) lds_fft_ip<+1, T, IP>(A, a.plan, nl, twl, 1, ld);
+  if constexpr (L > 0) lds_fft_ct<+1, T, L, PASS3_LINES, 256, L + 1>(A, nl, twl, 1);
+  else if constexpr (IP > 0) lds_fft_ip<+1, T, IP>(A, a.plan, nl, twl, 1, ld);
   else r = lds_fft<+1, T>(A, Bf, a.plan, nl, twl, 1, ld);
   if constexpr (std::is_same<T, float>::value) {
     if (a.gs) {
@@ -991,31 +999,47 @@ static void set_lds(const void* f, size_t lds) {
   (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
-template <typename T, int IP>
+template <typename T, int IP, int L>
 static void launch_delay3_t(const Delay3Args& a, hipStream_t s, size_t lds) {
-  set_lds<T>((const void*)k3_delay<T, IP>, lds);
-  hipLaunchKernelGGL((k3_delay<T, IP>), dim3((a.g.nvb + a.NL - 1) / a.NL * a.g.nub), dim3(256), lds, s, a);
+  set_lds<T>((const void*)k3_delay<T, IP, L>, lds);
+  hipLaunchKernelGGL((k3_delay<T, IP, L>), dim3((a.g.nvb + a.NL - 1) / a.NL * a.g.nub), dim3(256), lds, s, a);
 }
+// compile-time transforms: 96 to 768 channels (bands of 96 2^k and the 256-point grids in use)
 template <typename T>
 static void launch_delay3_ip(const Delay3Args& a, hipStream_t s, size_t lds) {
-  if (a.ip == 2) launch_delay3_t<T, 2>(a, s, lds);
-  else if (a.ip == 4) launch_delay3_t<T, 4>(a, s, lds);
-  else launch_delay3_t<T, 0>(a, s, lds);
+  const int L = a.ip > 0 && fft_ct_plan(a.plan, a.plan.L) && a.NL == delay_lines<T>(a.plan.L) ? a.plan.L : 0;
+  if (L == 96) launch_delay3_t<T, 2, 96>(a, s, lds);
+  else if (L == 128) launch_delay3_t<T, 2, 128>(a, s, lds);
+  else if (L == 192) launch_delay3_t<T, 2, 192>(a, s, lds);
+  else if (L == 256) launch_delay3_t<T, 2, 256>(a, s, lds);
+  else if (L == 384) launch_delay3_t<T, 2, 384>(a, s, lds);
+  else if (L == 768) launch_delay3_t<T, 2, 768>(a, s, lds);
+  else if (a.ip == 2) launch_delay3_t<T, 2, 0>(a, s, lds);
+  else if (a.ip == 4) launch_delay3_t<T, 4, 0>(a, s, lds);
+  else launch_delay3_t<T, 0, 0>(a, s, lds);
 }
 void launch_delay3_f32(const Delay3Args& a, hipStream_t s, size_t lds) { launch_delay3_ip<float>(a, s, lds); }
 void launch_delay3_f64(const Delay3Args& a, hipStream_t s, size_t lds) { launch_delay3_ip<double>(a, s, lds); }
-template <typename T, int IP>
+template <typename T, int IP, int L>
 static void launch_pass3_t(bool upass, const Pass3Args& a, int nwork, hipStream_t s, size_t lds) {
-  const void* f = upass ? (const void*)k3_upass<T, IP> : (const void*)k3_vpass<T, IP>;
+  const void* f = upass ? (const void*)k3_upass<T, IP, L> : (const void*)k3_vpass<T, IP, L>;
   set_lds<T>(f, lds);
-  if (upass) hipLaunchKernelGGL((k3_upass<T, IP>), dim3(nwork), dim3(256), lds, s, a);
-  else hipLaunchKernelGGL((k3_vpass<T, IP>), dim3(nwork), dim3(256), lds, s, a);
+  if (upass) hipLaunchKernelGGL((k3_upass<T, IP, L>), dim3(nwork), dim3(256), lds, s, a);
+  else hipLaunchKernelGGL((k3_vpass<T, IP, L>), dim3(nwork), dim3(256), lds, s, a);
 }
+// compile-time transforms: uv grids of 48 to 256
 template <typename T>
 static void launch_pass3_ip(bool upass, const Pass3Args& a, int nwork, hipStream_t s, size_t lds) {
-  if (a.ip == 2) launch_pass3_t<T, 2>(upass, a, nwork, s, lds);
-  else if (a.ip == 4) launch_pass3_t<T, 4>(upass, a, nwork, s, lds);
-  else launch_pass3_t<T, 0>(upass, a, nwork, s, lds);
+  const int L = a.ip > 0 && fft_ct_plan(a.plan, a.plan.L) && a.NL == PASS3_LINES ? a.plan.L : 0;
+  if (L == 48) launch_pass3_t<T, 2, 48>(upass, a, nwork, s, lds);
+  else if (L == 64) launch_pass3_t<T, 2, 64>(upass, a, nwork, s, lds);
+  else if (L == 96) launch_pass3_t<T, 2, 96>(upass, a, nwork, s, lds);
+  else if (L == 128) launch_pass3_t<T, 2, 128>(upass, a, nwork, s, lds);
+  else if (L == 192) launch_pass3_t<T, 2, 192>(upass, a, nwork, s, lds);
+  else if (L == 256) launch_pass3_t<T, 2, 256>(upass, a, nwork, s, lds);
+  else if (a.ip == 2) launch_pass3_t<T, 2, 0>(upass, a, nwork, s, lds);
+  else if (a.ip == 4) launch_pass3_t<T, 4, 0>(upass, a, nwork, s, lds);
+  else launch_pass3_t<T, 0, 0>(upass, a, nwork, s, lds);
 }
 void launch_vpass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds) {
   if (nwork <= 0) return;
