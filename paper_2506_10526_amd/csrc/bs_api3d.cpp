@@ -324,6 +324,9 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
   e.nblk = std::min<long long>(2048, (e.nvox + 127) / 128);
   e.chunk = ((e.nvox + e.nblk - 1) / e.nblk + 127) / 128 * 128;
   e.nblk = (e.nvox + e.chunk - 1) / e.chunk;
+  e.nblk64 = std::min<long long>(1024, (e.nvox + 127) / 128);
+  e.chunk64 = ((e.nvox + e.nblk64 - 1) / e.nblk64 + 127) / 128 * 128;
+  e.nblk64 = (e.nvox + e.chunk64 - 1) / e.chunk64;
   // partial sums: one slot per contraction block, or per wave of the MFMA synthesis kernel (8 x 256)
   e.partial = (double*)ctx_ws(c, (tag + "_partial").c_str(), (size_t)std::max<long long>(e.nblk, 2048) * 112 * 32 * 8);
   e.reduced = (double*)ctx_ws(c, (tag + "_reduced").c_str(), (size_t)112 * 32 * 8);
@@ -350,11 +353,11 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
     const long long nvox = e.nvox;
     // Certification of the rounding: the FP64 count fields come from C2C passes along v and u
     // and a C2R pass along eta (three rounded normalisations); the contraction's longest chain
-    // of roundings is one slab (8 MFMA steps of 4 products), one flush per slab of the block's
-    // chunk, the four waves of the block, and the two stages of the fixed-order partial sums.
+    // of roundings is one run of MFMA steps (128 products), one flush per run of a wave's quarter of the
+    // block's chunk, the four waves of the block, and the two stages of the fixed-order partial sums.
     const double eps_field = bsplan::field_error_units(2 * bsplan::fft_stage_units(P.n) + bsplan::fft_stage_units(P.nc) + 2, 3);
-    const double depth = 33.0 + (double)(e.chunk / 128) + 5.0 + (double)kReduceGroup +
-                         (double)((e.nblk + kReduceGroup - 1) / kReduceGroup) + 1.0;
+    const double depth = 129.0 + (double)((e.chunk64 / 4 + 127) / 128) + 5.0 + (double)kReduceGroup +
+                         (double)((e.nblk64 + kReduceGroup - 1) / kReduceGroup) + 1.0;
     double bound = 0.0;
     for (int t = 0; t < ntri; ++t)
       bound = std::max(bound, bsplan::count_error_bound((double)P.modes[P.tri[3 * t]], (double)P.modes[P.tri[3 * t + 1]],
@@ -371,14 +374,14 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
     if (rc) return rc;
     Con3Args ca{};
     ca.F = F64; ca.vox = nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
-    ca.chunk = e.chunk; ca.partial = e.partial;
-    launch_contract3(ca, 0, (int)e.nblk, c->stream);
+    ca.chunk = e.chunk64; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
+    launch_contract64(ca, (int)e.nblk64, c->stream);
     LAUNCHCHK(c, "count contraction");
     double* Ssum = (double*)ctx_ws(c, "c3_Ssum", (size_t)ntri * 8 + 16);
     unsigned long long* bad = (unsigned long long*)ctx_ws(c, "count_dev", 256);
     if (!Ssum || !bad) return ctx_fail(c, BS_ENOMEM, "workspace (count sums)");
     Fin3Args f{};
-    f.partial = e.partial; f.nparts = (int)e.nblk; f.tri_pair = e.d_tp; f.tri_col = e.d_tc; f.ntri = ntri;
+    f.partial = e.partial; f.nparts = (int)e.nblk64; f.nent = (e.npairs + 15) / 16 * 16 * 32; f.tri_pair = e.d_tp; f.tri_col = e.d_tc; f.ntri = ntri;
     f.T3D = nullptr; f.Ssum = Ssum; f.sfac = (double)nvox * (double)nvox;
     launch_fin3(f, e.reduced, c->stream);
     LAUNCHCHK(c, "count finalize");
@@ -510,7 +513,7 @@ int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights*
                  int64_t* N_tri, double* N_eff, const float* rho3_w) {
   if (e.ntri == 0) return BS_OK;
   int rc;
-  int nparts = (int)e.nblk;
+  int nparts = (int)(e.fp64 ? e.nblk64 : e.nblk);
   if (e.fused) {
     rc = fields3_enqueue(c, vis, w, e.pd, e.fd, nullptr);
     if (rc) return rc;
@@ -530,14 +533,16 @@ int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights*
     if (c->timing) { (void)hipEventRecord(c->ev[5], c->stream); (void)hipEventRecord(c->ev[2], c->stream); }
     Con3Args ca{};
     ca.F = e.F; ca.vox = e.nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
-    ca.chunk = e.chunk; ca.partial = e.partial;
-    launch_contract3(ca, e.fp64 ? 0 : (e.precision == BS_FP32 ? 1 : 2), (int)e.nblk, c->stream);
+    ca.chunk = e.fp64 ? e.chunk64 : e.chunk; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
+    if (e.fp64) launch_contract64(ca, (int)e.nblk64, c->stream);
+    else launch_contract3(ca, e.precision == BS_FP32 ? 1 : 2, (int)e.nblk, c->stream);
     LAUNCHCHK(c, "contraction");
   }
   if (c->timing) (void)hipEventRecord(c->ev[3], c->stream);
   Fin3Args f{};
   f.partial = e.partial; f.nparts = nparts; f.tri_pair = e.d_tp; f.tri_col = e.d_tc; f.ntri = e.ntri;
-  if (e.fused && e.dft) { f.pstride = DFT_WAVES; f.nent = (e.npairs + 15) / 16 * 16 * 32; }
+  if (e.fused && e.dft) f.pstride = DFT_WAVES;
+  if (e.fp64 || (e.fused && e.dft)) f.nent = (e.npairs + 15) / 16 * 16 * 32;
   f.T3D = e.d_counts; f.rho3 = e.rho3; f.rho3_w = rho3_w; f.nc = b->P.nc; f.nvox = (double)e.nvox; f.norm = norm; f.sfac = e.sfac;
   f.B = B; f.N = N_tri; f.Neff = N_eff;
   launch_fin3(f, e.reduced, c->stream);

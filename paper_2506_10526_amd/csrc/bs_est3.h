@@ -57,6 +57,7 @@ struct Est3 {
   std::vector<int> blocks;
   int *d_pairs = nullptr, *d_tp = nullptr, *d_tc = nullptr;
   long long nvox = 0, nblk = 0, chunk = 0;
+  long long nblk64 = 0, chunk64 = 0;   // blocks of the FP64 contraction and their voxels
   double *partial = nullptr, *reduced = nullptr;
   double rho3 = 1.0;
   const int64_t* d_counts = nullptr;

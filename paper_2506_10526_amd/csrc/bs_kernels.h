@@ -183,7 +183,11 @@ struct Con3Args {
   int npairs;                  // <= 112
   long long chunk;             // voxels per block (multiple of 128)
   double* partial;             // [gridDim.x][112][32]
+  int ct1;                     // FP64 form: pair row tiles (the leading ones) contracted against fields 16..31 too
 };
+constexpr int kCon64Fields = 32;
+// FP64 form: writes the rows of the pair tiles in use only
+void launch_contract64(const Con3Args& a, int nblocks, hipStream_t s);
 
 struct Fin3Args {
   const double* partial; int nparts;  // reduce over parts: part p at partial + p * pstride * 112 * 32
@@ -203,7 +207,7 @@ void launch_delay3_f64(const Delay3Args& a, hipStream_t s, size_t lds);
 void launch_vpass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds);
 void launch_upass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds);
 void launch_etapass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds);
-void launch_contract3(const Con3Args& a, int mode, int nblocks, hipStream_t s);  // mode: 0 FP64, 1 FP32, 2 split
+void launch_contract3(const Con3Args& a, int mode, int nblocks, hipStream_t s);  // mode: 1 FP32, 2 split
 struct Fused3Args {
   const void* G;               // line-major delay spectra G_j[line][eta] (complex float)
   const long long* offG;       // per block

@@ -343,7 +343,7 @@ __device__ __forceinline__ void split8(const float* v, bf16x8& h, bf16x8& l) {
 }
 
 template <int MODE>
-using acc_t = typename std::conditional<MODE == 0, f64x4, f32x4>::type;
+using acc_t = f32x4;
 
 // One 32-voxel step of one wave: voxels v0 .. v0+31 of the LDS field rows sF + j*ld
 // (j < nbu; rows beyond nbu read as zero).  A rows are the pair products F_a F_b, B columns
@@ -415,10 +415,7 @@ __device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int 
 #pragma unroll
           for (int ct = 0; ct < C3_CT; ++ct) {
             if (ct < CT) {
-              if constexpr (MODE == 0)
-                acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[ct], acc[rt][ct], 0, 0, 0);
-              else
-                acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[ct], acc[rt][ct], 0, 0, 0);
+              acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[ct], acc[rt][ct], 0, 0, 0);
             }
           }
         }
@@ -451,8 +448,7 @@ __device__ __forceinline__ void con3_store(acc_t<MODE> (&acc)[C3_RT][C3_CT], dou
         for (int j = 0; j < C3_CT; ++j)
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            // 16x16 MFMA output rows: 4*(lane/16)+q for the f32/bf16 forms, lane/16+4*q for f64
-            int p = i * 16 + (MODE == 0 ? kq + 4 * q : kq * 4 + q), c = j * 16 + r16;
+            int p = i * 16 + kq * 4 + q, c = j * 16 + r16;   // 16x16 MFMA output rows 4*(lane/16)+q
             red[p * 32 + c] += acc64[i][j][q] + (double)acc[i][j][q];
           }
     }
@@ -462,7 +458,7 @@ __device__ __forceinline__ void con3_store(acc_t<MODE> (&acc)[C3_RT][C3_CT], dou
 }
 
 // Contraction over precomputed fields F[j][vox] streamed through LDS in 128-voxel slabs.
-template <int MODE, typename T>  // MODE 0: FP64 MFMA, 1: FP32 MFMA, 2: split-BF16 MFMA
+template <int MODE, typename T>  // MODE 1: FP32 MFMA, 2: split-BF16 MFMA
 __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
   __shared__ T sF[32 * C3_LDS];
   __shared__ int sp[2 * 112];
@@ -494,11 +490,124 @@ __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
     con3_step<MODE, T>(sF, C3_LDS, a.nbu, wave * 32, sp, RT, CT, acc);
     __syncthreads();
     since += C3_SLAB;
-    // FP32 forms: FP64 flush every 512 voxels.  FP64 form (the triangle counts): every slab, so
-    // that no accumulation chain is longer than one slab plus the slab count of the block.
-    if (since >= (MODE == 0 ? C3_SLAB : 512)) { since = 0; con3_flush<MODE>(acc, acc64); }
+    if (since >= 512) { since = 0; con3_flush<MODE>(acc, acc64); }   // FP64 flush
   }
   con3_store<MODE>(acc, acc64, red, a.partial + (size_t)blockIdx.x * 112 * 32);
+}
+
+// The FP64 form (FP64 data, triangle counts).  A block streams slabs of 128 voxels of all fields through
+// two LDS buffers, the next slab's loads in flight under the MFMAs of this one; wave w takes voxels 32 w ..
+// 32 w + 31, lane group g voxels 8 s + 2 g and + 1 of every eight (one 16-byte read per operand serves two
+// mfma_f64_16x16x4 steps; the row stride of 130 doubles puts 16 rows on distinct banks), row nbu of a
+// buffer is zero and stands in for padding pairs and fields.  Only the leading a.ct1 pair tiles serve a
+// third field past 15.  Sums: MFMA chains of C64_FLUSH voxels a wave, added into a second FP64 sum (the
+// count certification bounds the longest chain of roundings).  Bound: HBM (each field read once) and FP64
+// issue.  Against 128-voxel slabs
+// without prefetch, a flush every slab and seven pair tiles always: 48^2 x 768, 20 shells 630 -> 116 us,
+// 256^2 x 768 counts 16.4 -> 2.9 ms (8 GB of fields).
+constexpr int C64_SLAB = 128, C64_LD = C64_SLAB + 2, C64_FLUSH = 128;
+template <int RT>
+__global__ __launch_bounds__(256, RT <= 4 ? 2 : 1) void k3_contract64(Con3Args a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  double* sh = (double*)smem_raw;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int nbu = a.nbu, bufsz = (nbu + 1) * C64_LD;
+  const bool wide = nbu > 16;
+  for (int e = tid; e < 2 * C64_LD; e += 256) sh[(e / C64_LD) * bufsz + nbu * C64_LD + e % C64_LD] = 0.0;
+  // LDS offsets of the lane's operand rows
+  int oa[RT], ob[RT], oc[2];
+  const int v0 = 32 * w + 2 * g;
+#pragma unroll
+  for (int i = 0; i < RT; ++i) {
+    const int p = 16 * i + c;
+    oa[i] = (p < a.npairs ? a.pairs[2 * p] : nbu) * C64_LD + v0;
+    ob[i] = (p < a.npairs ? a.pairs[2 * p + 1] : nbu) * C64_LD + v0;
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) oc[j] = (16 * j + c < nbu ? 16 * j + c : nbu) * C64_LD + v0;
+  f64x4 acc[RT][2] = {}, sum[RT][2] = {};
+  const long long x_beg = (long long)blockIdx.x * a.chunk;
+  const long long x_end = x_beg + a.chunk < a.vox ? x_beg + a.chunk : a.vox;
+  // staging: 64 threads a field row, two voxels each (the voxel count is even), four rows a pass
+  constexpr int Q = kCon64Fields / 4;
+  double2 v[Q];
+  const int kk = 2 * (tid & 63), jr = tid >> 6;
+  const double* F = (const double*)a.F + kk;
+  auto load = [&](long long x0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int j = jr + 4 * q;
+      v[q] = make_double2(0.0, 0.0);
+      if (j < nbu && x0 + kk < x_end) v[q] = *(const double2*)(F + (long long)j * a.vox + x0);
+    }
+  };
+  auto store = [&](double* buf) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int j = jr + 4 * q;
+      if (j < nbu) *(double2*)&buf[j * C64_LD + kk] = v[q];
+    }
+  };
+  load(x_beg);
+  store(sh);
+  __syncthreads();
+  int cur = 0, since = 0;
+  for (long long x0 = x_beg; x0 < x_end; x0 += C64_SLAB) {
+    const bool more = x0 + C64_SLAB < x_end;
+    if (more) load(x0 + C64_SLAB);
+    const double* buf = sh + cur * bufsz;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double2 b0 = *(const double2*)&buf[oc[0] + 8 * s];
+      double2 b1 = make_double2(0.0, 0.0);
+      if (wide) b1 = *(const double2*)&buf[oc[1] + 8 * s];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        const double2 x = *(const double2*)&buf[oa[i] + 8 * s], y = *(const double2*)&buf[ob[i] + 8 * s];
+        const double p0 = x.x * y.x, p1 = x.y * y.y;
+        acc[i][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(p0, b0.x, acc[i][0], 0, 0, 0);
+        acc[i][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(p1, b0.y, acc[i][0], 0, 0, 0);
+        if (wide && i < a.ct1) {
+          acc[i][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(p0, b1.x, acc[i][1], 0, 0, 0);
+          acc[i][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(p1, b1.y, acc[i][1], 0, 0, 0);
+        }
+      }
+    }
+    since += C64_SLAB / 4;
+    if (since >= C64_FLUSH || !more) {
+      since = 0;
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+        }
+    }
+    if (more) {
+      store(sh + (cur ^ 1) * bufsz);
+      __syncthreads();
+      cur ^= 1;
+    }
+  }
+  // the waves' sums in wave order; element q of a lane is pair row g + 4 q
+  __syncthreads();
+  for (int wv = 0; wv < 4; ++wv) {
+    if (w == wv) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            double* r = &sh[(16 * i + g + 4 * q) * 32 + 16 * j + c];
+            *r = wv ? *r + sum[i][j][q] : sum[i][j][q];
+          }
+    }
+    __syncthreads();
+  }
+  double* out = a.partial + (size_t)blockIdx.x * 112 * 32;
+  for (int e = tid; e < RT * 16 * 32; e += 256) out[e] = sh[e];
 }
 
 // Fused C2R along eta + contraction.  A block owns a range of (x_u, x_v) lines; for each line
@@ -1057,9 +1166,25 @@ void launch_etapass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, si
   else { set_lds<float>((const void*)k3_etapass<float>, lds); hipLaunchKernelGGL(k3_etapass<float>, dim3(nwork), dim3(256), lds, s, a); }
 }
 void launch_contract3(const Con3Args& a, int mode, int nblocks, hipStream_t s) {
-  if (mode == 0) hipLaunchKernelGGL((k3_contract<0, double>), dim3(nblocks), dim3(256), 0, s, a);
-  else if (mode == 1) hipLaunchKernelGGL((k3_contract<1, float>), dim3(nblocks), dim3(256), 0, s, a);
+  if (mode == 1) hipLaunchKernelGGL((k3_contract<1, float>), dim3(nblocks), dim3(256), 0, s, a);
   else hipLaunchKernelGGL((k3_contract<2, float>), dim3(nblocks), dim3(256), 0, s, a);
+}
+template <int RT>
+static void launch_contract64_rt(const Con3Args& a, int nblocks, hipStream_t s) {
+  const size_t lds = std::max(2 * (size_t)(a.nbu + 1) * C64_LD, (size_t)RT * 16 * 32) * sizeof(double);
+  set_lds<double>((const void*)k3_contract64<RT>, lds);
+  hipLaunchKernelGGL(k3_contract64<RT>, dim3(nblocks), dim3(256), lds, s, a);
+}
+void launch_contract64(const Con3Args& a, int nblocks, hipStream_t s) {
+  switch ((a.npairs + 15) / 16) {
+    case 1: launch_contract64_rt<1>(a, nblocks, s); break;
+    case 2: launch_contract64_rt<2>(a, nblocks, s); break;
+    case 3: launch_contract64_rt<3>(a, nblocks, s); break;
+    case 4: launch_contract64_rt<4>(a, nblocks, s); break;
+    case 5: launch_contract64_rt<5>(a, nblocks, s); break;
+    case 6: launch_contract64_rt<6>(a, nblocks, s); break;
+    default: launch_contract64_rt<7>(a, nblocks, s); break;
+  }
 }
 void launch_fin3(const Fin3Args& a, double* reduced, hipStream_t s) {
   const int groups = (a.nparts + RGROUP - 1) / RGROUP;
