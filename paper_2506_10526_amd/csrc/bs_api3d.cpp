@@ -166,6 +166,7 @@ int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3
   const int M = nc;
   a.work = fd.d_we; a.off_in = fd.d_offG; a.off_out = nullptr; a.in = fd.Gm; a.out = F;
   a.tw = fd.tw_nc; a.plan = make_fft_plan(M / 2); a.NL = p.NLe; a.M = M;
+  if (fd.fp64) std::reverse(a.plan.rad, a.plan.rad + a.plan.nr);   // smallest radices first, as above
   a.scale = 1.0 / ((double)M * (double)n * (double)n);
   a.fstride = (long long)M * n * n;
   launch_etapass3(a, (int)p.we.size(), fd.fp64, c->stream, 2 * (size_t)p.NLe * (M / 2 + 1) * cz);

@@ -320,6 +320,55 @@ __global__ __launch_bounds__(256) void k3_etapass(Pass3Args a) {
   }
 }
 
+// The FP64 eta pass at lengths with a compile-time transform: in place in one buffer (half the LDS, twice
+// the blocks a CU), both spectrum entries of six of a thread's elements in flight, and neighbouring line
+// blocks on one XCD, so that the 64-byte pieces they write to one row of lines meet in its L2.  Bound: HBM, the
+// fields written once.  48^2 x 768, 20 shells (283 MB): 362 us with the two-buffer form above,
+// now 134; 256^2 x 768 (8 GB): 10.5 -> 4.2 ms.
+constexpr int ETA64_LINES = 8;
+template <int L>   // M / 2
+__global__ __launch_bounds__(256) void k3_etapass64(Pass3Args a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  typedef Cx<double> C;
+  constexpr int LD = L + 1, NL = ETA64_LINES, U = 6;
+  const Work3 w = a.work[xcd_block(blockIdx.x, gridDim.x)];
+  const long long n2 = (long long)a.g.n * a.g.n;
+  const int nl = (int)min((long long)NL, n2 - w.start), Hj = a.hj[w.j];
+  C* A = (C*)smem_raw;
+  C* tw = A + NL * LD;
+  for (int e = threadIdx.x; e < 2 * L; e += 256) tw[e] = ((const C*)a.tw)[e];
+  const C* in = (const C*)a.in + a.off_in[w.j] + (size_t)w.start * (Hj + 1);
+  for (int e0 = threadIdx.x; e0 < NL * L; e0 += U * 256) {
+    C hk[U], hm[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned e = e0 + 256 * u, l = e / L, k = e % L;
+      const C* gl = in + (size_t)l * (Hj + 1);
+      hk[u] = hm[u] = cmk(0.0, 0.0);
+      if ((int)l < nl) {
+        if ((int)k <= Hj) hk[u] = gl[k];
+        if (L - (int)k <= Hj) hm[u] = gl[L - k];
+      }
+    }
+    if (e0 == (int)threadIdx.x) __syncthreads();   // the table
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned e = e0 + 256 * u, l = e / L, k = e % L;
+      if ((int)l < nl) A[l * LD + k] = c2r_pack<double>((int)k, L, [&](int v) { return v == (int)k ? hk[u] : hm[u]; }, tw, 1);
+    }
+  }
+  __syncthreads();
+  lds_fft_ct<+1, double, L, NL, 256, LD>(A, nl, tw, 2);
+  double* out = (double*)a.out + (size_t)w.j * a.fstride + w.start;
+  for (int e = threadIdx.x; e < NL * L; e += 256) {
+    const int k = e / NL, l = e % NL;
+    if (l >= nl) continue;
+    const C z = A[l * LD + k];
+    out[(size_t)(2 * k) * n2 + l] = z.x * a.scale;
+    out[(size_t)(2 * k + 1) * n2 + l] = z.y * a.scale;
+  }
+}
+
 // --------------------------------------------------------------- contraction
 // C[p][c] = sum_x F_a(x) F_b(x) F_c(x) for every pair p = (a, b) and field c, as a GEMM
 // with M = pairs, N = fields, K = voxels: 16 x 16 MFMA tiles, up to 7 x 2 tiles per wave.
@@ -1160,8 +1209,25 @@ void launch_upass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size
   if (fp64) launch_pass3_ip<double>(true, a, nwork, s, lds);
   else launch_pass3_ip<float>(true, a, nwork, s, lds);
 }
+template <int L>
+static void launch_etapass64(const Pass3Args& a, int nwork, hipStream_t s) {
+  const size_t lds = (ETA64_LINES * (L + 1) + 2 * L) * sizeof(Cx<double>);
+  set_lds<double>((const void*)k3_etapass64<L>, lds);
+  hipLaunchKernelGGL(k3_etapass64<L>, dim3(nwork), dim3(256), lds, s, a);
+}
 void launch_etapass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds) {
   if (nwork <= 0) return;
+  if (fp64 && a.NL == ETA64_LINES && fft_ct_plan(a.plan, a.plan.L)) {
+    switch (a.plan.L) {
+      case 48: launch_etapass64<48>(a, nwork, s); return;
+      case 64: launch_etapass64<64>(a, nwork, s); return;
+      case 96: launch_etapass64<96>(a, nwork, s); return;
+      case 128: launch_etapass64<128>(a, nwork, s); return;
+      case 192: launch_etapass64<192>(a, nwork, s); return;
+      case 256: launch_etapass64<256>(a, nwork, s); return;
+      case 384: launch_etapass64<384>(a, nwork, s); return;
+    }
+  }
   if (fp64) { set_lds<double>((const void*)k3_etapass<double>, lds); hipLaunchKernelGGL(k3_etapass<double>, dim3(nwork), dim3(256), lds, s, a); }
   else { set_lds<float>((const void*)k3_etapass<float>, lds); hipLaunchKernelGGL(k3_etapass<float>, dim3(nwork), dim3(256), lds, s, a); }
 }
