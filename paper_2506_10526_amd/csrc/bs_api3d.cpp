@@ -87,8 +87,9 @@ const void* ctx_dft_twiddle(bs_ctx* c, int M) {
   return d;
 }
 
+// M: length of the eta pass (nc, or a shorter grid that closes the same triangles)
 int fields3_prepare(bs_ctx* c, const bs_bins* b, bool fp64, bool indicator, const Plan3& p, const std::string& t,
-                    Fields3Dev& fd) {
+                    int M, Fields3Dev& fd) {
   const auto& P = b->P;
   const int n = P.n, nc = P.nc, nh = P.nh, nub = 2 * P.vmax + 1, nvb = P.vmax + 1;
   const size_t cz = fp64 ? 16 : 8;
@@ -102,7 +103,9 @@ int fields3_prepare(bs_ctx* c, const bs_bins* b, bool fp64, bool indicator, cons
   g.uvm = nullptr;
   fd.tw_nc = ctx_twiddle(c, nc, fp64);
   fd.tw_n = ctx_twiddle(c, n, fp64);
-  if (!fd.tw_nc || !fd.tw_n) return ctx_fail(c, BS_ENOMEM, "twiddle tables");
+  fd.M = M;
+  fd.tw_M = ctx_twiddle(c, M, fp64);
+  if (!fd.tw_nc || !fd.tw_n || !fd.tw_M) return ctx_fail(c, BS_ENOMEM, "twiddle tables");
   fd.D = nullptr;
   if (!indicator) {
     fd.D = ctx_ws(c, (t + "_D").c_str(), (size_t)(2 * p.H + 1) * nub * nvb * cz);
@@ -122,7 +125,7 @@ int fields3_prepare(bs_ctx* c, const bs_bins* b, bool fp64, bool indicator, cons
 }
 
 // Launches the field pipeline prepared in `fd` (no allocation, copy or synchronisation).
-// With F != NULL the eta pass writes the real fields F ([block][nc n^2]); with F == NULL the
+// With F != NULL the eta pass writes the real fields F ([block][fd.M n^2]); with F == NULL the
 // pipeline stops after the u pass and the caller consumes the line-major spectra fd.Gm.
 int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3& p, Fields3Dev& fd, void* F) {
   const int n = fd.g.n, nc = fd.g.nc;
@@ -162,10 +165,10 @@ int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3
   LAUNCHCHK(c, "u pass");
   a.gs = nullptr; a.off_gs = nullptr; a.ip = 0; a.shell_iv = 0;
   if (!F) return BS_OK;
-  // eta pass (C2R), output length nc
-  const int M = nc;
+  // eta pass (C2R), output length M
+  const int M = fd.M;
   a.work = fd.d_we; a.off_in = fd.d_offG; a.off_out = nullptr; a.in = fd.Gm; a.out = F;
-  a.tw = fd.tw_nc; a.plan = make_fft_plan(M / 2); a.NL = p.NLe; a.M = M;
+  a.tw = fd.tw_M; a.plan = make_fft_plan(M / 2); a.NL = p.NLe; a.M = M;
   if (fd.fp64) std::reverse(a.plan.rad, a.plan.rad + a.plan.nr);   // smallest radices first, as above
   a.scale = 1.0 / ((double)M * (double)n * (double)n);
   a.fstride = (long long)M * n * n;
@@ -176,10 +179,10 @@ int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3
 
 // Both steps at once (fields output, count pass).
 int run_fields3(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights* w, bool fp64, bool indicator,
-                const Plan3& p, void* F, const std::string& tag) {
+                const Plan3& p, int M, void* F, const std::string& tag) {
   if (b->P.nc % 2) return ctx_fail(c, BS_EUNSUPPORTED, "3D fields need an even number of channels");
   Fields3Dev fd;
-  int rc = fields3_prepare(c, b, fp64, indicator, p, tag, fd);
+  int rc = fields3_prepare(c, b, fp64, indicator, p, tag, M, fd);
   if (rc) return rc;
   return fields3_enqueue(c, vis, w, p, fd, F);
 }
@@ -220,7 +223,7 @@ int filter_fields_3d(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weig
       Plan3 p;
       build_plan3(P, std::vector<int>{j}, f64, p);
       void* dst = (char*)out + (size_t)j * fst * esz;
-      rc = run_fields3(c, b, vis, w, f64, pass == 1, p, dst, pass == 0 ? "ff3" : "ff3c");
+      rc = run_fields3(c, b, vis, w, f64, pass == 1, p, P.nc, dst, pass == 0 ? "ff3" : "ff3c");
       if (rc) return rc;
     }
   }
@@ -325,9 +328,18 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
   e.nblk = std::min<long long>(2048, (e.nvox + 127) / 128);
   e.chunk = ((e.nvox + e.nblk - 1) / e.nblk + 127) / 128 * 128;
   e.nblk = (e.nvox + e.chunk - 1) / e.chunk;
-  e.nblk64 = std::min<long long>(1024, (e.nvox + 127) / 128);
-  e.chunk64 = ((e.nvox + e.nblk64 - 1) / e.nblk64 + 127) / 128 * 128;
-  e.nblk64 = (e.nvox + e.chunk64 - 1) / e.chunk64;
+  // FP64 fields (counts and FP64 data) on the shortest delay grid that closes the same triangles and has a
+  // compile-time transform: with true closure (3 H < nc) any M > 3 H does, and the sums are rescaled
+  // by (M / nc)^2.  At 768 channels and H = 104 it halves the fields (M = 384).
+  e.M64 = P.nc;
+  if (P.true_closure && !getenv("BS_3D_FULLGRID"))
+    for (int m : {96, 128, 192, 256, 384, 512, 768})
+      if (m > 3 * P.eta_max && m < P.nc) { e.M64 = m; break; }
+  e.vox64 = (long long)e.M64 * P.n * P.n;
+  // blocks of a dozen slabs or more, at most 1024 (two resident a CU, two rounds)
+  e.nblk64 = std::max<long long>(1, std::min<long long>(1024, e.vox64 / (12 * 128)));
+  e.chunk64 = ((e.vox64 + e.nblk64 - 1) / e.nblk64 + 127) / 128 * 128;
+  e.nblk64 = (e.vox64 + e.chunk64 - 1) / e.chunk64;
   // partial sums: one slot per contraction block, or per wave of the MFMA synthesis kernel (8 x 256)
   e.partial = (double*)ctx_ws(c, (tag + "_partial").c_str(), (size_t)std::max<long long>(e.nblk, 2048) * 112 * 32 * 8);
   e.reduced = (double*)ctx_ws(c, (tag + "_reduced").c_str(), (size_t)112 * 32 * 8);
@@ -351,12 +363,11 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
   }
   auto it = c->counts.find(key);
   if (it == c->counts.end()) {
-    const long long nvox = e.nvox;
     // Certification of the rounding: the FP64 count fields come from C2C passes along v and u
     // and a C2R pass along eta (three rounded normalisations); the contraction's longest chain
     // of roundings is one run of MFMA steps (128 products), one flush per run of a wave's quarter of the
     // block's chunk, the four waves of the block, and the two stages of the fixed-order partial sums.
-    const double eps_field = bsplan::field_error_units(2 * bsplan::fft_stage_units(P.n) + bsplan::fft_stage_units(P.nc) + 2, 3);
+    const double eps_field = bsplan::field_error_units(2 * bsplan::fft_stage_units(P.n) + bsplan::fft_stage_units(e.M64) + 2, 3);
     const double depth = 129.0 + (double)((e.chunk64 / 4 + 127) / 128) + 5.0 + (double)kReduceGroup +
                          (double)((e.nblk64 + kReduceGroup - 1) / kReduceGroup) + 1.0;
     double bound = 0.0;
@@ -369,12 +380,12 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
                                         std::to_string(bound) + " >= 1/2)");
     Plan3 pc;
     build_plan3(P, e.blocks, true, pc);
-    void* F64 = ctx_ws(c, "c3_F64", (size_t)e.blocks.size() * nvox * 8);
+    void* F64 = ctx_ws(c, "c3_F64", (size_t)e.blocks.size() * e.vox64 * 8);
     if (!F64) return ctx_fail(c, BS_ENOMEM, "workspace (count fields)");
-    rc = run_fields3(c, b, nullptr, w, true, true, pc, F64, "c3c");
+    rc = run_fields3(c, b, nullptr, w, true, true, pc, e.M64, F64, "c3c");
     if (rc) return rc;
     Con3Args ca{};
-    ca.F = F64; ca.vox = nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
+    ca.F = F64; ca.vox = e.vox64; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
     ca.chunk = e.chunk64; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
     launch_contract64(ca, (int)e.nblk64, c->stream);
     LAUNCHCHK(c, "count contraction");
@@ -383,7 +394,7 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
     if (!Ssum || !bad) return ctx_fail(c, BS_ENOMEM, "workspace (count sums)");
     Fin3Args f{};
     f.partial = e.partial; f.nparts = (int)e.nblk64; f.nent = (e.npairs + 15) / 16 * 16 * 32; f.tri_pair = e.d_tp; f.tri_col = e.d_tc; f.ntri = ntri;
-    f.T3D = nullptr; f.Ssum = Ssum; f.sfac = (double)nvox * (double)nvox;
+    f.T3D = nullptr; f.Ssum = Ssum; f.sfac = (double)e.vox64 * (double)e.vox64;
     launch_fin3(f, e.reduced, c->stream);
     LAUNCHCHK(c, "count finalize");
     CountCache cc;
@@ -420,10 +431,10 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
       if (m > 3 * P.eta_max && fft_len_ok(m) && P.nc % 2 == 0) { M = m; break; }
   }
   e.fused = !e.fp64 && (M % 128 == 0) && !getenv("BS_3D_UNFUSED");
-  if (!e.fused) M = P.nc;
+  if (!e.fused) M = e.fp64 ? e.M64 : P.nc;
   e.M = M;
   e.sfac = ((double)M / P.nc) * ((double)M / P.nc);
-  rc = fields3_prepare(c, b, e.fp64, false, e.pd, tag + "d", e.fd);
+  rc = fields3_prepare(c, b, e.fp64, false, e.pd, tag + "d", e.fp64 ? e.M64 : P.nc, e.fd);
   if (rc) return rc;
   if (e.fused) {
     const long long nlines = (long long)P.n * P.n;
@@ -502,7 +513,7 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
       e.dlds = dlds;
     }
   } else {
-    e.F = ctx_ws(c, (tag + "_F").c_str(), (size_t)e.blocks.size() * e.nvox * (e.fp64 ? 8 : 4));
+    e.F = ctx_ws(c, (tag + "_F").c_str(), (size_t)e.blocks.size() * (e.fp64 ? e.vox64 * 8 : e.nvox * 4));
     if (!e.F) return ctx_fail(c, BS_ENOMEM, "workspace (fields)");
   }
   return BS_OK;
@@ -533,7 +544,7 @@ int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights*
     if (rc) return rc;
     if (c->timing) { (void)hipEventRecord(c->ev[5], c->stream); (void)hipEventRecord(c->ev[2], c->stream); }
     Con3Args ca{};
-    ca.F = e.F; ca.vox = e.nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
+    ca.F = e.F; ca.vox = e.fp64 ? e.vox64 : e.nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
     ca.chunk = e.fp64 ? e.chunk64 : e.chunk; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
     if (e.fp64) launch_contract64(ca, (int)e.nblk64, c->stream);
     else launch_contract3(ca, e.precision == BS_FP32 ? 1 : 2, (int)e.nblk, c->stream);

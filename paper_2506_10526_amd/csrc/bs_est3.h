@@ -43,6 +43,8 @@ struct Fields3Dev {
   long long* d_offGs = nullptr;
   int* d_ctab = nullptr;             // fragment copy table of the split-BF16 3D kernel
   double gscale = 1.0;               // folded into the fragments: 1 / (M n^2)
+  int M = 0;                         // length of the eta pass (the fields' delay grid)
+  const void* tw_M = nullptr;
 };
 
 // Everything one 3D estimate needs besides the cube: resolved on the host once (plans, tables,
@@ -57,7 +59,8 @@ struct Est3 {
   std::vector<int> blocks;
   int *d_pairs = nullptr, *d_tp = nullptr, *d_tc = nullptr;
   long long nvox = 0, nblk = 0, chunk = 0;
-  long long nblk64 = 0, chunk64 = 0;   // blocks of the FP64 contraction and their voxels
+  int M64 = 0;                          // delay grid of the FP64 fields (counts, FP64 data)
+  long long vox64 = 0, nblk64 = 0, chunk64 = 0;   // its voxels, the FP64 contraction's blocks and their voxels
   double *partial = nullptr, *reduced = nullptr;
   double rho3 = 1.0;
   const int64_t* d_counts = nullptr;

@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256) void k3_etapass(Pass3Args a) {
 // the blocks a CU), both spectrum entries of six of a thread's elements in flight, and neighbouring line
 // blocks on one XCD, so that the 64-byte pieces they write to one row of lines meet in its L2.  Bound: HBM, the
 // fields written once.  48^2 x 768, 20 shells (283 MB): 362 us with the two-buffer form above,
-// now 134; 256^2 x 768 (8 GB): 10.5 -> 4.2 ms.
+// now 134 (46 on the 192-point grid that closes its triangles); 256^2 x 768 (8 GB): 10.5 -> 4.2 ms (1.9 on 384).
 constexpr int ETA64_LINES = 8;
 template <int L>   // M / 2
 __global__ __launch_bounds__(256) void k3_etapass64(Pass3Args a) {
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
 // count certification bounds the longest chain of roundings).  Bound: HBM (each field read once) and FP64
 // issue.  Against 128-voxel slabs
 // without prefetch, a flush every slab and seven pair tiles always: 48^2 x 768, 20 shells 630 -> 116 us,
-// 256^2 x 768 counts 16.4 -> 2.9 ms (8 GB of fields).
+// 256^2 x 768 counts 16.4 -> 2.9 ms (8 GB of fields; 1.6 ms on the 384-point delay grid).
 constexpr int C64_SLAB = 128, C64_LD = C64_SLAB + 2, C64_FLUSH = 128;
 template <int RT>
 __global__ __launch_bounds__(256, RT <= 4 ? 2 : 1) void k3_contract64(Con3Args a) {

@@ -47,3 +47,39 @@ def test_counts_and_fp64_estimate(ctx, n, nc, shells):
         bs.bs_free_bins(h)
     assert nt == len(b.triangles) and np.array_equal(Ng, T)
     compare_B(Bg, Bref, T, scale, 1e-10)
+
+
+@pytest.mark.parametrize("n,nc,eta", [(12, 128, 31), (12, 128, 32), (16, 192, 42), (16, 192, 43), (16, 256, 63), (12, 768, 127)])
+def test_short_delay_grid_equals_full_grid(ctx, monkeypatch, n, nc, eta):
+    """H = eta on either side of M > 3 H (H = 31 runs on 96 points, 32 not, and so on): the counts and the
+    FP64 estimates of the short delay grid and of the nc-point grid agree, counts bit for bit, B within
+    the rounding of two FP64 transforms and sums (1e-12 of B_abs)."""
+    # k = q_eta with cpar = 1 and a small k_perp, so the top edge fixes the largest delay
+    edges = np.array([1.0, 0.3 * eta, 0.7 * eta, eta + 0.5])
+    kw = dict(du_lambda=0.05, r_mpc=2 * np.pi, rprime_mpc_per_mhz=2 * np.pi / nc, dnu_mhz=1.0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nc)
+    V = torch.randn((nc, n, n // 2 + 1), generator=g, device="cuda", dtype=torch.complex128)
+    out = []
+    for full in (False, True):
+        if full:
+            monkeypatch.setenv("BS_3D_FULLGRID", "1")
+        c = Ctx()
+        h, nt = bs.bs_make_bins(c.h, bs.BS_SHELL_K, n, nc, edges, **kw)
+        try:
+            B = torch.empty(nt, dtype=torch.float64, device="cuda")
+            N = torch.empty(nt, dtype=torch.int64, device="cuda")
+            assert bs.bs_bins_info(h)[0] == eta
+            bs.bs_estimate_3d(c.h, h, V, bs.BS_FP64, B, N)
+            F = torch.empty((3, nc, n, n), dtype=torch.float64, device="cuda")
+            bs.bs_filter_fields(c.h, h, V, 1, bs.BS_FP64, F)
+            out.append((host(B), host(N)))
+            Fa, tri = F.abs().reshape(3, -1), bs.bs_bins_triangles(h, nt, 3)[0]
+            mag = np.array([float((Fa[i] * Fa[j] * Fa[k]).sum()) for i, j, k in tri]) * nc * n * n
+        finally:
+            bs.bs_free_bins(h)
+            c.close()
+    assert np.array_equal(out[0][1], out[1][1])
+    ok = out[0][1] > 0
+    assert ok.any()
+    assert np.all(np.abs(out[0][0][ok] - out[1][0][ok]) <= 1e-12 * mag[ok] / out[0][1][ok])
