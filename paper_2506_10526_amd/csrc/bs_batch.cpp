@@ -49,14 +49,14 @@ struct BCube {
   std::vector<int64_t> tperp;
   GenArgs ga{};
   MabsFieldArgs fa{};
-  size_t off_vis = 0, off_g = 0, off_F = 0, off_Fh = 0, off_Fl = 0, off_S = 0;   // arena offsets
+  size_t off_vis = 0, off_F = 0, off_Fh = 0, off_Fl = 0, off_S = 0;   // arena offsets
   double* Bbar = nullptr;
   int32_t* Nnu = nullptr;
   long long products = 0;
   size_t bytes_fields() const { return (size_t)nbu * nc * (size_t)n * n; }
   size_t footprint(int kc) const {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
-    return al((size_t)nc * n * nh * 8) + al((size_t)nc * n * n * 4) + al(bytes_fields() * 4) + 2 * al(bytes_fields() * 2) +
+    return al((size_t)nc * n * nh * 8) + al(bytes_fields() * 4) + 2 * al(bytes_fields() * 2) +
            al((size_t)kc * ntri * n_nu1 * nc * (size_t)nc * 8);
   }
 };
@@ -158,7 +158,6 @@ bool tile_ok(int kind, int m1, int kchunks, int n, int nc, int n_nu1) {
 void enqueue_front(const BCube& q, char* arena, hipStream_t s) {
   GenArgs ga = q.ga;
   ga.W = (Cx<float>*)(arena + q.off_vis);
-  ga.g = (float*)(arena + q.off_g);
   launch_gen_set_state(const_cast<unsigned long long*>(ga.state), q.seed, q.real, s);
   launch_gen_cube(ga, s);
   MabsFieldArgs fa = q.fa;
@@ -233,7 +232,6 @@ int pick_tile(bs_ctx* c, bs_batch* bt, BCube& q, int nrings, hipStream_t s) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) / 256 * 256; return o; };
   t.off_vis = take((size_t)q.nc * q.n * q.nh * 8);
-  t.off_g = take((size_t)q.nc * q.n * q.n * 4);
   t.off_F = take(q.bytes_fields() * 4);
   t.off_Fh = take(q.bytes_fields() * 2);
   t.off_Fl = take(q.bytes_fields() * 2);
@@ -421,7 +419,6 @@ extern "C" int bs_batch_create(bs_ctx* c, const bs_batch_cube* cubes, int32_t nc
     size_t off = cur;
     auto take = [&](size_t bytes) { size_t o = off; off += (bytes + 255) / 256 * 256; return o; };
     q.off_vis = take((size_t)q.nc * q.n * q.nh * 8);
-    q.off_g = take((size_t)q.nc * q.n * q.n * 4);
     q.off_F = take(q.bytes_fields() * 4);
     q.off_Fh = take(q.bytes_fields() * 2);
     q.off_Fl = take(q.bytes_fields() * 2);

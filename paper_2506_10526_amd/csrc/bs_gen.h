@@ -16,7 +16,6 @@ struct GenArgs {
   double* part;                  // device per-block partial sums (>= max(nc, row blocks))
   const float* chw;              // channel weights [nc] or NULL
   Cx<float>* W;                  // output / work cube [nc][n][nh]
-  float* g;                      // real field [nc][n][n]
   const void* tw_n;              // exp(-2 pi i m / n)
   const void* tw_nc;             // exp(-2 pi i m / nc)
   FftPlan pn, pnc;               // lengths n and nc

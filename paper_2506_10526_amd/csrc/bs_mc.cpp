@@ -104,8 +104,7 @@ extern "C" int bs_generate_cube(bs_ctx* c, const bs_field_desc* d, uint64_t seed
   a.state = (unsigned long long*)ctx_ws(c, "gen_state", 64);
   a.stat = (double*)ctx_ws(c, "gen_stat", 64);
   a.part = (double*)ctx_ws(c, "gen_part", part_len(a) * 8);
-  a.g = (float*)ctx_ws(c, "gen_g", (size_t)d->nc * d->n * d->n * 4);
-  if (!a.state || !a.stat || !a.part || !a.g) return ctx_fail(c, BS_ENOMEM, "generator workspace");
+  if (!a.state || !a.stat || !a.part) return ctx_fail(c, BS_ENOMEM, "generator workspace");
   a.chw = chan_w;
   a.W = (Cx<float>*)vis;
   launch_gen_set_state((unsigned long long*)a.state, seed, realization, c->stream);
@@ -233,7 +232,6 @@ extern "C" int bs_mc_create(bs_ctx* c, const bs_bins* b, const bs_field_desc* d,
   m->ga.state = m->state;
   m->ga.stat = (double*)mc_alloc(m, 64);
   m->ga.part = (double*)mc_alloc(m, part_len(m->ga) * 8);
-  m->ga.g = (float*)mc_alloc(m, (size_t)d->nc * d->n * d->n * 4);
   m->ga.W = (Cx<float>*)mc_alloc(m, cube);
   m->ga.chw = m->w.chan_w;
   const size_t nt = (size_t)std::max(m->ntri, 1);
@@ -242,7 +240,7 @@ extern "C" int bs_mc_create(bs_ctx* c, const bs_bins* b, const bs_field_desc* d,
   m->cnt = (long long*)mc_alloc(m, nt * 8);
   m->mean = (double*)mc_alloc(m, nt * 8);
   m->m2 = (double*)mc_alloc(m, nt * 8);
-  if (!m->state || !m->ga.stat || !m->ga.part || !m->ga.g || !m->ga.W || !m->B || !m->N || !m->cnt || !m->mean || !m->m2) {
+  if (!m->state || !m->ga.stat || !m->ga.part || !m->ga.W || !m->B || !m->N || !m->cnt || !m->mean || !m->m2) {
     mc_free(m);
     return ctx_fail(c, BS_ENOMEM, "Monte Carlo buffers");
   }
