@@ -348,16 +348,27 @@ struct GridArgs {
   // exp(i k_o . delta_i), k_o = knode[2o], knode[2o+1] (radians per wavelength), delta_i = U_i - du q_i
   // its offset from its grid point
   const double* knode;
-  // the LDS cells' block partials [nco][blocks][GRID_NHOT] (sums re, im and counts), stored whole
-  // by every block and added over blocks in block order by launch_grid_hot
+  unsigned* code;              // workspace: the baselines' grid points [nvis]
+  // the LDS cells |q_u| < hot, q_v < hot of a share of the baselines (share: a multiple of 4), its partials
+  // [nco][shares][grid_nhot(hot)] (sums re, im and counts) when a channel has more than one share
+  int hot;
+  long long share;
   double* hot_v;
   int* hot_c;
 };
-constexpr int GRID_HOT = 32;                                   // LDS cells: |q_u| < 32, q_v < 32
-constexpr int GRID_NHOT = (2 * GRID_HOT - 1) * GRID_HOT;
-constexpr int GRID_VPB = 16384;                                // visibilities a block
-inline long long grid_blocks(long long nvis) { return (nvis + GRID_VPB - 1) / GRID_VPB; }
-void launch_grid_hot(const GridArgs& a, hipStream_t s);
+constexpr __host__ __device__ int grid_nhot(int hot) { return (2 * hot - 1) * hot; }
+// LDS cells and shares.  From 32,768 baselines the 64-cell region (one block a CU, 162 KB) pays for clearing
+// and storing it, with as many shares as fill the chip once; below, 32 cells (40 KB, three blocks a CU)
+// and shares of 2048 baselines at least, up to two blocks a CU.
+inline void grid_layout(GridArgs& a) {
+  const bool big = a.nvis >= 32768;
+  a.hot = big ? 64 : 32;
+  const long long want = (big ? 256 : 512) / (a.nco > 0 ? a.nco : 1), most = (a.nvis + 2047) / 2048;
+  const long long k = want < 1 ? 1 : want < most ? want : most < 1 ? 1 : most;
+  a.share = ((a.nvis + k - 1) / k + 3) / 4 * 4;
+  if (a.share < 4) a.share = 4;
+}
+inline long long grid_shares(const GridArgs& a) { return a.nvis > 0 ? (a.nvis + a.share - 1) / a.share : 1; }
 void launch_grid_zero(const GridArgs& a, hipStream_t s);
 void launch_grid_scatter(const GridArgs& a, hipStream_t s);
 // out: complex64 (fp64 == 0) or complex128 [nco][n][n/2+1]; ng: int32 of the same shape
