@@ -648,6 +648,17 @@ static bool grid_workspace(bs_ctx* c, GridArgs& a) {
   const size_t part = grid_shares(a) > 1 ? (size_t)a.nco * grid_shares(a) * grid_nhot(a.hot) : 1;
   a.hot_v = static_cast<double*>(ctx_ws(c, "grid_hot_v", part * 2 * sizeof(double)));
   a.hot_c = static_cast<int*>(ctx_ws(c, "grid_hot_c", part * sizeof(int)));
+  if (a.cap > 0) {
+    const size_t plane = (size_t)a.n * (a.n / 2 + 1);
+    a.fcnt = static_cast<unsigned*>(ctx_ws(c, "grid_fcnt", (plane + 2) * sizeof(unsigned)));
+    a.foff = static_cast<unsigned*>(ctx_ws(c, "grid_foff", plane * sizeof(unsigned)));
+    a.fcell = static_cast<unsigned*>(ctx_ws(c, "grid_fcell", (size_t)a.cap * sizeof(unsigned)));
+    a.frank = static_cast<unsigned*>(ctx_ws(c, "grid_frank", (size_t)a.cap * sizeof(unsigned)));
+    a.flist = static_cast<unsigned*>(ctx_ws(c, "grid_flist", (size_t)a.cap * sizeof(unsigned)));
+    a.stage_v = static_cast<double*>(ctx_ws(c, "grid_stage_v", (size_t)a.nco * a.cap * 2 * sizeof(double)));
+    a.stage_c = static_cast<int*>(ctx_ws(c, "grid_stage_c", (size_t)a.nco * a.cap * sizeof(int)));
+    if (!a.fcnt || !a.foff || !a.fcell || !a.frank || !a.flist || !a.stage_v || !a.stage_c) a.cap = 0;   // no memory for it: atomics
+  }
   return a.code && a.hot_v && a.hot_c;
 }
 

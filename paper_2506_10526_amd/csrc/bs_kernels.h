@@ -348,7 +348,14 @@ struct GridArgs {
   // exp(i k_o . delta_i), k_o = knode[2o], knode[2o+1] (radians per wavelength), delta_i = U_i - du q_i
   // its offset from its grid point
   const double* knode;
-  unsigned* code;              // workspace: the baselines' grid points [nvis]
+  unsigned* code;              // workspace: the baselines' places [nvis]
+  // staging of the far baselines (cap slots a channel; 0: none, global atomics instead): far baselines per
+  // cell [n (n/2+1)] and two totals, a cell's first place in the list of slots, a slot's cell and rank in it,
+  // the list, group sums [nco][cap] (re, im) and counts
+  long long cap;
+  unsigned *fcnt, *foff, *fcell, *frank, *flist;
+  double* stage_v;
+  int* stage_c;
   // the LDS cells |q_u| < hot, q_v < hot of a share of the baselines (share: a multiple of 4), its partials
   // [nco][shares][grid_nhot(hot)] (sums re, im and counts) when a channel has more than one share
   int hot;
@@ -367,6 +374,10 @@ inline void grid_layout(GridArgs& a) {
   const long long k = want < 1 ? 1 : want < most ? want : most < 1 ? 1 : most;
   a.share = ((a.nvis + k - 1) / k + 3) / 4 * 4;
   if (a.share < 4) a.share = 4;
+  // staging: a slot for every baseline within 1 GiB (slots past it: atomics; slots and ranks are 32 bits); its
+  // two extra launches do not pay in small calls (8128 x 24: 20 us in all, 21 with them)
+  const long long slots = (1LL << 30) / (20LL * (a.nco > 0 ? a.nco : 1));
+  a.cap = !big || a.nvis >> 31 ? 0 : a.nvis < slots ? a.nvis : slots;
 }
 inline long long grid_shares(const GridArgs& a) { return a.nvis > 0 ? (a.nvis + a.share - 1) / a.share : 1; }
 void launch_grid_zero(const GridArgs& a, hipStream_t s);

@@ -2,11 +2,12 @@
 // axis, with the flag factor F; the grid is the half plane q_v >= 0 (a point with q_v < 0 stands
 // for (-q_u, -q_v), the visibility conjugated; a point on the line q_v = 0, which the half plane
 // stores whole, also enters at (-q_u, 0) conjugated), and chan_avg consecutive channels are gridded
-// together.  A thread sums the channel group of each of its visibilities in registers and adds it to
-// the FP64 cell sums and the integer counts with atomics (through LDS for the crowded cells around
-// the origin); the cell sums are then written in the output precision.
+// together.  A thread sums the channel group of each of its visibilities in registers; the sums of the
+// crowded cells around the origin are formed in LDS, the far baselines' group sums staged by cell (or added
+// with atomics), and the cell sums written in the output precision.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "bs_kernels.h"
@@ -16,28 +17,108 @@ namespace {
 constexpr int GRID_THREADS = 1024;
 
 __global__ void k_grid_zero(GridArgs a) {
-  const long long cells = (long long)a.nco * a.n * (a.n / 2 + 1);
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < cells; i += (long long)gridDim.x * blockDim.x) {
-    a.acc[2 * i] = 0.0;
-    a.acc[2 * i + 1] = 0.0;
-    a.cnt[i] = 0;
+  const long long plane = (long long)a.n * (a.n / 2 + 1), cells = a.nco * plane;
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < cells + 2; i += (long long)gridDim.x * blockDim.x) {
+    if (i < cells) {
+      *(double2*)&a.acc[2 * i] = make_double2(0.0, 0.0);
+      a.cnt[i] = 0;
+    }
+    if (a.cap > 0 && i <= plane + 1) a.fcnt[i] = 0;   // two totals after the cells
   }
 }
 
-// A baseline's grid point, decided once a call: q = rint(U / du) per axis in FP64, reversed where q_v < 0.
-// Code: 0 = off the grid, else 1 | reversed << 1 | q_v << 2 | (q_u + 2048) << 13.
+// A baseline's place, decided once a call: its grid point is q = rint(U / du) per axis in FP64, reversed where
+// q_v < 0.  Code: kind | reversed << 2 | (q_v = 0) << 3 | payload << 4, kind
+//   0 off the grid;  1 LDS cell (payload its index);  2 staged (payload the slot);  3 global atomics (payload
+//   the cell)
+// A far baseline on the line q_v = 0, which enters two cells, is not staged.  Slots are handed out in baseline
+// order, a block's far baselines in one run; fcell and frank keep a slot's cell and its rank there for the
+// cells' lists.  STAGE takes four baselines a thread, so that a block's atomic on the total hands out 1024; a
+// short list without staging takes one a thread, its FP64 divisions the only thing that takes time.
+template <bool STAGE>
 __global__ __launch_bounds__(256) void k_grid_code(GridArgs a) {
+  constexpr int NB = STAGE ? 4 : 1;
+  __shared__ unsigned wsum[4], wbase;
   const double half = (double)(a.n / 2);
-  for (long long i = blockIdx.x * 256LL + threadIdx.x; i < a.nvis; i += gridDim.x * 256LL) {
-    double qu = rint(a.uv[2 * i] / a.du), qv = rint(a.uv[2 * i + 1] / a.du);
-    const bool neg = qv < 0.0;
-    if (neg) {
-      qu = -qu;
-      qv = -qv;
+  const int nh = a.n / 2 + 1, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (long long b0 = blockIdx.x * 256LL * NB; b0 < a.nvis; b0 += gridDim.x * 256LL * NB) {
+    const long long i0 = b0 + NB * threadIdx.x;
+    unsigned code[NB], cell[NB], far = 0u;
+    bool stage[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      code[q] = cell[q] = 0u;
+      stage[q] = false;
+      if (i0 + q >= a.nvis) continue;
+      double qu = rint(a.uv[2 * (i0 + q)] / a.du), qv = rint(a.uv[2 * (i0 + q) + 1] / a.du);
+      const bool neg = qv < 0.0;
+      if (neg) {
+        qu = -qu;
+        qv = -qv;
+      }
+      if (!(fabs(qu) < half && fabs(qv) < half)) continue;
+      const int iu = (int)qu, iv = (int)qv;
+      if (iu > -a.hot && iu < a.hot && iv < a.hot) {
+        code[q] = 1u | (unsigned)((iu + a.hot - 1) * a.hot + iv) << 4;
+      } else {
+        cell[q] = (unsigned)((iu < 0 ? iu + a.n : iu) * nh + iv);
+        code[q] = 3u | cell[q] << 4;
+        stage[q] = STAGE && iv > 0;
+        far += stage[q];
+      }
+      code[q] |= (neg ? 4u : 0u) | (iv == 0 ? 8u : 0u);
     }
-    const bool in = fabs(qu) < half && fabs(qv) < half;
-    a.code[i] = in ? 1u | (neg ? 2u : 0u) | (unsigned)(int)qv << 2 | (unsigned)((int)qu + 2048) << 13 : 0u;
+    if constexpr (STAGE) {
+      unsigned inc = far;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned x = __shfl_up(inc, o);
+        if (lane >= o) inc += x;
+      }
+      if (lane == 63) wsum[w] = inc;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const unsigned tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        wbase = tot ? atomicAdd(a.fcnt + a.n * nh, tot) : 0u;
+      }
+      __syncthreads();
+      unsigned slot = wbase + inc - far;
+      for (int k = 0; k < w; ++k) slot += wsum[k];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        if (!stage[q]) continue;
+        if (slot < (unsigned)a.cap) {   // past the staging space: atomics
+          a.fcell[slot] = cell[q];
+          a.frank[slot] = atomicAdd(a.fcnt + cell[q], 1u);
+          code[q] = 2u | (code[q] & 4u) | slot << 4;
+        }
+        ++slot;
+      }
+      __syncthreads();   // wsum and wbase are written again
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (i0 + q < a.nvis) a.code[i0 + q] = code[q];
   }
+}
+// the far cells' runs in the list of slots, in no particular order of cells (one atomic a wave)
+__global__ __launch_bounds__(256) void k_grid_off(GridArgs a) {
+  const int plane = a.n * (a.n / 2 + 1), i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+  const unsigned k = i < plane ? a.fcnt[i] : 0u;
+  unsigned inc = k;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned x = __shfl_up(inc, o);
+    if (lane >= o) inc += x;
+  }
+  unsigned base = 0u;
+  if (lane == 63 && inc) base = atomicAdd(a.fcnt + plane + 1, inc);
+  base = __shfl(base, 63);
+  if (i < plane) a.foff[i] = base + inc - k;
+}
+__global__ __launch_bounds__(256) void k_grid_list(GridArgs a) {
+  const unsigned tot = a.fcnt[a.n * (a.n / 2 + 1)], m = tot < (unsigned)a.cap ? tot : (unsigned)a.cap;
+  for (unsigned s = blockIdx.x * 256 + threadIdx.x; s < m; s += gridDim.x * 256) a.flist[a.foff[a.fcell[s]] + a.frank[s]] = s;
 }
 
 __device__ __forceinline__ void cell_add(const GridArgs& a, long long o, long long cell, double re, double im, int c) {
@@ -55,15 +136,18 @@ __device__ __forceinline__ int hot_cell(const GridArgs& a, int h) {
 }
 
 // Short baselines crowd into the cells around the origin (number density ~ 1 / U^2), so the cells |q_u| <
-// a.hot, q_v < a.hot are summed in LDS and the others take global atomics.  blockIdx.y: output channel o
-// (all its input channels: a visibility's group is summed in registers first); blockIdx.x: the
-// baselines i of share blockIdx.x of gridDim.x.  A thread takes four consecutive baselines (VEC: with
-// 16-byte loads), and every channel's visibilities and flags are loaded before any is used, four
-// channels at a time: the loads of flagged samples are wasted, but no load waits for a flag.
-// Bound: HBM (9 bytes a sample) and the far cells' atomics.  hot = 64 fills a CU's LDS (8128 cells) and holds
-// nine tenths of log-uniform baselines; with one share a channel its sums are stored for good.  262,144 baselines x
-// 768 channels, 4:1, flags: 1560 us with 32 x 63 LDS cells, a division per channel group and loads that
-// waited for flags, now 695.
+// a.hot, q_v < a.hot are summed in LDS.  A far baseline's group sum goes to its slot of a staging array, in
+// baseline order, so that neighbouring threads fill whole lines; k_grid_fin gathers a cell's slots.  (Slots
+// in cell order cost 200 us more in scattered 16-byte stores: 24 blocks' staging planes share an L2; float64
+// atomics on the far cells ran at 27 G a second, 65 us per percent of the samples.)
+// blockIdx.y: output channel o (all its input channels: a visibility's group is summed in registers
+// first); blockIdx.x: the baselines i of share blockIdx.x of gridDim.x.  A thread takes four consecutive
+// baselines (VEC: with 16-byte loads), and every channel's visibilities and flags are loaded before any is
+// used, four channels at a time: the loads of flagged samples are wasted, but no load waits for a flag.
+// Bound: HBM (9 bytes a sample).  hot = 64 fills a CU's LDS (8128 cells) and holds nine tenths of
+// log-uniform baselines; with one share a channel its sums are stored for good.  262,144 baselines x 768
+// channels, 4:1, flags: 1560 us with 32 x 63 LDS cells, a division per channel group, loads that waited for
+// flags and atomics for the far cells; 695 with the atomics alone left, now 463: 4.1 TB/s.
 template <bool VEC, bool PHASE>
 __global__ __launch_bounds__(GRID_THREADS) void k_grid_scatter(GridArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char grid_sh[];
@@ -145,23 +229,27 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_scatter(GridArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (!code[q] || !c[q]) continue;
-      const int iu = (int)(code[q] >> 13) - 2048, iv = (int)(code[q] >> 2 & 2047u);
-      const double vi = code[q] & 2u ? -im[q] : im[q];
-      if (iu > -hot && iu < hot && iv < hot) {
-        const int h = (iu + hot - 1) * hot + iv;
-        atomicAdd(&hre[h], re[q]);
-        atomicAdd(&him[h], vi);
-        atomicAdd(&hc[h], c[q]);
-        if (iv == 0) {   // the mirror baseline on the stored line q_v = 0: (-q_u, 0), conjugated
-          const int hm = (-iu + hot - 1) * hot;
+      const unsigned kind = code[q] & 3u, at = code[q] >> 4;
+      const double vi = code[q] & 4u ? -im[q] : im[q];
+      if (kind == 2u) {   // every slot is written, a wholly flagged baseline's with zeros
+        const long long p = o * a.cap + at;
+        *(double2*)&a.stage_v[2 * p] = make_double2(re[q], vi);
+        a.stage_c[p] = c[q];
+      } else if (!kind || !c[q]) {
+        continue;
+      } else if (kind == 1u) {
+        atomicAdd(&hre[at], re[q]);
+        atomicAdd(&him[at], vi);
+        atomicAdd(&hc[at], c[q]);
+        if (code[q] & 8u) {   // q_v = 0: the mirror baseline on the stored line, (-q_u, 0), conjugated
+          const int hm = 2 * (hot - 1) * hot - (int)at;
           atomicAdd(&hre[hm], re[q]);
           atomicAdd(&him[hm], -vi);
           atomicAdd(&hc[hm], c[q]);
         }
       } else {
-        cell_add(a, o, (long long)(iu < 0 ? iu + a.n : iu) * nh + iv, re[q], vi, c[q]);
-        if (iv == 0) cell_add(a, o, (long long)(iu > 0 ? a.n - iu : -iu) * nh, re[q], -vi, c[q]);
+        cell_add(a, o, at, re[q], vi, c[q]);
+        if (code[q] & 8u) cell_add(a, o, at ? a.n * nh - (int)at : 0, re[q], -vi, c[q]);
       }
     }
   }
@@ -203,14 +291,42 @@ __global__ __launch_bounds__(256) void k_grid_hot(GridArgs a, int shares) {
   a.cnt[at] = c;
 }
 
+// The cell sums in the output precision.
 template <typename T>
-__global__ void k_grid_fin(GridArgs a, T* __restrict__ out, int32_t* __restrict__ ng) {
+__global__ void k_grid_out(GridArgs a, T* __restrict__ out, int32_t* __restrict__ ng) {
   const long long cells = (long long)a.nco * a.n * (a.n / 2 + 1);
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < cells; i += (long long)gridDim.x * blockDim.x) {
-    out[2 * i] = (T)__hip_atomic_load(a.acc + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    out[2 * i + 1] = (T)__hip_atomic_load(a.acc + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ng[i] = __hip_atomic_load(a.cnt + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double2 v = *(const double2*)&a.acc[2 * i];
+    out[2 * i] = (T)v.x;
+    out[2 * i + 1] = (T)v.y;
+    ng[i] = a.cnt[i];
   }
+}
+// The same with the far cells' staged group sums gathered first.  Blocks are dealt to the eight XCDs in turn;
+// block b works on a channel o with o mod 8 = b mod 8, so that the gathers of a channel meet its staging
+// plane in one L2.  192 channels of 256^2, 262,144 baselines: 105 us.
+template <typename T>
+__global__ __launch_bounds__(256) void k_grid_fin(GridArgs a, T* __restrict__ out, int32_t* __restrict__ ng, int nx) {
+  const int plane = a.n * (a.n / 2 + 1);
+  const int x = blockIdx.x & 7, y = blockIdx.x >> 3;
+  const long long o = (long long)(y / nx) * 8 + x;
+  const int i = (y % nx) * 256 + threadIdx.x;
+  if (o >= a.nco || i >= plane) return;
+  const long long at = o * plane + i;
+  double2 v = *(const double2*)&a.acc[2 * at];
+  int c = a.cnt[at];
+  const unsigned k = a.fcnt[i];
+  const unsigned* run = a.flist + a.foff[i];
+  for (unsigned s = 0; s < k; ++s) {
+    const long long p = o * a.cap + run[s];
+    const double2 t = *(const double2*)&a.stage_v[2 * p];
+    v.x += t.x;
+    v.y += t.y;
+    c += a.stage_c[p];
+  }
+  out[2 * at] = (T)v.x;
+  out[2 * at + 1] = (T)v.y;
+  ng[at] = c;
 }
 
 }  // namespace
@@ -220,8 +336,14 @@ void launch_grid_zero(const GridArgs& a, hipStream_t s) {
 }
 
 void launch_grid_scatter(const GridArgs& a, hipStream_t s) {
-  const long long cb = (a.nvis + 255) / 256;
-  hipLaunchKernelGGL(k_grid_code, dim3((unsigned)(cb < 2048 ? cb : 2048)), dim3(256), 0, s, a);
+  if (a.cap > 0) {
+    const long long cb = (a.nvis + 1023) / 1024, lb = (a.cap + 255) / 256;
+    hipLaunchKernelGGL(k_grid_code<true>, dim3((unsigned)std::min(cb, 2048LL)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_grid_off, dim3((a.n * (a.n / 2 + 1) + 255) / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_grid_list, dim3((unsigned)std::min(lb, 1024LL)), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_grid_code<false>, dim3((unsigned)std::min((a.nvis + 255) / 256, 2048LL)), dim3(256), 0, s, a);
+  }
   const unsigned shares = (unsigned)grid_shares(a);
   const size_t lds = (size_t)grid_nhot(a.hot) * 20;
   const bool vec = a.nvis % 4 == 0 && (uintptr_t)a.vis % 16 == 0 && (uintptr_t)a.flags % 4 == 0;
@@ -237,6 +359,8 @@ void launch_grid_scatter(const GridArgs& a, hipStream_t s) {
     if (a.flags) b.flags += (long long)o0 * a.chan_avg * a.nvis;
     b.hot_v += 2 * (long long)o0 * shares * grid_nhot(a.hot);
     b.hot_c += (long long)o0 * shares * grid_nhot(a.hot);
+    b.stage_v += 2 * (long long)o0 * a.cap;
+    b.stage_c += (long long)o0 * a.cap;
     hipLaunchKernelGGL(k, dim3(shares, no), dim3(GRID_THREADS), lds, s, b);
     if (shares > 1)
       hipLaunchKernelGGL(k_grid_hot, dim3((grid_nhot(a.hot) + 255) / 256, no), dim3(256), 0, s, b, (int)shares);
@@ -244,6 +368,24 @@ void launch_grid_scatter(const GridArgs& a, hipStream_t s) {
 }
 
 void launch_grid_fin(const GridArgs& a, bool fp64, void* out, int32_t* ng, hipStream_t s) {
-  if (fp64) hipLaunchKernelGGL(k_grid_fin<double>, dim3(1024), dim3(256), 0, s, a, static_cast<double*>(out), ng);
-  else hipLaunchKernelGGL(k_grid_fin<float>, dim3(1024), dim3(256), 0, s, a, static_cast<float*>(out), ng);
+  if (a.cap == 0) {
+    if (fp64) hipLaunchKernelGGL(k_grid_out<double>, dim3(1024), dim3(256), 0, s, a, static_cast<double*>(out), ng);
+    else hipLaunchKernelGGL(k_grid_out<float>, dim3(1024), dim3(256), 0, s, a, static_cast<float*>(out), ng);
+    return;
+  }
+  const int nx = (a.n * (a.n / 2 + 1) + 255) / 256, o8 = (a.nco + 7) / 8;
+  // channels in slices whose blocks fit a grid
+  const int per = std::max(1, std::min(o8, (1 << 20) / nx)) * 8;
+  const size_t plane = (size_t)a.n * (a.n / 2 + 1);
+  for (int o0 = 0; o0 < a.nco; o0 += per) {
+    GridArgs b = a;
+    b.nco = std::min(per, a.nco - o0);
+    b.acc += 2 * o0 * plane;
+    b.cnt += o0 * plane;
+    b.stage_v += 2 * (long long)o0 * a.cap;
+    b.stage_c += (long long)o0 * a.cap;
+    const dim3 g((unsigned)(8LL * nx * ((b.nco + 7) / 8)));
+    if (fp64) hipLaunchKernelGGL(k_grid_fin<double>, g, dim3(256), 0, s, b, static_cast<double*>(out) + 2 * o0 * plane, ng + o0 * plane, nx);
+    else hipLaunchKernelGGL(k_grid_fin<float>, g, dim3(256), 0, s, b, static_cast<float*>(out) + 2 * o0 * plane, ng + o0 * plane, nx);
+  }
 }
