@@ -23,11 +23,11 @@ __device__ __forceinline__ int shape_bin(double x) {
 }
 
 // Number of edges k1e[0..nk] at or below k1, minus one: the k1 bin, or -1 / nk outside (edges
-// strictly increasing, nk <= 64, so a seven-step binary search finds the same count as a linear scan).
+// strictly increasing, so a binary search from the largest power of two <= nk + 1 finds the same count as a
+// linear scan; its steps wait for one another, hence not from 64 for every nk).
 __device__ __forceinline__ int k1_bin(const double* __restrict__ k1e, int nk, double k1) {
   int c = 0;
-#pragma unroll
-  for (int step = 64; step > 0; step >>= 1)
+  for (int step = 1 << (31 - __clz(nk + 1)); step > 0; step >>= 1)
     if (c + step <= nk + 1 && k1e[c + step - 1] <= k1) c += step;
   return c - 1;
 }
@@ -109,13 +109,13 @@ __global__ __launch_bounds__(MONO_THREADS) void k_mono_bin(MonoArgs a) {
   const double lo2 = elo * elo, hi2 = ehi * ehi;
   const int nc = a.nc, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int row = blockIdx.x * WPB + wave; row < a.nt * nc; row += gridDim.x * WPB) {
-    const int t = row / nc, ai = row - t * nc;
+    const int ai = row / a.nt, t = row - ai * a.nt;
     const double kq0 = a.kperp[3 * t], kq1 = a.kperp[3 * t + 1], kq2 = a.kperp[3 * t + 2];
     const double kp1 = a.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc);
     if (row_above_edges(hi2, kq0, kp1)) continue;   // wave-uniform
     int jlo, jhi;
     row_span(hi2, kq1, kq2, kp1, a.kpar_unit, nc, jlo, jhi);
-    const double* __restrict__ rowp = a.B + 2 * (long long)row * nc;
+    const double* __restrict__ rowp = a.B + 2 * ((long long)t * nc + ai) * nc;
     for (int j0 = jlo; j0 <= jhi; j0 += MONO_NB * 64) {   // the same trip count for every lane
       // the bins first (they need no memory), then the values of the binned cells only (MONO_NB loads
       // in flight)
@@ -265,13 +265,13 @@ __device__ int cell_bin_orient(const double* __restrict__ k1e, int nk, double lo
   return j * 25 + shape_bin(mu) * 5 + shape_bin(t);
 }
 
-// w[i] for i in lm order: lm_norm[i] Q_l^m(x) Re((px + i py)^m), with m > 0 zero without azimuth and
-// every l > lmax zero.  The loops run to the largest lmax with constant bounds, so that the
-// recurrence's coefficients, 1 / (l - m) among them, are constants.
-__device__ __forceinline__ void multi_weights(const double* __restrict__ norm, int lmax, double x, double px,
-                                              double py, bool azimuth, double* w) {
-  double cr = 1.0, ci = 0.0;   // Re, Im of (px + i py)^m
+// acc[i] += v Q_l^m(x) Re((px + i py)^m) for i in lm order up to the largest lmax (the caller drops l > lmax and
+// multiplies the sums by lm_norm), with m > 0 zero without azimuth.  The loops' bounds are constant, so that
+// the recurrence's coefficients, 1 / (l - m) among them, are constants.
+__device__ __forceinline__ void multi_add(double v, double x, double px, double py, bool azimuth, double* acc) {
+  double cr = 1.0, ci = 0.0;   // Re, Im of (px + i py)^m (without v: an infinite value gives the signs of its weights)
   double qmm = 1.0;            // Q_m^m = (-1)^m (2m - 1)!!
+  if (!azimuth) px = py = 0.0;
 #pragma unroll
   for (int m = 0; m <= MULTI_MAX_LMAX; ++m) {
     if (m > 0) {
@@ -280,7 +280,6 @@ __device__ __forceinline__ void multi_weights(const double* __restrict__ norm, i
       cr = r;
       qmm *= -(2.0 * m - 1.0);
     }
-    const double c = (m == 0 || azimuth) ? cr : 0.0;
     double q2 = 0.0, q1 = qmm;   // Q_{l-2}^m, Q_{l-1}^m
 #pragma unroll
     for (int l = m; l <= MULTI_MAX_LMAX; ++l) {
@@ -289,8 +288,7 @@ __device__ __forceinline__ void multi_weights(const double* __restrict__ norm, i
       else if (l == m + 1) q = x * (2.0 * m + 1.0) * qmm;
       else q = ((2.0 * l - 1.0) * x * q1 - (l + m - 1.0) * q2) * (1.0 / (double)(l - m));
       if (l > m) { q2 = q1; q1 = q; }
-      const int i = l * (l + 1) / 2 + m;
-      w[i] = l <= lmax ? norm[i] * q * c : 0.0;
+      acc[l * (l + 1) / 2 + m] += q * cr * v;
     }
   }
 }
@@ -301,24 +299,52 @@ constexpr int MULTI_THREADS = 512;   // eight waves share the block's bins
 constexpr int MQ_R = 2, MQ_NB = 2, MQ_BATCH = 64 * MQ_R, MQ_CAP = 256;
 static_assert(MQ_CAP >= MQ_BATCH + 64 * MQ_NB, "a scan step must fit behind an unprocessed batch");
 
-struct MultiRun {   // a lane's running sums over consecutive cells of one bin
+struct MultiRun {   // a lane's sums over consecutive cells of one bin
   int cur = -1, cnt = 0;
   double acc[MULTI_MAX_NLM];
 };
 
-__device__ __forceinline__ void multi_flush(MultiRun& r, double* ssum, int* scnt, int nb, int nlm) {
+__device__ __forceinline__ void multi_flush(const MultiRun& r, double* ssum, int* scnt, int nb, int nlm) {
 #pragma unroll
   for (int i = 0; i < MULTI_MAX_NLM; ++i)   // constant indices keep acc in registers
     if (i < nlm) atomicAdd(&ssum[i * nb + r.cur], r.acc[i]);
   atomicAdd(&scnt[r.cur], r.cnt);
 }
 
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(dpp<CTRL>(__double2hiint(v)), dpp<CTRL>(__double2loint(v)));
+}
+// Lane i (a multiple of 2 S, S <= 8) takes over lane i + S's sums where both are of one bin (row_shl / row_shr).
+template <int S>
+__device__ __forceinline__ void multi_merge(MultiRun& r, int nlm, int lane) {
+  const int up = dpp<0x100 + S>(r.cur), down = dpp<0x110 + S>(r.cur), at = lane & (2 * S - 1);
+  const bool take = at == 0 && up == r.cur, gone = at == S && down == r.cur;
+#pragma unroll
+  for (int i = 0; i < MULTI_MAX_NLM; ++i)
+    if (i < nlm) {
+      const double p = dpp<0x100 + S>(r.acc[i]);
+      r.acc[i] += take ? p : 0.0;
+    }
+  const int n = dpp<0x100 + S>(r.cnt);
+  r.cnt += take ? n : 0;
+  if (gone) r.cur = -1;
+}
+
 // Lane j takes entries start + j MQ_R + r, r < MQ_R, of the n queued: the exact bin decision, the
-// orientation and the weights, all lanes busy; sums stay in registers while the bin does not change.
+// orientation and the weights, all lanes busy.  Neighbouring cells share bins: a lane's sums stay in
+// registers while the bin does not change, then those of four lanes are merged in pairs, and only
+// what is left is added to the block's bins (the LDS serialises the lanes that add to one address).  133 x 768^2,
+// l <= 4, 12 k1 bins: 190 us a call without merging, 167 / 162 / 166 / 174 merging 2 / 4 / 8 / 16 lanes.
 __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1e, double lo2, double hi2,
                                             const int* qt, const unsigned* qab, const double* qv, int start,
-                                            int n, MultiRun& run, double* ssum, int* scnt, int nb, int lane) {
+                                            int n, double* ssum, int* scnt, int nb, int lane) {
   const int nc = a.m.nc;
+  MultiRun run;
+#pragma unroll
+  for (int i = 0; i < MULTI_MAX_NLM; ++i) run.acc[i] = 0.0;
 #pragma unroll 1
   for (int r = 0; r < MQ_R; ++r) {
     const int idx = lane * MQ_R + r;
@@ -341,18 +367,31 @@ __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1
 #pragma unroll
       for (int i = 0; i < MULTI_MAX_NLM; ++i) run.acc[i] = 0.0;
     }
-    double w[MULTI_MAX_NLM];
-    multi_weights(a.lm_norm, a.lmax, pz, px, py, az, w);
-#pragma unroll
-    for (int i = 0; i < MULTI_MAX_NLM; ++i) run.acc[i] += w[i] * v;
+    multi_add(v, pz, px, py, az, run.acc);
     ++run.cnt;
   }
+  if (n > MQ_BATCH / 2) {   // a short last batch (small calls) is not worth the merges
+    multi_merge<1>(run, a.nlm, lane);
+    multi_merge<2>(run, a.nlm, lane);
+  }
+  if (run.cur >= 0) multi_flush(run, ssum, scnt, nb, a.nlm);
 }
 
-// Rows (t, a) one per wave.  A scan over the row's span of j, lanes over j, applies the cheap first test
+__device__ __forceinline__ int lane_get(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ double lane_get(double v, int l) {
+  return __hiloint2double(lane_get(__double2hiint(v), l), lane_get(__double2loint(v), l));
+}
+
+// Rows (t, a) one per wave, triangles fastest: only rows near a = 0 (mod nc) have cells, and in this order the
+// rows of a wave lie nt-th parts of the grid's stride apart in a (with a fastest, 4096 waves and nc = 768 gave
+// all of them to few waves).  The spans of 64 of a wave's rows are found at a time, a row a lane (a row at a time, the wave waited for its triangle's loads, two square roots and two divisions before the first
+// value).  A scan over the row's span of j, lanes over j, applies the cheap first test
 // and reads the values of the surviving cells only (about one cell in twenty at the usual k1 edges);
 // those are queued, and whenever a batch is full it is binned, oriented and weighted with every lane
 // busy (a lane per cell would leave most lanes idle through the costly part).
+// Bound: instruction issue (some 400 a queued cell, most of them FP64: five divisions, four square roots, the
+// weights).  133 x 768^2, l <= 4, 12 k1 bins, 4.4 M cells: 250 us with the rows a fastest (few waves had the cells),
+// a row at a time and every lane's sums added to the bins; now 116
 __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   extern __shared__ double ssum[];            // [nlm][nb] sums, then nb counts
   __shared__ double k1e[MONO_MAX_K1 + 1];
@@ -368,59 +407,70 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   __syncthreads();
   const double elo = k1e[0] * (1.0 - 0x1p-20), ehi = k1e[a.m.nk] * (1.0 + 0x1p-20);
   const double lo2 = elo * elo, hi2 = ehi * ehi;
-  const int nc = a.m.nc, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nc = a.m.nc, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = gridDim.x * WPB;
   int* qt = sqt[wave];
   unsigned* qab = sqab[wave];
   double* qv = sqv[wave];
   int head = 0, tail = 0;   // wave-uniform queue positions (mod MQ_CAP on use)
-  MultiRun run;
-  for (int row = blockIdx.x * WPB + wave; row < a.m.nt * nc; row += gridDim.x * WPB) {
-    const int t = row / nc, ai = row - t * nc;
-    const double kq0 = a.m.kperp[3 * t], kq1 = a.m.kperp[3 * t + 1], kq2 = a.m.kperp[3 * t + 2];
-    const double kp1 = a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc);
-    if (row_above_edges(hi2, kq0, kp1)) continue;   // wave-uniform
-    int jlo, jhi;
-    row_span(hi2, kq1, kq2, kp1, a.m.kpar_unit, nc, jlo, jhi);
-    const double* __restrict__ rowp = a.m.B + 2 * (long long)row * nc;
-    for (int j0 = jlo; j0 <= jhi; j0 += 64 * MQ_NB) {
-      bool in[MQ_NB];
-      double v[MQ_NB];
+  for (long long r0 = blockIdx.x * WPB + wave; r0 < (long long)a.m.nt * nc; r0 += 64LL * nwave) {
+    // this lane's row: empty (jlo > jhi) beyond the last row and above the edges
+    const long long row = r0 + (long long)lane * nwave;
+    int t = 0, ai = 0, jlo = 0, jhi = -1;
+    double kq0 = 0.0, kq1 = 0.0, kq2 = 0.0, kp1 = 0.0;
+    if (row < (long long)a.m.nt * nc) {
+      ai = (int)row / a.m.nt;
+      t = (int)row - ai * a.m.nt;
+      kq0 = a.m.kperp[3 * t];
+      kq1 = a.m.kperp[3 * t + 1];
+      kq2 = a.m.kperp[3 * t + 2];
+      kp1 = a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc);
+      if (!row_above_edges(hi2, kq0, kp1)) row_span(hi2, kq1, kq2, kp1, a.m.kpar_unit, nc, jlo, jhi);
+    }
+    for (unsigned long long left = __ballot(jlo <= jhi); left; left &= left - 1) {
+      const int l = __ffsll(left) - 1;
+      const int rt = lane_get(t, l), ra = lane_get(ai, l), rlo = lane_get(jlo, l), rhi = lane_get(jhi, l);
+      const double q0 = lane_get(kq0, l), q1 = lane_get(kq1, l), q2 = lane_get(kq2, l), p1 = lane_get(kp1, l);
+      const double* __restrict__ rowp = a.m.B + 2 * ((long long)rt * nc + ra) * nc;
+      for (int j0 = rlo; j0 <= rhi; j0 += 64 * MQ_NB) {
+        bool in[MQ_NB];
+        double v[MQ_NB];
 #pragma unroll
-      for (int u = 0; u < MQ_NB; ++u) {
-        const int j = j0 + u * 64 + lane;
-        in[u] = j <= jhi && cell_may_bin(lo2, hi2, kq0, kq1, kq2, kp1, a.m.kpar_unit * (double)j);
-      }
-#pragma unroll
-      for (int u = 0; u < MQ_NB; ++u) {
-        const int j = j0 + u * 64 + lane;
-        v[u] = in[u] ? rowp[2 * (j < 0 ? j + nc : j)] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < MQ_NB; ++u) {
-        const unsigned long long m = __ballot(in[u]);
-        if (in[u]) {
+        for (int u = 0; u < MQ_NB; ++u) {
           const int j = j0 + u * 64 + lane;
-          const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-          const int e = (tail + below) & (MQ_CAP - 1);
-          qt[e] = t;
-          qab[e] = ((unsigned)ai << 16) | (unsigned)(j < 0 ? j + nc : j);
-          qv[e] = v[u];
+          in[u] = j <= rhi && cell_may_bin(lo2, hi2, q0, q1, q2, p1, a.m.kpar_unit * (double)j);
         }
-        tail += (int)__popcll(m);
-      }
-      if (tail - head >= MQ_BATCH) {
-        __builtin_amdgcn_wave_barrier();   // a wave's LDS accesses stay in program order
-        multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, run, ssum, scnt, nb, lane);
-        __builtin_amdgcn_wave_barrier();
-        head += MQ_BATCH;
+#pragma unroll
+        for (int u = 0; u < MQ_NB; ++u) {
+          const int j = j0 + u * 64 + lane;
+          v[u] = in[u] ? rowp[2 * (j < 0 ? j + nc : j)] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < MQ_NB; ++u) {
+          const unsigned long long m = __ballot(in[u]);
+          if (in[u]) {
+            const int j = j0 + u * 64 + lane;
+            const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            const int e = (tail + below) & (MQ_CAP - 1);
+            qt[e] = rt;
+            qab[e] = ((unsigned)ra << 16) | (unsigned)(j < 0 ? j + nc : j);
+            qv[e] = v[u];
+          }
+          tail += (int)__popcll(m);
+        }
+        if (tail - head >= MQ_BATCH) {
+          __builtin_amdgcn_wave_barrier();   // a wave's LDS accesses stay in program order
+          multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, ssum, scnt, nb, lane);
+          __builtin_amdgcn_wave_barrier();
+          head += MQ_BATCH;
+        }
       }
     }
   }
   __builtin_amdgcn_wave_barrier();
-  if (tail > head) multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, run, ssum, scnt, nb, lane);
-  if (run.cur >= 0) multi_flush(run, ssum, scnt, nb, nlm);
+  if (tail > head) multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
   __syncthreads();
-  for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS) a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i];
+  for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS)
+    a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i] * a.lm_norm[i / nb];
   for (int i = threadIdx.x; i < nb; i += MULTI_THREADS) a.m.pcnt[(long long)blockIdx.x * nb + i] = scnt[i];
 }
 
