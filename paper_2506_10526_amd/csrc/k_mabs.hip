@@ -1027,6 +1027,194 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // ---------------------------------------------------------------------------
+// The same contraction for few channels, where 192 columns are mostly padding: tiles of 32 NJ columns,
+// and the rows in units of 8 nu1 x 16 nu2, one a wave.  A wave keeps its A operand to itself: its 8 + 16 raw FP32
+// rows are copied into LDS (double-buffered, with the block's B columns) and the products F1 F2 are
+// formed and split in registers in the fragment's layout, which saves writing A to LDS and reading it back.
+// Every entry takes the operations of split3_tile in its order (per 16 pixels A lo B hi, A hi B hi, A hi B lo;
+// FP64 every T3_FLUSH pixels), so the results are the same bits.  Two blocks a CU, one forming while the
+// other multiplies.  Bound: VALU of the formation (about as long as the MFMAs at NJ = 2).  48 channels of
+// 96^2, 6 rings, every nu1: 766 us in 256 x 192 tiles, now 386.
+// ---------------------------------------------------------------------------
+constexpr int TN_I = 8, TN_J = 16;              // unit: nu1 x nu2
+constexpr int TN_F2 = 128 * 4;                  // floats before the F_b2 rows: two copy instructions of F_b1
+constexpr int TN_RAW = 5 * 64 * 4;              // floats of a wave's raw buffer: 5 copy instructions
+
+__device__ __host__ __forceinline__ long long splitn_units(const MabsGemmArgs& a) {
+  return (long long)((a.n_nu1 + TN_I - 1) / TN_I) * ((a.nc + TN_J - 1) / TN_J);
+}
+__device__ __host__ __forceinline__ long long splitn_blocks(const MabsGemmArgs& a, int nj) {
+  return (splitn_units(a) + 3) / 4 * ((a.nc + 32 * nj - 1) / (32 * nj)) * a.kchunks * a.ntri;
+}
+
+template <int NJ>
+__device__ __forceinline__ void splitn_tile(const MabsGemmArgs& a, uint16_t* bbuf0, uint16_t* bbuf1, float* rawb0,
+                                            float* rawb1) {
+  constexpr int BL = 32 * NJ * T3_K;            // B stage buffer: hi columns, then lo
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int units = (int)splitn_units(a), ublocks = (units + 3) / 4, nj2 = (a.nc + TN_J - 1) / TN_J;
+  const int ctiles = (a.nc + 32 * NJ - 1) / (32 * NJ);
+  int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int unit = (b % ublocks) * 4 + wave;
+  b /= ublocks;
+  const int col0 = (b % ctiles) * 32 * NJ;
+  b /= ctiles;
+  const int kc = b % a.kchunks, t = b / a.kchunks;
+  const bool live = unit < units;               // a wave past the last unit copies and stores nothing of its own
+  const int un = live ? unit : units - 1;
+  const int i0 = un / nj2 * TN_I, n20 = un % nj2 * TN_J;
+  const int b1 = a.tri[3 * t], b2 = a.tri[3 * t + 1], b3 = a.tri[3 * t + 2];
+  const int kbeg = __builtin_amdgcn_readfirstlane(kc * a.kchunk);
+  const int kend = __builtin_amdgcn_readfirstlane(min(a.P, kbeg + a.kchunk));
+  const int nst = (kend - kbeg) / T3_K, klast = kend - T3_K;
+
+  const int plane4 = __builtin_amdgcn_readfirstlane((int)(unsigned)(a.bin_stride * 4));
+  const int plane2 = __builtin_amdgcn_readfirstlane((int)(unsigned)(a.bin_stride * 2));
+  auto rsrc = [](const void* p, int bytes) {
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)hi << 32) | lo), (short)0, bytes, BUF_DWORD3);
+  };
+  const __amdgpu_buffer_rsrc_t rF1 = rsrc(a.F + (size_t)b1 * a.bin_stride, plane4);
+  const __amdgpu_buffer_rsrc_t rF2 = rsrc(a.F + (size_t)b2 * a.bin_stride, plane4);
+  const __amdgpu_buffer_rsrc_t rH = rsrc(a.Fh + (size_t)b3 * a.bin_stride, plane2);
+  const __amdgpu_buffer_rsrc_t rL = rsrc(a.Fl + (size_t)b3 * a.bin_stride, plane2);
+  // raw copies as in split3_tile: nine 16-byte chunks a row, the ninth a pad; rows past the valid ones clamped
+  unsigned roff[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const int h = (k < 2 ? k : k - 2) * 64 + lane;
+    const int q = min(h / 9, (k < 2 ? TN_I : TN_J) - 1), c = h % 9 == 8 ? 0 : h % 9;
+    const int row = k < 2 ? a.nu1[min(i0 + q, a.n_nu1 - 1)] : min(n20 + q, a.nc - 1);
+    roff[k] = (unsigned)(((size_t)row * a.P + 4 * c) * 4);
+  }
+  // B copies: instruction wave + 4 q of 4 NJ, 16 columns each (2 NJ of hi, then 2 NJ of lo)
+  unsigned boff[NJ];
+#pragma unroll
+  for (int q = 0; q < NJ; ++q) {
+    const int I = wave + 4 * q, br = (I % (2 * NJ)) * 16 + (lane >> 2);
+    const int col = min(col0 + br, a.nc - 1);
+    boff[q] = (unsigned)(((size_t)col * a.P + 8 * swz_rows(br, lane & 3)) * 2);
+  }
+  auto copies = [&](int k0, uint16_t* bb, float* rb) {
+#pragma unroll
+    for (int q = 0; q < NJ; ++q) {
+      const int I = wave + 4 * q;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(I < 2 * NJ ? rH : rL, (lds_void*)(bb + I * 16 * T3_K), 16, boff[q], 2 * k0, 0, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(k < 2 ? rF1 : rF2, (lds_void*)(rb + wave * TN_RAW + k * 256), 16, roff[k], 4 * k0, 0, 0);
+  };
+  // row r of the wave's tile i: nu1 i0 + 2 i + (r >> 4), nu2 n20 + (r & 15)
+  const int o1 = wave * TN_RAW + (lane >> 4 & 1) * T3_RAWLD + 8 * (lane >> 5);
+  const int o2 = wave * TN_RAW + TN_F2 + (lane & 15) * T3_RAWLD + 8 * (lane >> 5);
+  int ob[2][NJ];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int c = j * 32 + (lane & 31);
+      ob[kk][j] = c * T3_K + swz_rows(c, kk * 2 + (lane >> 5)) * 8;
+    }
+
+  f32x16 acc[4][NJ];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  auto multiply = [&](const uint16_t* bb, const float* rb) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const float4 y0 = *(const float4*)&rb[o2 + 16 * kk], y1 = *(const float4*)&rb[o2 + 16 * kk + 4];
+      bf16x8 bh[NJ], bl[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        bh[j] = *(const bf16x8*)&bb[ob[kk][j]];
+        bl[j] = *(const bf16x8*)&bb[BL + ob[kk][j]];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float* f1 = &rb[o1 + 2 * i * T3_RAWLD + 16 * kk];
+        const float4 x0 = *(const float4*)f1, x1 = *(const float4*)(f1 + 4);
+        uint32_t h[4], l[4];
+        bf16_split2(x0.x * y0.x, x0.y * y0.y, h[0], l[0]);
+        bf16_split2(x0.z * y0.z, x0.w * y0.w, h[1], l[1]);
+        bf16_split2(x1.x * y1.x, x1.y * y1.y, h[2], l[2]);
+        bf16_split2(x1.z * y1.z, x1.w * y1.w, h[3], l[3]);
+        const v4u hw = {h[0], h[1], h[2], h[3]}, lw = {l[0], l[1], l[2], l[3]};
+        const bf16x8 ah = __builtin_bit_cast(bf16x8, hw), al = __builtin_bit_cast(bf16x8, lw);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+
+  double* S = a.S + ((size_t)kc * a.ntri + t) * (size_t)a.n_nu1 * a.nc * a.nc;
+  bool first_flush = true;
+  auto flush = [&]() {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));   // keeps the entries' addresses out of the stages
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int col = col0 + j * 32 + (ln & 31);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int r = (e >> 2) * 8 + (ln >> 5) * 4 + (e & 3);
+          const int ii = i0 + 2 * i + (r >> 4), nu2 = n20 + (r & 15);
+          if (live && ii < a.n_nu1 && nu2 < a.nc && col < a.nc) {
+            double* d = &S[((size_t)ii * a.nc + nu2) * a.nc + col];
+            const double v = (double)acc[i][j][e];
+            *d = first_flush ? v : *d + v;
+          }
+          acc[i][j][e] = 0.f;
+        }
+      }
+    first_flush = false;
+  };
+
+  copies(kbeg, bbuf0, rawb0);
+  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_s_barrier();
+  // Stage s multiplies from buffer s & 1 while the copies of stage s + 1 fill the other one (whose readers have
+  // passed the barrier that ended stage s - 1); past the last stage they re-read it.
+  auto stage = [&](int s, auto par) {
+    constexpr int PAR = decltype(par)::value;
+    copies(__builtin_amdgcn_readfirstlane(min(kbeg + (s + 1) * T3_K, klast)), PAR ? bbuf0 : bbuf1, PAR ? rawb0 : rawb1);
+    multiply(PAR ? bbuf1 : bbuf0, PAR ? rawb1 : rawb0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_s_barrier();
+  };
+  for (int s = 0; s < nst;) {
+    const int se = min(nst, s + T3_FLUSH / T3_K);   // s is even here
+    while (true) {
+      stage(s, std::integral_constant<int, 0>{});
+      if (++s >= se) break;
+      stage(s, std::integral_constant<int, 1>{});
+      if (++s >= se) break;
+    }
+    flush();
+  }
+}
+
+template <int NJ>
+__global__ __launch_bounds__(256, 2) void k_mabs_gemm_splitn(MabsGemmArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t bbuf0[64 * NJ * T3_K], bbuf1[64 * NJ * T3_K];
+  __shared__ __attribute__((aligned(16))) float raw0[4 * TN_RAW], raw1[4 * TN_RAW];
+  splitn_tile<NJ>(a, bbuf0, bbuf1, raw0, raw1);
+}
+
+// ---------------------------------------------------------------------------
 // FP32 contraction on FP32 MFMA (v_mfma_f32_32x32x2_f32), 128 x 128 tiles laid out like the split
 // kernel above: rows are an m1 x (128 / m1) block of (nu1, nu2), the A tile is formed in LDS from
 // the m1 + m2 raw FP32 rows (one FP32 product per element), B is the F_b3 rows copied straight into
@@ -1746,8 +1934,25 @@ void launch_mabs_gemm_split(const MabsGemmArgs& a, hipStream_t s) {
     MabsGemmArgs b = a;
     if (const char* e = getenv("BS_MABS_M1")) b.tile_m1 = atoi(e);   // tuning switch: 4, 8, 16 or 32
     const int m1 = b.tile_m1 ? b.tile_m1 : (b.n_nu1 >= 16 ? 16 : (b.n_nu1 >= 8 ? 8 : 4)), m2 = T3_M / m1;
-    const long long nb = (long long)((a.n_nu1 + m1 - 1) / m1) * ((a.nc + m2 - 1) / m2) * ((a.nc + T3_N - 1) / T3_N) *
-                         a.ntri * a.kchunks;
+    const long long rt = (long long)((a.n_nu1 + m1 - 1) / m1) * ((a.nc + m2 - 1) / m2);
+    const long long nb = rt * ((a.nc + T3_N - 1) / T3_N) * a.ntri * a.kchunks;
+    // Narrow tiles where they compute less: in units of 128 rows x 32 columns a narrow tile costs 0.6 + nj (its
+    // formation and its MFMAs), a 256 x 192 one 2 x 7.2.  64^2 or 96^2, 6 rings, every nu1, us a call with 192
+    // columns / the best narrow: nc 16 83 / 69, 32 223 / 94, 48 835 / 468, 64 695 / 386; 16 nu1: 96 374 / 240,
+    // 128 523 / 429, 160 and 192 equal, 256 1418 / 1184.
+    if (!b.tile_m1) {
+      int nj = 0;
+      double best = 0.95 * 14.4 * (double)rt * ((a.nc + T3_N - 1) / T3_N);
+      for (int k = 1; k <= 3; ++k) {
+        const double cost = (0.6 + k) * (double)splitn_units(a) * ((a.nc + 32 * k - 1) / (32 * k));
+        if (cost < best) { best = cost; nj = k; }
+      }
+      const dim3 g((unsigned)(nj ? splitn_blocks(a, nj) : 1));
+      if (nj == 1) hipLaunchKernelGGL(k_mabs_gemm_splitn<1>, g, dim3(256), 0, s, a);
+      if (nj == 2) hipLaunchKernelGGL(k_mabs_gemm_splitn<2>, g, dim3(256), 0, s, a);
+      if (nj == 3) hipLaunchKernelGGL(k_mabs_gemm_splitn<3>, g, dim3(256), 0, s, a);
+      if (nj) return;
+    }
     hipLaunchKernelGGL(k_mabs_gemm_split3, dim3((unsigned)nb), dim3(256), 0, s, b);
     return;
   }
