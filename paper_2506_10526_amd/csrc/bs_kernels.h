@@ -25,6 +25,7 @@ struct MabsFieldArgs {
   int n, nh, nc, vmax;
   int G;                    // fold of the column transform: length n / G, G blocks per column tile
   int CB, RB;               // columns, rows per block
+  int stream;               // rows leave by non-temporal stores (set by the launcher)
   int count_mode;           // 0: W V, 1: unit indicator [N_g > 0]
   int chan_offset;          // first channel of this launch (grid.y indexes channels from here)
   int ignore_chan;          // count mode, separable: channel-independent indicator

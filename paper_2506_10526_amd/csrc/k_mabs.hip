@@ -154,6 +154,28 @@ __global__ __launch_bounds__(256) void k_ring_rows(MabsFieldArgs a) {
   if constexpr (L > 0) lds_fft_ct<+1, T, L, RING_BLOCK / L, 256, L + 1>(A, nb, tw, 2);
   else lds_fft_ip<+1, T, 4>(A, a.prow, nb, tw, 2, ld);
   const T sc = T(a.scale);
+  if constexpr (L > 0) {
+    if (a.stream) {   // 16 bytes a store, past the caches
+      typedef T out16 __attribute__((ext_vector_type(16 / sizeof(T))));
+      constexpr int V = 16 / sizeof(Cx<T>);   // values a store: 2 or 1
+#pragma unroll
+      for (int u = 0; u < U / V; ++u) {
+        const int e = V * (threadIdx.x + 256 * u);
+        if (e >= nb * M) break;
+        int rl, k;
+        split(e, rl, k);
+        out16 o;
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+          const Cx<T> z = A[(size_t)rl * ld + k + q];
+          o[2 * q] = z.x * sc;
+          o[2 * q + 1] = z.y * sc;
+        }
+        __builtin_nontemporal_store(o, (out16*)&((Cx<T>*)(out + (size_t)rl * n))[k]);
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int e = threadIdx.x + 256 * u;
@@ -1885,8 +1907,14 @@ static void launch_ring_rows(const MabsFieldArgs& a, dim3 grid, size_t lds, hipS
   hipLaunchKernelGGL((k_ring_rows<T, L>), grid, dim3(256), lds, s, a);
 }
 // lengths with a compile-time transform: those of the uv grids in use (48 to 256, folded or not)
+// Fields larger than the 256 MB last-level cache leave it by non-temporal stores (no later pass could find them
+// there; the column pass's values do not have to make room): 192 x 256^2, 10 rings, 503 MB: 258 -> 240 us.  Smaller
+// ones stay for the contraction (48 x 96^2: 1 % slower with such stores).
 template <typename T>
-static void launch_mabs_fields(const MabsFieldArgs& a, int nbins, int nchan, hipStream_t s) {
+static void launch_mabs_fields(const MabsFieldArgs& a0, int nbins, int nchan, hipStream_t s) {
+  MabsFieldArgs a = a0;
+  a.stream = (long long)nbins * nchan * a.plane_stride * (long long)sizeof(T) > 1LL << 28 && (uintptr_t)a.out % 16 == 0 &&
+             a.plane_stride % (16 / sizeof(T)) == 0 && a.bin_stride % (16 / sizeof(T)) == 0;
   const int lc = a.n / a.G, lr = a.n / 2;
   const dim3 gc(a.G * ((a.vmax + a.CB) / a.CB), nchan, nbins), gr((a.n + a.RB - 1) / a.RB, nchan, nbins);
   const size_t bc = ((size_t)a.CB * (lc + 1) + a.n) * sizeof(Cx<T>), br = ((size_t)a.RB * (lr + 1) + a.n) * sizeof(Cx<T>);
