@@ -38,7 +38,7 @@ __device__ __forceinline__ double window_at(const MdftArgs& a, const double* __r
 //
 // Pass n deals each XCD one contiguous eighth of the groups, in that order: a group's rows are runs of 64
 // bytes that start anywhere in a line, and the neighbour that holds the rest of the line meets it in the same
-// L2 (dealt to the XCDs in turn, the pass fetched 1.4 times its input).
+// L2 (dealt to the XCDs in turn, the pass fetched 2.9 times its input).
 //
 // Pass n: W = 2 CB window columns (residues) c0 .. c0 + W - 1 per group, columns 2q and 2q + 1 packed
 // into complex line q (z = x0 + i x1), transformed along n; the half spectra a < H of both columns
