@@ -43,7 +43,7 @@ TRAFFIC_BYTES = {"k3_dft": (269.0 + 71.3) * 1e6,   # profiles/k3_dft_split_3d_25
                  "mono": (73.0 + 7.4) * 1e6,   # profiles/mono_multi_bin_133x768x768_k1x12.md
                  "multi": (73.1 + 19.1) * 1e6,   # the same
                  "kpar": (78.1 + 3.4) * 1e6,   # the same
-                 "grid": (126.9 + 8.1 + 1821.2 + 139.2 + 225.7 + 76.1) * 1e6}   # profiles/grid_262144x768_to_192x256x129.md
+                 "grid": (3.3 + 8.1 + 1821.4 + 139.1 + 142.0 + 76.1) * 1e6}   # profiles/grid_262144x768_to_192x256x129.md
 
 
 def log(*a):

@@ -659,6 +659,7 @@ static bool grid_workspace(bs_ctx* c, GridArgs& a) {
     a.stage_c = static_cast<int*>(ctx_ws(c, "grid_stage_c", (size_t)a.nco * a.cap * sizeof(int)));
     if (!a.fcnt || !a.foff || !a.fcell || !a.frank || !a.flist || !a.stage_v || !a.stage_c) a.cap = 0;   // no memory for it: atomics
   }
+  a.all_staged = a.cap > 0 && a.cap >= a.nvis;
   return a.code && a.hot_v && a.hot_c;
 }
 

@@ -354,6 +354,7 @@ struct GridArgs {
   // cell [n (n/2+1)] and two totals, a cell's first place in the list of slots, a slot's cell and rank in it,
   // the list, group sums [nco][cap] (re, im) and counts
   long long cap;
+  int all_staged;              // cap slots are enough for every baseline
   unsigned *fcnt, *foff, *fcell, *frank, *flist;
   double* stage_v;
   int* stage_c;

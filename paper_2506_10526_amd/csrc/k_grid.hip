@@ -16,15 +16,23 @@ namespace {
 
 constexpr int GRID_THREADS = 1024;
 
+// Whether acc and cnt hold a cell at all when every far baseline off the line q_v = 0 is staged: an LDS cell
+// (stored whole) or one of that line (atomics); the others are not cleared, written or read.
+__device__ __forceinline__ bool cell_held(const GridArgs& a, int iu, int iv) {
+  const int u = iu < a.n / 2 ? iu : a.n - iu;   // |q_u|
+  return iv == 0 || (u < a.hot && iv < a.hot && u < a.n / 2 && iv < a.n / 2);
+}
 __global__ void k_grid_zero(GridArgs a) {
-  const long long plane = (long long)a.n * (a.n / 2 + 1), cells = a.nco * plane;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < cells + 2; i += (long long)gridDim.x * blockDim.x) {
-    if (i < cells) {
-      *(double2*)&a.acc[2 * i] = make_double2(0.0, 0.0);
-      a.cnt[i] = 0;
-    }
-    if (a.cap > 0 && i <= plane + 1) a.fcnt[i] = 0;   // two totals after the cells
+  const int nh = a.n / 2 + 1, plane = a.n * nh;
+  const long long i0 = blockIdx.x * (long long)blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+  const long long cells = (long long)a.nco * (a.all_staged ? a.n : plane);
+  for (long long i = i0; i < cells; i += step) {
+    const long long at = a.all_staged ? i * nh : i;
+    *(double2*)&a.acc[2 * at] = make_double2(0.0, 0.0);
+    a.cnt[at] = 0;
   }
+  if (a.cap > 0)
+    for (long long i = i0; i < plane + 2; i += step) a.fcnt[i] = 0;   // two totals after the cells
 }
 
 // A baseline's place, decided once a call: its grid point is q = rint(U / du) per axis in FP64, reversed where
@@ -147,7 +155,7 @@ __device__ __forceinline__ int hot_cell(const GridArgs& a, int h) {
 // Bound: HBM (9 bytes a sample).  hot = 64 fills a CU's LDS (8128 cells) and holds nine tenths of
 // log-uniform baselines; with one share a channel its sums are stored for good.  262,144 baselines x 768
 // channels, 4:1, flags: 1560 us with 32 x 63 LDS cells, a division per channel group, loads that waited for
-// flags and atomics for the far cells; 695 with the atomics alone left, now 463: 4.1 TB/s.
+// flags and atomics for the far cells; 695 with the atomics alone left, now 453: 4.3 TB/s.
 template <bool VEC, bool PHASE>
 __global__ __launch_bounds__(GRID_THREADS) void k_grid_scatter(GridArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char grid_sh[];
@@ -304,7 +312,8 @@ __global__ void k_grid_out(GridArgs a, T* __restrict__ out, int32_t* __restrict_
 }
 // The same with the far cells' staged group sums gathered first.  Blocks are dealt to the eight XCDs in turn;
 // block b works on a channel o with o mod 8 = b mod 8, so that the gathers of a channel meet its staging
-// plane in one L2.  192 channels of 256^2, 262,144 baselines: 105 us.
+// plane in one L2.  192 channels of 256^2, 262,144 baselines: 98 us (105 reading every cell of acc, which k_grid_zero
+// then had to clear: 21 us, now 5).
 template <typename T>
 __global__ __launch_bounds__(256) void k_grid_fin(GridArgs a, T* __restrict__ out, int32_t* __restrict__ ng, int nx) {
   const int plane = a.n * (a.n / 2 + 1);
@@ -313,8 +322,13 @@ __global__ __launch_bounds__(256) void k_grid_fin(GridArgs a, T* __restrict__ ou
   const int i = (y % nx) * 256 + threadIdx.x;
   if (o >= a.nco || i >= plane) return;
   const long long at = o * plane + i;
-  double2 v = *(const double2*)&a.acc[2 * at];
-  int c = a.cnt[at];
+  const int nh = a.n / 2 + 1, iu = i / nh;
+  double2 v = make_double2(0.0, 0.0);
+  int c = 0;
+  if (!a.all_staged || cell_held(a, iu, i - iu * nh)) {
+    v = *(const double2*)&a.acc[2 * at];
+    c = a.cnt[at];
+  }
   const unsigned k = a.fcnt[i];
   const unsigned* run = a.flist + a.foff[i];
   for (unsigned s = 0; s < k; ++s) {
