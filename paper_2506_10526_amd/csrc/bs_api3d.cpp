@@ -597,7 +597,11 @@ extern "C" int bs_estimate_3d(bs_ctx* c, const bs_bins* b, const void* vis, cons
     held = std::make_shared<Est3>();
     rc = est3_prepare(c, b, &wm, precision, "c3", *held);
     if (rc) return rc;
-    c->est3 = held;
+    // a replay of a captured call that planned anew copies that call's tables into the workspaces, so the
+    // contents of the tables are unknown from then on and every call plans anew
+    bool in_graph = false;
+    for (const auto& kv : c->ws) in_graph = in_graph || (kv.second.in_graph && kv.first.compare(0, 2, "c3") == 0);
+    c->est3 = in_graph ? nullptr : held;
     c->est3_key = key;
     c->est3_gen = c->ws_gen;
   }

@@ -18,6 +18,7 @@ struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   std::vector<unsigned char> mirror;   // bytes last uploaded into p from the host (tables only)
+  bool in_graph = false;               // a captured graph copies a table into p on every replay
 };
 
 struct CountCache {
@@ -50,6 +51,7 @@ struct bs_ctx {
   uint64_t ws_gen = 0;                    // bumped whenever a workspace is reallocated or re-uploaded
   // last prepared unweighted 3D estimate, reused while its key and ws_gen still match
   std::shared_ptr<Est3> est3;
+  std::vector<std::unique_ptr<std::vector<unsigned char>>> graph_tables;   // host copies read by captured uploads
   std::string est3_key;
   uint64_t est3_gen = 0;
 };
@@ -73,7 +75,13 @@ void* ctx_ws(bs_ctx* c, const char* name, size_t bytes);       // grow-only; NUL
 const void* ctx_twiddle(bs_ctx* c, int L, bool fp64);          // NULL on failure
 // Host table -> named device workspace.  A table equal to what the workspace already holds is not
 // copied again: a copy from pageable memory would hold the host until the stream reaches it, so
-// repeated calls could no longer be queued ahead of the running kernels.
+// repeated calls could no longer be queued ahead of the running kernels.  Under stream capture the copy is
+// recorded, not made, and made again on every replay: it reads a host copy that the context keeps, and the
+// workspace's contents are not known from then on, so every later call copies.
+inline bool capturing(hipStream_t s) {   // the null stream cannot be captured
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
 template <typename X>
 inline X* upload(bs_ctx* c, const std::string& name, const std::vector<X>& v, int& rc) {
   X* d = (X*)ctx_ws(c, name.c_str(), std::max<size_t>(v.size() * sizeof(X), 16));
@@ -81,13 +89,20 @@ inline X* upload(bs_ctx* c, const std::string& name, const std::vector<X>& v, in
   DevBuf& wb = c->ws[name];
   const size_t nb = v.size() * sizeof(X);
   const unsigned char* hv = (const unsigned char*)v.data();
-  if (nb > 0 && !(wb.mirror.size() == nb && std::memcmp(wb.mirror.data(), hv, nb) == 0)) {
-    if (hipMemcpyAsync(d, v.data(), nb, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
-      wb.mirror.clear();
+  const bool cap = nb > 0 && capturing(c->stream);
+  if (nb > 0 && (cap || wb.in_graph || !(wb.mirror.size() == nb && std::memcmp(wb.mirror.data(), hv, nb) == 0))) {
+    const void* src = v.data();
+    if (cap) {
+      c->graph_tables.push_back(std::make_unique<std::vector<unsigned char>>(hv, hv + nb));
+      src = c->graph_tables.back()->data();
+      wb.in_graph = true;
+    }
+    wb.mirror.clear();
+    if (hipMemcpyAsync(d, src, nb, hipMemcpyHostToDevice, c->stream) != hipSuccess) {
       rc = ctx_fail(c, BS_EHIP, "upload " + name);
       return nullptr;
     }
-    wb.mirror.assign(hv, hv + nb);
+    if (!wb.in_graph) wb.mirror.assign(hv, hv + nb);
     ++c->ws_gen;
   }
   rc = BS_OK;
