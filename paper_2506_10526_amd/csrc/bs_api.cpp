@@ -1020,16 +1020,20 @@ extern "C" int bs_estimate_mabs(bs_ctx* c, const bs_bins* b, const void* vis, co
   int tb = (int)std::max<size_t>(1, std::min<size_t>(ntri, budget / std::max<size_t>(per_tri, 1)));
   MabsGemmArgs shape{};
   shape.nc = nc; shape.n_nu1 = n_nu1; shape.ntri = tb;
-  const int kchunks64 = pixel_chunks(mabs_f64_blocks(shape), 512);
-  const int kchunks = fp64 ? kchunks64 : pixel_chunks(((nrows + 127) / 128) * ((nc + 127) / 128) * tb, 1024);
-  const int kchunk = Ppix / kchunks, kchunk64 = Ppix / kchunks64;
+  int kchunks64 = pixel_chunks(mabs_f64_blocks(shape), 512);
   if (!separable) {
-    // per-channel count fields, FP64 GEMM: chains of kchunk products, then the chunk sums
-    c->last_count_bound = ring_count_bound(P, tri, (double)kchunk64 + (double)kchunks64 + 4.0);
+    // Per-channel count fields, FP64 GEMM: chains of Ppix / kchunks64 products, then the chunk sums.  Where many
+    // blocks leave chunks too long to certify the counts, shorter ones (768^2, 4 channels, 98 triangles with a
+    // ring of 200,000 cells: one chunk has the bound 2.7, eight have 0.35).
+    auto bound = [&](int k) { return ring_count_bound(P, tri, (double)(Ppix / k) + (double)k + 4.0); };
+    while (!(bound(kchunks64) < 0.5) && Ppix / (kchunks64 * 2) >= 512 && (Ppix / (kchunks64 * 2)) % 32 == 0) kchunks64 *= 2;
+    c->last_count_bound = bound(kchunks64);
     if (!(c->last_count_bound < 0.5))
       return ctx_fail(c, BS_ECOUNT, "triangle counts cannot be certified at this size (FP64 error bound " +
                                         std::to_string(c->last_count_bound) + " >= 1/2)");
   }
+  const int kchunks = fp64 ? kchunks64 : pixel_chunks(((nrows + 127) / 128) * ((nc + 127) / 128) * tb, 1024);
+  const int kchunk = Ppix / kchunks, kchunk64 = Ppix / kchunks64;
   // the batch must hold kchunks partial copies
   tb = (int)std::max<size_t>(1, std::min<size_t>(ntri, budget / std::max<size_t>(per_tri * std::max(kchunks, separable ? 1 : kchunks64), 1)));
   double* S = (double*)ctx_ws(c, "mabs_S", per_tri * kchunks * tb);
