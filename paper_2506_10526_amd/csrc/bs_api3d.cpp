@@ -365,15 +365,23 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
   if (it == c->counts.end()) {
     // Certification of the rounding: the FP64 count fields come from C2C passes along v and u
     // and a C2R pass along eta (three rounded normalisations); the contraction's longest chain
-    // of roundings is one run of MFMA steps (128 products), one flush per run of a wave's quarter of the
-    // block's chunk, the four waves of the block, and the two stages of the fixed-order partial sums.
+    // of roundings is one run of MFMA steps, the flushes of the runs of a wave's quarter of the block's
+    // chunk, the four waves of the block, and the two stages of the fixed-order partial sums.  Runs of
+    // kCon64Flush voxels are the fastest; where only shorter ones certify the counts (64 or 32 voxels on
+    // blocks of few slabs: 128^2 x 324: depth 206 / 152 / 140), those are taken.
     const double eps_field = bsplan::field_error_units(2 * bsplan::fft_stage_units(P.n) + bsplan::fft_stage_units(e.M64) + 2, 3);
-    const double depth = 129.0 + (double)((e.chunk64 / 4 + 127) / 128) + 5.0 + (double)kReduceGroup +
-                         (double)((e.nblk64 + kReduceGroup - 1) / kReduceGroup) + 1.0;
+    int flush = kCon64Flush;
     double bound = 0.0;
-    for (int t = 0; t < ntri; ++t)
-      bound = std::max(bound, bsplan::count_error_bound((double)P.modes[P.tri[3 * t]], (double)P.modes[P.tri[3 * t + 1]],
+    for (int run : {kCon64Flush, 64, 32}) {
+      const double depth = (double)run + (double)((e.chunk64 / 4 + run - 1) / run) + 3.0 + (double)kReduceGroup +
+                           (double)((e.nblk64 + kReduceGroup - 1) / kReduceGroup);
+      double most = 0.0;
+      for (int t = 0; t < ntri; ++t)
+        most = std::max(most, bsplan::count_error_bound((double)P.modes[P.tri[3 * t]], (double)P.modes[P.tri[3 * t + 1]],
                                                         (double)P.modes[P.tri[3 * t + 2]], eps_field, depth));
+      if (run == kCon64Flush || most < bound) { bound = most; flush = run; }
+      if (bound < 0.5) break;
+    }
     c->last_count_bound = bound;
     if (!(bound < 0.5))
       return ctx_fail(c, BS_ECOUNT, "3D triangle counts cannot be certified at this size (FP64 error bound " +
@@ -386,7 +394,7 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
     if (rc) return rc;
     Con3Args ca{};
     ca.F = F64; ca.vox = e.vox64; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
-    ca.chunk = e.chunk64; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
+    ca.chunk = e.chunk64; ca.partial = e.partial; ca.ct1 = e.ct1_tiles; ca.flush = flush;
     launch_contract64(ca, (int)e.nblk64, c->stream);
     LAUNCHCHK(c, "count contraction");
     double* Ssum = (double*)ctx_ws(c, "c3_Ssum", (size_t)ntri * 8 + 16);
@@ -545,7 +553,7 @@ int est3_enqueue(bs_ctx* c, const bs_bins* b, const void* vis, const bs_weights*
     if (c->timing) { (void)hipEventRecord(c->ev[5], c->stream); (void)hipEventRecord(c->ev[2], c->stream); }
     Con3Args ca{};
     ca.F = e.F; ca.vox = e.fp64 ? e.vox64 : e.nvox; ca.nbu = (int)e.blocks.size(); ca.pairs = e.d_pairs; ca.npairs = e.npairs;
-    ca.chunk = e.fp64 ? e.chunk64 : e.chunk; ca.partial = e.partial; ca.ct1 = e.ct1_tiles;
+    ca.chunk = e.fp64 ? e.chunk64 : e.chunk; ca.partial = e.partial; ca.ct1 = e.ct1_tiles; ca.flush = kCon64Flush;
     if (e.fp64) launch_contract64(ca, (int)e.nblk64, c->stream);
     else launch_contract3(ca, e.precision == BS_FP32 ? 1 : 2, (int)e.nblk, c->stream);
     LAUNCHCHK(c, "contraction");

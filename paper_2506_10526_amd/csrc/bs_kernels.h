@@ -185,8 +185,9 @@ struct Con3Args {
   long long chunk;             // voxels per block (multiple of 128)
   double* partial;             // [gridDim.x][112][32]
   int ct1;                     // FP64 form: pair row tiles (the leading ones) contracted against fields 16..31 too
+  int flush;                   // FP64 form: voxels a wave sums in one MFMA run (a multiple of 32)
 };
-constexpr int kCon64Fields = 32;
+constexpr int kCon64Fields = 32, kCon64Flush = 128;
 // FP64 form: writes the rows of the pair tiles in use only
 void launch_contract64(const Con3Args& a, int nblocks, hipStream_t s);
 

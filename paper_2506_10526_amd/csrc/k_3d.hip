@@ -549,12 +549,12 @@ __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
 // 32 w + 31, lane group g voxels 8 s + 2 g and + 1 of every eight (one 16-byte read per operand serves two
 // mfma_f64_16x16x4 steps; the row stride of 130 doubles puts 16 rows on distinct banks), row nbu of a
 // buffer is zero and stands in for padding pairs and fields.  Only the leading a.ct1 pair tiles serve a
-// third field past 15.  Sums: MFMA chains of C64_FLUSH voxels a wave, added into a second FP64 sum (the
+// third field past 15.  Sums: MFMA chains of a.flush voxels a wave, added into a second FP64 sum (the
 // count certification bounds the longest chain of roundings).  Bound: HBM (each field read once) and FP64
 // issue.  Against 128-voxel slabs
 // without prefetch, a flush every slab and seven pair tiles always: 48^2 x 768, 20 shells 630 -> 116 us,
 // 256^2 x 768 counts 16.4 -> 2.9 ms (8 GB of fields; 1.6 ms on the 384-point delay grid).
-constexpr int C64_SLAB = 128, C64_LD = C64_SLAB + 2, C64_FLUSH = 128;
+constexpr int C64_SLAB = 128, C64_LD = C64_SLAB + 2;
 template <int RT>
 __global__ __launch_bounds__(256, RT <= 4 ? 2 : 1) void k3_contract64(Con3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(256, RT <= 4 ? 2 : 1) void k3_contract64(Con3Args a
       }
     }
     since += C64_SLAB / 4;
-    if (since >= C64_FLUSH || !more) {
+    if (since >= a.flush || !more) {
       since = 0;
 #pragma unroll
       for (int i = 0; i < RT; ++i)
