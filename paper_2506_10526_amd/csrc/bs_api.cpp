@@ -475,7 +475,7 @@ extern "C" int bs_monopole(bs_ctx* c, int32_t nc, int32_t n_tri, const double* k
   const long long rows = (long long)n_tri * nc;
   const int nblocks = (int)std::max(1LL, std::min(2048LL, (rows + 3) / 4));
   MonoArgs a{};
-  double* dk = static_cast<double*>(ctx_ws(c, "mono_k", (size_t)(3 * std::max(n_tri, 1) + n_k1 + 1) * sizeof(double)));
+  double* dk = static_cast<double*>(ctx_ws(c, "mono_k", ((size_t)3 * std::max(n_tri, 1) + n_k1 + 1) * sizeof(double)));
   a.psum = static_cast<double*>(ctx_ws(c, "mono_psum", (size_t)nblocks * nb * sizeof(double)));
   a.pcnt = static_cast<int*>(ctx_ws(c, "mono_pcnt", (size_t)nblocks * nb * sizeof(int)));
   a.stage_s = static_cast<double*>(ctx_ws(c, "mono_stage_s", (size_t)part_groups(nblocks) * nb * sizeof(double)));
@@ -599,7 +599,7 @@ extern "C" int bs_multipoles(bs_ctx* c, int32_t nc, int32_t n_tri, const double*
   // a wave per row: blocks of eight rows, at most 512 blocks
   const int nblocks = (int)std::max(1LL, std::min(512LL, (rows + 7) / 8));
   MultiArgs a{};
-  double* dk = static_cast<double*>(ctx_ws(c, "multi_k", (size_t)(3 * std::max(n_tri, 1) + n_k1 + 1) * sizeof(double)));
+  double* dk = static_cast<double*>(ctx_ws(c, "multi_k", ((size_t)3 * std::max(n_tri, 1) + n_k1 + 1) * sizeof(double)));
   a.m.psum = static_cast<double*>(ctx_ws(c, "multi_psum", (size_t)nblocks * nb * nlm * sizeof(double)));
   a.m.pcnt = static_cast<int*>(ctx_ws(c, "multi_pcnt", (size_t)nblocks * nb * sizeof(int)));
   a.m.stage_s = static_cast<double*>(ctx_ws(c, "multi_stage_s", (size_t)part_groups(nblocks) * nb * nlm * sizeof(double)));

@@ -108,9 +108,11 @@ __global__ __launch_bounds__(MONO_THREADS) void k_mono_bin(MonoArgs a) {
   const double elo = k1e[0] * (1.0 - 0x1p-20), ehi = k1e[a.nk] * (1.0 + 0x1p-20);
   const double lo2 = elo * elo, hi2 = ehi * ehi;
   const int nc = a.nc, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int row = blockIdx.x * WPB + wave; row < a.nt * nc; row += gridDim.x * WPB) {
-    const int ai = row / a.nt, t = row - ai * a.nt;
-    const double kq0 = a.kperp[3 * t], kq1 = a.kperp[3 * t + 1], kq2 = a.kperp[3 * t + 2];
+  // 64 bits: nt nc may be 2^31 - 1, and the last rows' successors and 3 t exceed it
+  for (long long row = blockIdx.x * WPB + wave; row < (long long)a.nt * nc; row += gridDim.x * WPB) {
+    const int ai = (int)row / a.nt, t = (int)row - ai * a.nt;
+    const double* kq = a.kperp + 3LL * t;
+    const double kq0 = kq[0], kq1 = kq[1], kq2 = kq[2];
     const double kp1 = a.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc);
     if (row_above_edges(hi2, kq0, kp1)) continue;   // wave-uniform
     int jlo, jhi;
@@ -356,8 +358,8 @@ __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1
     const int ai = (int)(ab >> 16), b = (int)(ab & 0xffffu);
     double pz = 0.0, px = 0.0, py = 0.0;
     bool az = false;
-    const int bin = cell_bin_orient(k1e, a.m.nk, lo2, hi2, a.m.kperp[3 * t], a.m.kperp[3 * t + 1],
-                                    a.m.kperp[3 * t + 2], a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc),
+    const double* kq = a.m.kperp + 3LL * t;
+    const int bin = cell_bin_orient(k1e, a.m.nk, lo2, hi2, kq[0], kq[1], kq[2], a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc),
                                     a.m.kpar_unit * (double)(2 * b < nc ? b : b - nc), pz, px, py, az);
     if (bin < 0) continue;
     if (bin != run.cur) {
@@ -420,9 +422,10 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
     if (row < (long long)a.m.nt * nc) {
       ai = (int)row / a.m.nt;
       t = (int)row - ai * a.m.nt;
-      kq0 = a.m.kperp[3 * t];
-      kq1 = a.m.kperp[3 * t + 1];
-      kq2 = a.m.kperp[3 * t + 2];
+      const double* kq = a.m.kperp + 3LL * t;
+      kq0 = kq[0];
+      kq1 = kq[1];
+      kq2 = kq[2];
       kp1 = a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc);
       if (!row_above_edges(hi2, kq0, kp1)) row_span(hi2, kq1, kq2, kp1, a.m.kpar_unit, nc, jlo, jhi);
     }
