@@ -425,8 +425,9 @@ int bs_batch_tile(const bs_batch* batch, int32_t cube, int32_t* tile_m, int32_t*
  * bs_mlp_train: `steps` full-batch Adam steps (b1 0.9, b2 0.999, eps 1e-8; learning rate lr, or
  *   lr (1 + cos(pi k / steps)) / 2 at step k of this call when cosine != 0).  loss_host: the loss
  *   evaluated in the last step (before its update).
- * bs_mlp_predict: t = mu_t + s_t y'(x') for X (device float [n][4]) into y (device float [n]);
- *   bf16 != 0 evaluates layers 2-4 with bfloat16 weights and activations (FP32 accumulation).
+ * bs_mlp_predict: t = mu_t + s_t y'(x') for X (device float [n][4]) into y (device float [n], which may
+ *   overlap X: X is then copied first); bf16 != 0 evaluates layers 2-4 with bfloat16 weights and activations (FP32
+ *   accumulation).
  * bs_var_features (host only): X_host [n_cand][4] and, when T3D_host is given, base_host [n_cand]
  *   (the baseline above; -inf where T3D = 0) for the candidate triangles of 3D bins. */
 #define BS_MLP_NPARAM 133121

@@ -253,6 +253,12 @@ extern "C" int bs_mlp_predict(bs_mlp* m, const float* X, int32_t n, int32_t bf16
     if (!bf16) {
       MlpRowArgs a{};
       a.X = X; a.p = m->state; a.norm = norm; a.n = n; a.y = y;
+      // blocks write their rows of y while others have yet to read theirs of X
+      const uintptr_t x0 = (uintptr_t)X, y0 = (uintptr_t)y;
+      if (y0 < x0 + (size_t)n * 16 && x0 < y0 + (size_t)n * 4) {
+        HIPCHK(c, hipMemcpyAsync(m->Xp, X, (size_t)n * 16, hipMemcpyDeviceToDevice, s));
+        a.X = m->Xp;
+      }
       launch_mlp_predict(a, s);
     } else {
       launch_normalise(X, nullptr, n, norm, m->Xp, nullptr, s);
