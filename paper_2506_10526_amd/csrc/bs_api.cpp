@@ -39,7 +39,7 @@ void* ctx_ws(bs_ctx* c, const char* name, size_t bytes) {
   if (b.bytes >= bytes) return b.p;
   if (b.p) { (void)hipFree(b.p); b.p = nullptr; b.bytes = 0; }
   b.mirror.clear();
-  ++c->ws_gen;
+  if (ctx_plan3_ws(name)) ++c->est3_ws_gen;
   if (getenv("BS_FORCE_ENOMEM")) return nullptr;
   void* p = nullptr;
   if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
@@ -152,7 +152,7 @@ extern "C" int bs_set_stream(bs_ctx* c, void* s) {
   // tables uploaded on the old stream are uploaded again on the new one
   if ((hipStream_t)s != c->stream) {
     for (auto& kv : c->ws) kv.second.mirror.clear();
-    ++c->ws_gen;
+    ++c->est3_ws_gen;
   }
   c->stream = (hipStream_t)s;
   return BS_OK;

@@ -581,7 +581,7 @@ extern "C" int bs_estimate_3d(bs_ctx* c, const bs_bins* b, const void* vis, cons
   if (c->timing) { (void)hipEventRecord(c->ev[0], c->stream); (void)hipEventRecord(c->ev[4], c->stream); }
   // Calls reuse the last prepared estimate (pair cover, work lists, uploaded tables: 1.3 ms of host work
   // on the 256^2 x 768 cube) as long as the bins, the uv mask's contents, precision and path switches
-  // are the same and no workspace has changed since.  The channel weights do not enter it: the kernels
+  // are the same and none of its workspaces has changed since.  The channel weights do not enter it: the kernels
   // read them, rho3 included.
   const bs_weights wm{nullptr, w ? w->uv_mask : nullptr, nullptr};
   uint64_t mask = 0;
@@ -599,19 +599,19 @@ extern "C" int bs_estimate_3d(bs_ctx* c, const bs_bins* b, const void* vis, cons
     key += std::string(":") + (v ? v : "-");
   }
   std::shared_ptr<Est3> held;
-  if (c->est3 && c->est3_key == key && c->est3_gen == c->ws_gen) {
+  if (c->est3 && c->est3_key == key && c->est3_gen == c->est3_ws_gen) {
     held = c->est3;
   } else {
     held = std::make_shared<Est3>();
-    rc = est3_prepare(c, b, &wm, precision, "c3", *held);
+    rc = est3_prepare(c, b, &wm, precision, PLAN3_TAG, *held);
     if (rc) return rc;
     // a replay of a captured call that planned anew copies that call's tables into the workspaces, so the
     // contents of the tables are unknown from then on and every call plans anew
     bool in_graph = false;
-    for (const auto& kv : c->ws) in_graph = in_graph || (kv.second.in_graph && kv.first.compare(0, 2, "c3") == 0);
+    for (const auto& kv : c->ws) in_graph = in_graph || (kv.second.in_graph && ctx_plan3_ws(kv.first));
     c->est3 = in_graph ? nullptr : held;
     c->est3_key = key;
-    c->est3_gen = c->ws_gen;
+    c->est3_gen = c->est3_ws_gen;
   }
   Est3& e = *held;
   if (e.ntri == 0) return BS_OK;

@@ -48,8 +48,9 @@ struct bs_ctx {
   int last_grid_M = 0;   // delay-axis grid of the last 3D contraction
   double last_flops_vox = 0.0, last_vox = 0.0;   // algorithmic MFMA flops per voxel, voxels (MFMA synthesis path)
   std::map<std::string, int> tuned;       // autotuned launch parameters, by shape key
-  uint64_t ws_gen = 0;                    // bumped whenever a workspace is reallocated or re-uploaded
-  // last prepared unweighted 3D estimate, reused while its key and ws_gen still match
+  // bumped whenever a workspace of the 3D estimate (ctx_plan3_ws) is reallocated or uploaded to again
+  uint64_t est3_ws_gen = 0;
+  // last prepared 3D estimate, reused while its key and est3_ws_gen still match
   std::shared_ptr<Est3> est3;
   std::vector<std::unique_ptr<std::vector<unsigned char>>> graph_tables;   // host copies read by captured uploads
   std::string est3_key;
@@ -73,6 +74,10 @@ double ring_count_bound(const bsplan::Plan& P, const std::vector<int>& tri, doub
 int ctx_fail(bs_ctx* c, int code, const std::string& msg);
 void* ctx_ws(bs_ctx* c, const char* name, size_t bytes);       // grow-only; NULL on failure
 const void* ctx_twiddle(bs_ctx* c, int L, bool fp64);          // NULL on failure
+// The workspaces that a prepared bs_estimate_3d points to: those of its tag, PLAN3_TAG.  Other calls' workspaces
+// may change between two estimates without a new plan.
+constexpr const char* PLAN3_TAG = "c3";
+inline bool ctx_plan3_ws(const std::string& name) { return name.compare(0, 2, PLAN3_TAG) == 0; }
 // Host table -> named device workspace.  A table equal to what the workspace already holds is not
 // copied again: a copy from pageable memory would hold the host until the stream reaches it, so
 // repeated calls could no longer be queued ahead of the running kernels.  Under stream capture the copy is
@@ -103,7 +108,7 @@ inline X* upload(bs_ctx* c, const std::string& name, const std::vector<X>& v, in
       return nullptr;
     }
     if (!wb.in_graph) wb.mirror.assign(hv, hv + nb);
-    ++c->ws_gen;
+    if (ctx_plan3_ws(name)) ++c->est3_ws_gen;
   }
   rc = BS_OK;
   return d;
