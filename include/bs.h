@@ -142,9 +142,10 @@ int bs_filter_fields(bs_ctx* ctx, const bs_bins* bins, const void* vis, const bs
  * the same shape, the per-cell counts of bs_weights (W_g = 1/N_g; bs_weights takes them as uint16).  Sums are
  * accumulated in float64 (atomics: the order of additions, hence the last bits of a float64
  * result, may vary between calls); counts are exact.  Scratch, of context workspace: 20 bytes a cell,
- * 4 bytes a baseline, and from 32,768 baselines 20 bytes a baseline and output channel (1 GiB at most;
- * slower without) with lists of 12 bytes a baseline and 8 a cell of one channel; below, or with fewer output
- * channels than CUs, up to 512 partials of the cells around the origin (163 or 41 KB each).
+ * 4 bytes a baseline, and from 32,768 baselines, where channels and cells are many enough for it to pay, 20
+ * bytes a baseline and output channel (1 GiB at most; slower without) with lists of 12 bytes a baseline and 8 a
+ * cell of one channel; below, or with fewer output channels than CUs, up to 512 partials of the cells around
+ * the origin (163 or 40 KB each).
  * bs_last_timing reports [0] the call, [1] the scatter passes, [2] the output pass.
  * Errors: BS_EINVAL (n odd or outside [2, 4096], nc not a multiple of chan_avg, du <= 0,
  * n_vis outside [0, 2^34], NULL pointers), BS_ENOMEM, BS_EHIP. */

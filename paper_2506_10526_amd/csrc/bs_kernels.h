@@ -369,7 +369,9 @@ struct GridArgs {
 constexpr __host__ __device__ int grid_nhot(int hot) { return (2 * hot - 1) * hot; }
 // LDS cells and shares.  From 32,768 baselines the 64-cell region (one block a CU, 162 KB) pays for clearing
 // and storing it, with as many shares as fill the chip once; below, 32 cells (40 KB, three blocks a CU)
-// and shares of 2048 baselines at least, up to two blocks a CU.
+// and shares of 2048 baselines at least, up to two blocks a CU.  us a call, 64 / 32 cells, 256^2: 32,768 baselines x 1
+// channel 22 / 20, x 24 45 / 52, x 192 93 / 274; 8128 x 1 20 / 19, x 24 33 / 28; many channels gain from it sooner
+// (16,384 x 192 74 / 170).  Least shares of 1024 / 2048 / 4096: 8128 x 1 channel 18 / 18 / 20, x 24 25 / 23 / 23.
 inline void grid_layout(GridArgs& a) {
   const bool big = a.nvis >= 32768;
   a.hot = big ? 64 : 32;
@@ -377,10 +379,16 @@ inline void grid_layout(GridArgs& a) {
   const long long k = want < 1 ? 1 : want < most ? want : most < 1 ? 1 : most;
   a.share = ((a.nvis + k - 1) / k + 3) / 4 * 4;
   if (a.share < 4) a.share = 4;
-  // staging: a slot for every baseline within 1 GiB (slots past it: atomics; slots and ranks are 32 bits); its
-  // two extra launches do not pay in small calls (8128 x 24: 20 us in all, 21 with them)
-  const long long slots = (1LL << 30) / (20LL * (a.nco > 0 ? a.nco : 1));
-  a.cap = !big || a.nvis >> 31 ? 0 : a.nvis < slots ? a.nvis : slots;
+  // staging: a slot for every baseline within 1 GiB (slots past it: atomics; slots and ranks are 32 bits).  What it
+  // costs a call (two launches, a pass over a plane of counters) it gains from each channel: atomics of the far
+  // baselines, clearing and reading back the far cells.  In us, gain 1e-5 nco (nvis + 0.65 plane) against 15 + 2.7e-6
+  // plane.  Staged / not, plane of 256^2 unless given: 3 channels x 262,144 baselines 53 / 46, 12 x 100,000 53 / 50,
+  // 24 x 65,536 54 / 57, 9 x 262,144 58 / 69, 192 x 262,144 544 / 889; 512^2 1 x 262,144 51 / 38, 1024^2 4 x 40,000
+  // 55 / 41, 24 x 33,000 96 / 195, 2048^2 4 x 65,536 93 / 96, 4096^2 2 x 65,536 156 / 208.  Grids within the LDS
+  // region have no far cells (64^2, 64 x 33,000: 51 / 41).
+  const long long plane = (long long)a.n * (a.n / 2 + 1), slots = (1LL << 30) / (20LL * (a.nco > 0 ? a.nco : 1));
+  const bool pays = a.n / 2 > a.hot && 20 * a.nco * (20 * a.nvis + 13 * plane) > 600000000LL + 108 * plane;
+  a.cap = !big || !pays || a.nvis >> 31 ? 0 : a.nvis < slots ? a.nvis : slots;
 }
 inline long long grid_shares(const GridArgs& a) { return a.nvis > 0 ? (a.nvis + a.share - 1) / a.share : 1; }
 void launch_grid_zero(const GridArgs& a, hipStream_t s);

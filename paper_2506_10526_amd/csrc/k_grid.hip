@@ -109,20 +109,38 @@ __global__ __launch_bounds__(256) void k_grid_code(GridArgs a) {
       if (i0 + q < a.nvis) a.code[i0 + q] = code[q];
   }
 }
-// the far cells' runs in the list of slots, in no particular order of cells (one atomic a wave)
+// the far cells' runs in the list of slots, in no particular order of cells (four cells a thread and one atomic
+// a block: all of them meet on one address; 4096^2, an atomic a wave, 174 us)
 __global__ __launch_bounds__(256) void k_grid_off(GridArgs a) {
-  const int plane = a.n * (a.n / 2 + 1), i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
-  const unsigned k = i < plane ? a.fcnt[i] : 0u;
-  unsigned inc = k;
+  __shared__ unsigned wsum[4], base;
+  const int plane = a.n * (a.n / 2 + 1), lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i0 = 4 * (blockIdx.x * 256 + threadIdx.x);
+  unsigned k[4], sum = 0u;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    k[q] = i0 + q < plane ? a.fcnt[i0 + q] : 0u;
+    sum += k[q];
+  }
+  unsigned inc = sum;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const unsigned x = __shfl_up(inc, o);
     if (lane >= o) inc += x;
   }
-  unsigned base = 0u;
-  if (lane == 63 && inc) base = atomicAdd(a.fcnt + plane + 1, inc);
-  base = __shfl(base, 63);
-  if (i < plane) a.foff[i] = base + inc - k;
+  if (lane == 63) wsum[w] = inc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    base = tot ? atomicAdd(a.fcnt + plane + 1, tot) : 0u;
+  }
+  __syncthreads();
+  unsigned at = base + inc - sum;
+  for (int v = 0; v < w; ++v) at += wsum[v];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (i0 + q < plane) a.foff[i0 + q] = at;
+    at += k[q];
+  }
 }
 __global__ __launch_bounds__(256) void k_grid_list(GridArgs a) {
   const unsigned tot = a.fcnt[a.n * (a.n / 2 + 1)], m = tot < (unsigned)a.cap ? tot : (unsigned)a.cap;
@@ -278,24 +296,39 @@ __global__ __launch_bounds__(GRID_THREADS) void k_grid_scatter(GridArgs a) {
   }
 }
 
-// The LDS cells' partials added over the shares in order, one plain store per cell and output channel.
+// The LDS cells' partials added over the shares, one plain store per cell and output channel.  A block takes 32
+// cells; eight groups of threads sum interleaved shares, four loads in flight, then the groups in order (a
+// thread a cell over all shares waited for each in turn: 1 channel, 262,144 baselines, 256^2 65 us a call, now 34).
 __global__ __launch_bounds__(256) void k_grid_hot(GridArgs a, int shares) {
-  const int h = blockIdx.x * 256 + threadIdx.x, nhot = grid_nhot(a.hot);
+  __shared__ double sr[8][32], si[8][32];
+  __shared__ int sc[8][32];
+  const int l = threadIdx.x & 31, q = threadIdx.x >> 5, h = blockIdx.x * 32 + l, nhot = grid_nhot(a.hot);
   const long long o = blockIdx.y;
-  if (h >= nhot) return;
-  const int cell = hot_cell(a, h);
-  if (cell < 0) return;
   double re = 0.0, im = 0.0;
   int c = 0;
-  for (int b = 0; b < shares; ++b) {
-    const long long k = (o * shares + b) * nhot + h;
-    re += a.hot_v[2 * k];
-    im += a.hot_v[2 * k + 1];
-    c += a.hot_c[k];
+  if (h < nhot)
+#pragma unroll 4
+    for (int b = q; b < shares; b += 8) {
+      const long long k = (o * shares + b) * nhot + h;
+      const double2 v = *(const double2*)&a.hot_v[2 * k];
+      re += v.x;
+      im += v.y;
+      c += a.hot_c[k];
+    }
+  sr[q][l] = re;
+  si[q][l] = im;
+  sc[q][l] = c;
+  __syncthreads();
+  if (q || h >= nhot) return;
+  const int cell = hot_cell(a, h);
+  if (cell < 0) return;
+  for (int k = 1; k < 8; ++k) {
+    re += sr[k][l];
+    im += si[k][l];
+    c += sc[k][l];
   }
   const long long at = o * a.n * (a.n / 2 + 1) + cell;
-  a.acc[2 * at] = re;
-  a.acc[2 * at + 1] = im;
+  *(double2*)&a.acc[2 * at] = make_double2(re, im);
   a.cnt[at] = c;
 }
 
@@ -312,14 +345,16 @@ __global__ void k_grid_out(GridArgs a, T* __restrict__ out, int32_t* __restrict_
 }
 // The same with the far cells' staged group sums gathered first.  Blocks are dealt to the eight XCDs in turn;
 // block b works on a channel o with o mod 8 = b mod 8, so that the gathers of a channel meet its staging
-// plane in one L2.  192 channels of 256^2, 262,144 baselines: 98 us (105 reading every cell of acc, which k_grid_zero
-// then had to clear: 21 us, now 5).
+// plane in one L2; the channels past a multiple of eight are spread over all of them (4 channels of 2048^2 on
+// four XCDs: 220 us a call, now 93).  192 channels of 256^2, 262,144 baselines: 98 us (105 reading every cell
+// of acc, which k_grid_zero then had to clear: 21 us, now 5).
 template <typename T>
 __global__ __launch_bounds__(256) void k_grid_fin(GridArgs a, T* __restrict__ out, int32_t* __restrict__ ng, int nx) {
   const int plane = a.n * (a.n / 2 + 1);
-  const int x = blockIdx.x & 7, y = blockIdx.x >> 3;
-  const long long o = (long long)(y / nx) * 8 + x;
-  const int i = (y % nx) * 256 + threadIdx.x;
+  int y = blockIdx.x / nx;
+  if (y < a.nco / 8 * 8) y = (blockIdx.x >> 3) / nx * 8 + (blockIdx.x & 7);
+  const long long o = y;
+  const int i = (y < a.nco / 8 * 8 ? (blockIdx.x >> 3) % nx : blockIdx.x % nx) * 256 + threadIdx.x;
   if (o >= a.nco || i >= plane) return;
   const long long at = o * plane + i;
   const int nh = a.n / 2 + 1, iu = i / nh;
@@ -353,7 +388,7 @@ void launch_grid_scatter(const GridArgs& a, hipStream_t s) {
   if (a.cap > 0) {
     const long long cb = (a.nvis + 1023) / 1024, lb = (a.cap + 255) / 256;
     hipLaunchKernelGGL(k_grid_code<true>, dim3((unsigned)std::min(cb, 2048LL)), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_grid_off, dim3((a.n * (a.n / 2 + 1) + 255) / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_grid_off, dim3((a.n * (a.n / 2 + 1) + 1023) / 1024), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_grid_list, dim3((unsigned)std::min(lb, 1024LL)), dim3(256), 0, s, a);
   } else {
     hipLaunchKernelGGL(k_grid_code<false>, dim3((unsigned)std::min((a.nvis + 255) / 256, 2048LL)), dim3(256), 0, s, a);
@@ -377,7 +412,7 @@ void launch_grid_scatter(const GridArgs& a, hipStream_t s) {
     b.stage_c += (long long)o0 * a.cap;
     hipLaunchKernelGGL(k, dim3(shares, no), dim3(GRID_THREADS), lds, s, b);
     if (shares > 1)
-      hipLaunchKernelGGL(k_grid_hot, dim3((grid_nhot(a.hot) + 255) / 256, no), dim3(256), 0, s, b, (int)shares);
+      hipLaunchKernelGGL(k_grid_hot, dim3((grid_nhot(a.hot) + 31) / 32, no), dim3(256), 0, s, b, (int)shares);
   }
 }
 
@@ -398,7 +433,7 @@ void launch_grid_fin(const GridArgs& a, bool fp64, void* out, int32_t* ng, hipSt
     b.cnt += o0 * plane;
     b.stage_v += 2 * (long long)o0 * a.cap;
     b.stage_c += (long long)o0 * a.cap;
-    const dim3 g((unsigned)(8LL * nx * ((b.nco + 7) / 8)));
+    const dim3 g((unsigned)((long long)nx * b.nco));
     if (fp64) hipLaunchKernelGGL(k_grid_fin<double>, g, dim3(256), 0, s, b, static_cast<double*>(out) + 2 * o0 * plane, ng + o0 * plane, nx);
     else hipLaunchKernelGGL(k_grid_fin<float>, g, dim3(256), 0, s, b, static_cast<float*>(out) + 2 * o0 * plane, ng + o0 * plane, nx);
   }
