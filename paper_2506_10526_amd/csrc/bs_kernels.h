@@ -387,7 +387,7 @@ inline void grid_layout(GridArgs& a) {
   // 55 / 41, 24 x 33,000 96 / 195, 2048^2 4 x 65,536 93 / 96, 4096^2 2 x 65,536 156 / 208.  Grids within the LDS
   // region have no far cells (64^2, 64 x 33,000: 51 / 41).
   const long long plane = (long long)a.n * (a.n / 2 + 1), slots = (1LL << 30) / (20LL * (a.nco > 0 ? a.nco : 1));
-  const bool pays = a.n / 2 > a.hot && 20 * a.nco * (20 * a.nvis + 13 * plane) > 600000000LL + 108 * plane;
+  const bool pays = a.n / 2 > a.hot && 1e-5 * a.nco * ((double)a.nvis + 0.65 * plane) > 15.0 + 2.7e-6 * plane;
   a.cap = !big || !pays || a.nvis >> 31 ? 0 : a.nvis < slots ? a.nvis : slots;
 }
 inline long long grid_shares(const GridArgs& a) { return a.nvis > 0 ? (a.nvis + a.share - 1) / a.share : 1; }
