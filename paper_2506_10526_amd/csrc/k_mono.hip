@@ -23,11 +23,16 @@ __device__ __forceinline__ int shape_bin(double x) {
 }
 
 // Number of edges k1e[0..nk] at or below k1, minus one: the k1 bin, or -1 / nk outside (edges
-// strictly increasing, so a binary search from the largest power of two <= nk + 1 finds the same count as a
-// linear scan; its steps wait for one another, hence not from 64 for every nk).
+// strictly increasing, so a binary search from a power of two TOP with 2 TOP > nk + 1 finds the same count as a
+// linear scan).  Its steps wait for one another, hence 8 for up to 14 bins; unrolled, so that the searches of a
+// thread's cells run side by side (133 x 768^2, all cells binned, allocation-free: 64 bins 1360 us with a loop
+// from the first step <= nk + 1, 1222 now; 12 bins 718 and 683; 64 for every nk: 717).
+constexpr int K1_FEW = 14;
+template <int TOP>
 __device__ __forceinline__ int k1_bin(const double* __restrict__ k1e, int nk, double k1) {
   int c = 0;
-  for (int step = 1 << (31 - __clz(nk + 1)); step > 0; step >>= 1)
+#pragma unroll
+  for (int step = TOP; step > 0; step >>= 1)
     if (c + step <= nk + 1 && k1e[c + step - 1] <= k1) c += step;
   return c - 1;
 }
@@ -35,6 +40,7 @@ __device__ __forceinline__ int k1_bin(const double* __restrict__ k1e, int nk, do
 // (k1, mu, t) of one cell; returns the bin index, or -1 when k1 lies outside the edges.  lo2 / hi2
 // bound the squared largest side from outside the edges with a relative margin of 2^-20 on k1, far above
 // rounding: a cell beyond them is dropped without the square roots, the rest take the exact path.
+template <int TOP>
 __device__ int cell_bin(const double* __restrict__ k1e, int nk, double lo2, double hi2, double kq0, double kq1,
                         double kq2, double kp1, double kp2) {
 #pragma clang fp contract(off)
@@ -51,7 +57,7 @@ __device__ int cell_bin(const double* __restrict__ k1e, int nk, double lo2, doub
   double t = k2 / k1;
   mu = fmin(fmax(mu, 0.5), 1.0);
   t = fmin(fmax(t, 0.5), 1.0);
-  const int j = k1_bin(k1e, nk, k1);
+  const int j = k1_bin<TOP>(k1e, nk, k1);
   if (j < 0 || j >= nk) return -1;
   return j * 25 + shape_bin(mu) * 5 + shape_bin(t);
 }
@@ -93,6 +99,7 @@ __device__ __forceinline__ void row_span(double hi2, double kq1, double kq2, dou
 // into the block's LDS bins with its own atomic (neighbouring cells share bins, but the LDS
 // serialises those adds faster than a wave reduction per bin could combine them); each block
 // writes its partial bins.
+template <int TOP>
 __global__ __launch_bounds__(MONO_THREADS) void k_mono_bin(MonoArgs a) {
   __shared__ double ssum[MONO_MAX_K1 * 25];
   __shared__ int scnt[MONO_MAX_K1 * 25];
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(MONO_THREADS) void k_mono_bin(MonoArgs a) {
 #pragma unroll
       for (int u = 0; u < MONO_NB; ++u) {
         const int j = j0 + u * 64 + lane;
-        bin[u] = j <= jhi ? cell_bin(k1e, a.nk, lo2, hi2, kq0, kq1, kq2, kp1, a.kpar_unit * (double)j) : -1;
+        bin[u] = j <= jhi ? cell_bin<TOP>(k1e, a.nk, lo2, hi2, kq0, kq1, kq2, kp1, a.kpar_unit * (double)j) : -1;
       }
 #pragma unroll
       for (int u = 0; u < MONO_NB; ++u) {
@@ -225,6 +232,7 @@ void launch_part_fin(const double* psum, const int* pcnt, int nblocks, int E, in
 // and add 0 to m > 0.  The bin decision is the monopole's (FP64, no contraction).
 constexpr double MULTI_COLLINEAR_TOL = 1e-9;
 
+template <int TOP>
 __device__ int cell_bin_orient(const double* __restrict__ k1e, int nk, double lo2, double hi2, double kq0,
                                double kq1, double kq2, double kp1, double kp2, double& pz, double& px, double& py,
                                bool& azimuth) {
@@ -241,7 +249,7 @@ __device__ int cell_bin_orient(const double* __restrict__ k1e, int nk, double lo
   double t = k2 / k1;
   mu = fmin(fmax(mu, 0.5), 1.0);
   t = fmin(fmax(t, 0.5), 1.0);
-  const int j = k1_bin(k1e, nk, k1);
+  const int j = k1_bin<TOP>(k1e, nk, k1);
   if (j < 0 || j >= nk) return -1;
   // kpar of the largest and the second side, ties in index order (a stable descending sort)
   int i1 = 0;
@@ -340,6 +348,7 @@ __device__ __forceinline__ void multi_merge(MultiRun& r, int nlm, int lane) {
 // registers while the bin does not change, then those of four lanes are merged in pairs, and only
 // what is left is added to the block's bins (the LDS serialises the lanes that add to one address).  133 x 768^2,
 // l <= 4, 12 k1 bins: 190 us a call without merging, 167 / 162 / 166 / 174 merging 2 / 4 / 8 / 16 lanes.
+template <int TOP>
 __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1e, double lo2, double hi2,
                                             const int* qt, const unsigned* qab, const double* qv, int start,
                                             int n, double* ssum, int* scnt, int nb, int lane) {
@@ -359,7 +368,7 @@ __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1
     double pz = 0.0, px = 0.0, py = 0.0;
     bool az = false;
     const double* kq = a.m.kperp + 3LL * t;
-    const int bin = cell_bin_orient(k1e, a.m.nk, lo2, hi2, kq[0], kq[1], kq[2], a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc),
+    const int bin = cell_bin_orient<TOP>(k1e, a.m.nk, lo2, hi2, kq[0], kq[1], kq[2], a.m.kpar_unit * (double)(2 * ai < nc ? ai : ai - nc),
                                     a.m.kpar_unit * (double)(2 * b < nc ? b : b - nc), pz, px, py, az);
     if (bin < 0) continue;
     if (bin != run.cur) {
@@ -386,14 +395,16 @@ __device__ __forceinline__ double lane_get(double v, int l) {
 
 // Rows (t, a) one per wave, triangles fastest: only rows near a = 0 (mod nc) have cells, and in this order the
 // rows of a wave lie nt-th parts of the grid's stride apart in a (with a fastest, 4096 waves and nc = 768 gave
-// all of them to few waves).  The spans of 64 of a wave's rows are found at a time, a row a lane (a row at a time, the wave waited for its triangle's loads, two square roots and two divisions before the first
-// value).  A scan over the row's span of j, lanes over j, applies the cheap first test
+// all of them to few waves).  The spans of 64 of a wave's
+// rows are found at a time, a row a lane (a row at a time, the wave waited for its triangle's loads, two square
+// roots and two divisions before the first value).  A scan over the row's span of j, lanes over j, applies the cheap first test
 // and reads the values of the surviving cells only (about one cell in twenty at the usual k1 edges);
 // those are queued, and whenever a batch is full it is binned, oriented and weighted with every lane
 // busy (a lane per cell would leave most lanes idle through the costly part).
 // Bound: instruction issue (some 400 a queued cell, most of them FP64: five divisions, four square roots, the
 // weights).  133 x 768^2, l <= 4, 12 k1 bins, 4.4 M cells: 250 us with the rows a fastest (few waves had the cells),
-// a row at a time and every lane's sums added to the bins; now 116
+// a row at a time and every lane's sums added to the bins; now 116.
+template <int TOP>
 __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   extern __shared__ double ssum[];            // [nlm][nb] sums, then nb counts
   __shared__ double k1e[MONO_MAX_K1 + 1];
@@ -462,7 +473,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
         }
         if (tail - head >= MQ_BATCH) {
           __builtin_amdgcn_wave_barrier();   // a wave's LDS accesses stay in program order
-          multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, ssum, scnt, nb, lane);
+          multi_batch<TOP>(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, ssum, scnt, nb, lane);
           __builtin_amdgcn_wave_barrier();
           head += MQ_BATCH;
         }
@@ -470,7 +481,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
     }
   }
   __builtin_amdgcn_wave_barrier();
-  if (tail > head) multi_batch(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
+  if (tail > head) multi_batch<TOP>(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
   __syncthreads();
   for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS)
     a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i] * a.lm_norm[i / nb];
@@ -533,7 +544,7 @@ __global__ __launch_bounds__(256) void k_kpar_fin(KparArgs a, double* __restrict
 }  // namespace
 
 void launch_mono_bin(const MonoArgs& a, int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_mono_bin, dim3(nblocks), dim3(MONO_THREADS), 0, s, a);
+  hipLaunchKernelGGL(a.nk <= K1_FEW ? k_mono_bin<8> : k_mono_bin<64>, dim3(nblocks), dim3(MONO_THREADS), 0, s, a);
 }
 
 void launch_mono_fin(const MonoArgs& a, int nblocks, double* mean, int64_t* count, hipStream_t s) {
@@ -542,8 +553,9 @@ void launch_mono_fin(const MonoArgs& a, int nblocks, double* mean, int64_t* coun
 
 void launch_multi_bin(const MultiArgs& a, int nblocks, hipStream_t s) {
   const size_t lds = (size_t)a.m.nk * 25 * (a.nlm * sizeof(double) + sizeof(int));
-  (void)hipFuncSetAttribute((const void*)k_multi_bin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(k_multi_bin, dim3(nblocks), dim3(MULTI_THREADS), lds, s, a);
+  void (*k)(MultiArgs) = a.m.nk <= K1_FEW ? k_multi_bin<8> : k_multi_bin<64>;
+  (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(k, dim3(nblocks), dim3(MULTI_THREADS), lds, s, a);
 }
 
 void launch_multi_fin(const MultiArgs& a, int nblocks, double* moments, int64_t* count, hipStream_t s) {
