@@ -395,7 +395,8 @@ __device__ __forceinline__ double lane_get(double v, int l) {
 
 // Rows (t, a) one per wave, triangles fastest: only rows near a = 0 (mod nc) have cells, and in this order the
 // rows of a wave lie nt-th parts of the grid's stride apart in a (with a fastest, 4096 waves and nc = 768 gave
-// all of them to few waves).  The spans of 64 of a wave's
+// all of them to few waves).  Neighbouring rows go to different blocks (4 x 24^2, 12 k1 bins: 14.8 us with a
+// block's waves on neighbours, a few blocks then doing all the work, now 11.1).  The spans of 64 of a wave's
 // rows are found at a time, a row a lane (a row at a time, the wave waited for its triangle's loads, two square
 // roots and two divisions before the first value).  A scan over the row's span of j, lanes over j, applies the cheap first test
 // and reads the values of the surviving cells only (about one cell in twenty at the usual k1 edges);
@@ -412,11 +413,13 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   __shared__ int sqt[WPB][MQ_CAP];
   __shared__ unsigned sqab[WPB][MQ_CAP];
   __shared__ double sqv[WPB][MQ_CAP];
+  __shared__ double snorm[MULTI_MAX_NLM];   // lm_norm, read with the edges instead of after the sums
   const int nb = a.m.nk * 25, nlm = a.nlm;
   int* scnt = reinterpret_cast<int*>(ssum + nb * nlm);
   for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS) ssum[i] = 0.0;
   for (int i = threadIdx.x; i < nb; i += MULTI_THREADS) scnt[i] = 0;
   for (int i = threadIdx.x; i <= a.m.nk; i += MULTI_THREADS) k1e[i] = a.m.k1e[i];
+  if ((int)threadIdx.x < nlm) snorm[threadIdx.x] = a.lm_norm[threadIdx.x];
   __syncthreads();
   const double elo = k1e[0] * (1.0 - 0x1p-20), ehi = k1e[a.m.nk] * (1.0 + 0x1p-20);
   const double lo2 = elo * elo, hi2 = ehi * ehi;
@@ -425,7 +428,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   unsigned* qab = sqab[wave];
   double* qv = sqv[wave];
   int head = 0, tail = 0;   // wave-uniform queue positions (mod MQ_CAP on use)
-  for (long long r0 = blockIdx.x * WPB + wave; r0 < (long long)a.m.nt * nc; r0 += 64LL * nwave) {
+  for (long long r0 = blockIdx.x + (long long)wave * gridDim.x; r0 < (long long)a.m.nt * nc; r0 += 64LL * nwave) {
     // this lane's row: empty (jlo > jhi) beyond the last row and above the edges
     const long long row = r0 + (long long)lane * nwave;
     int t = 0, ai = 0, jlo = 0, jhi = -1;
@@ -484,7 +487,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   if (tail > head) multi_batch<TOP>(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
   __syncthreads();
   for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS)
-    a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i] * a.lm_norm[i / nb];
+    a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i] * snorm[i / nb];
   for (int i = threadIdx.x; i < nb; i += MULTI_THREADS) a.m.pcnt[(long long)blockIdx.x * nb + i] = scnt[i];
 }
 
