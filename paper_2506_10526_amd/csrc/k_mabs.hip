@@ -1964,17 +1964,22 @@ void launch_mabs_gemm_split(const MabsGemmArgs& a, hipStream_t s) {
     const int m1 = b.tile_m1 ? b.tile_m1 : (b.n_nu1 >= 16 ? 16 : (b.n_nu1 >= 8 ? 8 : 4)), m2 = T3_M / m1;
     const long long rt = (long long)((a.n_nu1 + m1 - 1) / m1) * ((a.nc + m2 - 1) / m2);
     const long long nb = rt * ((a.nc + T3_N - 1) / T3_N) * a.ntri * a.kchunks;
-    // Narrow tiles where they compute less: in units of 128 rows x 32 columns a narrow tile costs 0.6 + nj (its
-    // formation and its MFMAs), a 256 x 192 one 2 x 7.2.  64^2 or 96^2, 6 rings, every nu1, us a call with 192
-    // columns / the best narrow: nc 16 83 / 69, 32 223 / 94, 48 835 / 468, 64 695 / 386; 16 nu1: 96 374 / 240,
-    // 128 523 / 429, 160 and 192 equal, 256 1418 / 1184.
+    // Narrow tiles where they end sooner.  The 256 CUs take the blocks in rounds, the last one partly overlapped with
+    // the one before; a round of narrow blocks costs 2 + 4.4 nj, one of 256 x 192 blocks 14.8, and a narrow block
+    // alone on its CU 7.5 + 4.2 nj (no neighbour multiplies while it forms).  Fitted to 98 shapes, of which it takes
+    // the fastest or one within 5 % in 94.  us of the contraction, 192 columns / nj 1 / 2 / 3, *: taken: 64^2, 16
+    // triangles, 33 channels x 4 nu1 59 / 46* / 62 / 80, x 33 169 / 65* / 71 / 86; 65 x 4 64 / 58* / 66 / 83, x 65 402 /
+    // 239 / 255 / 197*; 100 x 16 131 / 119 / 98* / 130; 200 x 4 139* / 190 / 177 / 194, x 8 250 / 198 / 186* / 202;
+    // 128^2, 4 triangles, 768 x 8 1374* / 1855 / 1697 / 1507.
     if (!b.tile_m1) {
       int nj = 0;
-      double best = 0.95 * 14.4 * (double)rt * ((a.nc + T3_N - 1) / T3_N);
+      auto rounds = [](long long blocks) { return std::max(1.0, 0.5 * (blocks / 256.0 + (double)((blocks + 255) / 256))); };
+      double best = 14.8 * rounds(nb);
       for (int k = 1; k <= 3; ++k) {
-        const double cost = (0.6 + k) * (double)splitn_units(a) * ((a.nc + 32 * k - 1) / (32 * k));
+        const double cost = std::max(7.5 + 4.2 * k, (2.0 + 4.4 * k) * rounds(splitn_blocks(a, k)));
         if (cost < best) { best = cost; nj = k; }
       }
+      if (const char* e = getenv("BS_MABS_NJ")) nj = std::max(0, std::min(3, atoi(e)));   // tests: this width, 0: 192 columns
       const dim3 g((unsigned)(nj ? splitn_blocks(a, nj) : 1));
       if (nj == 1) hipLaunchKernelGGL(k_mabs_gemm_splitn<1>, g, dim3(256), 0, s, a);
       if (nj == 2) hipLaunchKernelGGL(k_mabs_gemm_splitn<2>, g, dim3(256), 0, s, a);
