@@ -133,7 +133,8 @@ int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3
   Shell3Geom g = fd.g;
   g.uvm = w ? w->uv_mask : nullptr;
   // the delay, v and u passes transform in place (one LDS buffer, twice the resident blocks)
-  // whenever their FFT plans fit; BS_3D_FFT_TWO_BUFFERS (tests) keeps the two-buffer form
+  // whenever their FFT plans fit, the FP64 eta pass at lengths with a compile-time transform;
+  // BS_3D_FFT_TWO_BUFFERS (tests) keeps the two-buffer forms
   const bool two = getenv("BS_3D_FFT_TWO_BUFFERS") != nullptr;
   if (!fd.indicator) {
     Delay3Args d{};
@@ -163,7 +164,7 @@ int fields3_enqueue(bs_ctx* c, const void* vis, const bs_weights* w, const Plan3
   a.ip = two ? 0 : fft_ip_fits(a.plan, p.NLu, 256, 2) ? 2 : fft_ip_fits(a.plan, p.NLu, 256, 4) ? 4 : 0;
   launch_upass3(a, (int)p.wu.size(), fd.fp64, c->stream, ((a.ip ? 1 : 2) * (size_t)p.NLu * (n + 1) + n) * cz);
   LAUNCHCHK(c, "u pass");
-  a.gs = nullptr; a.off_gs = nullptr; a.ip = 0; a.shell_iv = 0;
+  a.gs = nullptr; a.off_gs = nullptr; a.ip = two ? 0 : 1; a.shell_iv = 0;
   if (!F) return BS_OK;
   // eta pass (C2R), output length M
   const int M = fd.M;

@@ -166,6 +166,7 @@ struct Pass3Args {
   FftPlan plan;
   int NL;
   int ip;                      // v / u pass: 2 or 4 = in-place FFT with that many butterflies per thread; 0 = two buffers
+                               // (FP64 eta pass: not 0 = in place where its length has a compile-time transform)
   int indicator;               // v pass: 1 = unit indicator of shell and support, 0 = data
   int shell_iv;                // v pass: 1 = shell membership from the item's s range (Work3::pad)
   int M;                       // eta pass: output length along eta

@@ -1217,7 +1217,7 @@ static void launch_etapass64(const Pass3Args& a, int nwork, hipStream_t s) {
 }
 void launch_etapass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, size_t lds) {
   if (nwork <= 0) return;
-  if (fp64 && a.NL == ETA64_LINES && fft_ct_plan(a.plan, a.plan.L)) {
+  if (fp64 && a.ip > 0 && a.NL == ETA64_LINES && fft_ct_plan(a.plan, a.plan.L)) {
     switch (a.plan.L) {
       case 48: launch_etapass64<48>(a, nwork, s); return;
       case 64: launch_etapass64<64>(a, nwork, s); return;
