@@ -337,8 +337,11 @@ int est3_prepare(bs_ctx* c, const bs_bins* b, const bs_weights* w, int32_t preci
     for (int m : {96, 128, 192, 256, 384, 512, 768})
       if (m > 3 * P.eta_max && m < P.nc) { e.M64 = m; break; }
   e.vox64 = (long long)e.M64 * P.n * P.n;
-  // blocks of a dozen slabs or more, at most 1024 (two resident a CU, two rounds)
-  e.nblk64 = std::max<long long>(1, std::min<long long>(1024, e.vox64 / (12 * 128)));
+  // Up to two blocks a CU of three 128-voxel slabs or more, beyond them blocks of a dozen slabs, at most 1024 (two
+  // resident a CU, two rounds).  us of the FP64 contraction, least slabs of 3 / 6 / 12 / 24: 16^2 x 32 9.8 / 13 / 21 /
+  // 43, 48^2 x 96 23 / 22 / 27 / 45, 48^2 x 192 31 / 34 / 35 / 45, 48^2 x 768 162 / 157 / 150 / 182.
+  e.nblk64 = std::max<long long>(1, std::max(std::min<long long>(512, e.vox64 / (3 * 128)),
+                                             std::min<long long>(1024, e.vox64 / (12 * 128))));
   e.chunk64 = ((e.vox64 + e.nblk64 - 1) / e.nblk64 + 127) / 128 * 128;
   e.nblk64 = (e.vox64 + e.chunk64 - 1) / e.chunk64;
   // partial sums: one slot per contraction block, or per wave of the MFMA synthesis kernel (8 x 256)

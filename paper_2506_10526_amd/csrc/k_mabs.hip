@@ -2034,8 +2034,10 @@ void launch_mabs_gemm_f32(const MabsGemmArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_mabs_gemm<1>, gemm_grid(a, TM, TN), dim3(256), 0, s, a);
 }
 // Tile of the FP64 contraction.  Column tiles of 16 CT: the CT in 1..4 with the least padded work, a
-// tile of few columns counted dearer for its staging per MFMA.  Two nu1 a wave where there are two, and as
-// many of the four waves along nu1 as have rows (the others take further nu2 rows).
+// tile of few columns counted dearer for its staging per MFMA.  us of the contraction for CT 1 / 2 / 3 / 4, *: taken:
+// 64^2, 75 triangles, 16 channels 70* / 104 / 141 / 182; 16 triangles, 17 77 / 64* / 88 / 111, 40 x 8 nu1 67 / 67 / 65* /
+// 82, 65 1247* / 1279 / 1241 / 1617, 80 x 8 149 / 155* / 144 / 183, 128 x 8 356 / 297 / 327 / 288*.  Two nu1 a wave
+// where there are two, and as many of the four waves along nu1 as have rows (the others take further nu2 rows).
 static void f64_tile(const MabsGemmArgs& a, int& ti, int& wi, int& ct) {
   const int n16 = (a.nc + 15) / 16;
   double best = 0.0;
