@@ -171,7 +171,8 @@ int bs_grid_visibilities(bs_ctx* ctx, int32_t n, int32_t nc, double du_lambda, i
  * rings: BS_RING_U bins (their n, edges and umax are used); uv: device float64 [n_vis][2] baselines in
  * wavelengths, the same in every channel, no flags.  D_host: host float64 [n_candidates], NaN where
  * no closed grid triangle has all three cells sampled.  Synchronises the context's stream.
- * Scratch: about (n_nodes^2 / 2) n (n/2+1) 40 bytes of context workspace.
+ * Scratch: about (n_nodes^2 / 2) n (n/2+1) 40 bytes of context workspace, and that of gridding the baselines in
+ * n_nodes^2 / 2 output channels (bs_grid_visibilities: up to 1 GiB of staging from 32,768 baselines).
  * Errors: BS_EINVAL (not ring bins, n_nodes not even in [2, 32], du or theta0 not positive, more than
  * 65535 baselines in one cell, bad pointers), BS_ENOMEM, BS_EHIP, and those of bs_estimate_mabs. */
 int bs_decorrelation(bs_ctx* ctx, const bs_bins* rings, int64_t n_vis, const double* uv, double du_lambda,

@@ -391,15 +391,12 @@ __device__ __forceinline__ void split8(const float* v, bf16x8& h, bf16x8& l) {
   l = __builtin_bit_cast(bf16x8, v4u_t{lw[0], lw[1], lw[2], lw[3]});
 }
 
-template <int MODE>
-using acc_t = f32x4;
-
 // One 32-voxel step of one wave: voxels v0 .. v0+31 of the LDS field rows sF + j*ld
 // (j < nbu; rows beyond nbu read as zero).  A rows are the pair products F_a F_b, B columns
 // the fields F_c; sp holds the pair table (-1 = padding row).
-template <int MODE, typename T>
-__device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int nbu, int v0, const int* sp, int RT,
-                                          int CT, acc_t<MODE> (&acc)[C3_RT][C3_CT]) {
+template <int MODE>
+__device__ __forceinline__ void con3_step(const float* __restrict__ sF, int ld, int nbu, int v0, const int* sp, int RT,
+                                          int CT, f32x4 (&acc)[C3_RT][C3_CT]) {
   const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
   if constexpr (MODE == 2) {
     const int vb = v0 + kq * 8;
@@ -409,7 +406,7 @@ __device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int 
       float v[8];
       const int c = ct * 16 + r16;
       if (c < nbu) {
-        const T* src = &sF[(size_t)c * ld + vb];
+        const float* src = &sF[(size_t)c * ld + vb];
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q] = (float)src[q];
       } else {
@@ -425,8 +422,8 @@ __device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int 
         int pa = sp[2 * p], pb = sp[2 * p + 1];
         float v[8];
         if (pa >= 0) {
-          const T* sa = &sF[(size_t)pa * ld + vb];
-          const T* sb = &sF[(size_t)pb * ld + vb];
+          const float* sa = &sF[(size_t)pa * ld + vb];
+          const float* sb = &sF[(size_t)pb * ld + vb];
 #pragma unroll
           for (int q = 0; q < 8; ++q) v[q] = (float)sa[q] * (float)sb[q];
         } else {
@@ -449,18 +446,18 @@ __device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int 
 #pragma unroll 2
     for (int ks = 0; ks < 8; ++ks) {
       const int vx = v0 + ks * 4 + kq;
-      T bv[C3_CT];
+      float bv[C3_CT];
 #pragma unroll
       for (int ct = 0; ct < C3_CT; ++ct) {
         const int c = ct * 16 + r16;
-        bv[ct] = c < nbu ? sF[(size_t)c * ld + vx] : T(0);
+        bv[ct] = c < nbu ? sF[(size_t)c * ld + vx] : 0.f;
       }
 #pragma unroll
       for (int rt = 0; rt < C3_RT; ++rt) {
         if (rt < RT) {
           int p = rt * 16 + r16;
           int pa = sp[2 * p], pb = sp[2 * p + 1];
-          T av = pa >= 0 ? sF[(size_t)pa * ld + vx] * sF[(size_t)pb * ld + vx] : T(0);
+          float av = pa >= 0 ? sF[(size_t)pa * ld + vx] * sF[(size_t)pb * ld + vx] : 0.f;
 #pragma unroll
           for (int ct = 0; ct < C3_CT; ++ct) {
             if (ct < CT) {
@@ -473,8 +470,7 @@ __device__ __forceinline__ void con3_step(const T* __restrict__ sF, int ld, int 
   }
 }
 
-template <int MODE>
-__device__ __forceinline__ void con3_flush(acc_t<MODE> (&acc)[C3_RT][C3_CT], double (&acc64)[C3_RT][C3_CT][4]) {
+__device__ __forceinline__ void con3_flush(f32x4 (&acc)[C3_RT][C3_CT], double (&acc64)[C3_RT][C3_CT][4]) {
 #pragma unroll
   for (int i = 0; i < C3_RT; ++i)
 #pragma unroll
@@ -485,8 +481,7 @@ __device__ __forceinline__ void con3_flush(acc_t<MODE> (&acc)[C3_RT][C3_CT], dou
 
 // Reduce the four waves' sums in a fixed order into red[112][32] and store them as this
 // block's partial sums.  red must be zeroed and visible to all threads before the call.
-template <int MODE>
-__device__ __forceinline__ void con3_store(acc_t<MODE> (&acc)[C3_RT][C3_CT], double (&acc64)[C3_RT][C3_CT][4],
+__device__ __forceinline__ void con3_store(f32x4 (&acc)[C3_RT][C3_CT], double (&acc64)[C3_RT][C3_CT][4],
                                            double* red, double* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, kq = lane >> 4;
   for (int wv = 0; wv < 4; ++wv) {
@@ -507,16 +502,16 @@ __device__ __forceinline__ void con3_store(acc_t<MODE> (&acc)[C3_RT][C3_CT], dou
 }
 
 // Contraction over precomputed fields F[j][vox] streamed through LDS in 128-voxel slabs.
-template <int MODE, typename T>  // MODE 1: FP32 MFMA, 2: split-BF16 MFMA
+template <int MODE>  // 1: FP32 MFMA, 2: split-BF16 MFMA
 __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
-  __shared__ T sF[32 * C3_LDS];
+  __shared__ float sF[32 * C3_LDS];
   __shared__ int sp[2 * 112];
   __shared__ double red[112 * 32];
   const int tid = threadIdx.x, wave = tid >> 6;
   for (int e = tid; e < 2 * 112; e += 256) sp[e] = e < 2 * a.npairs ? a.pairs[e] : -1;
   for (int e = tid; e < 112 * 32; e += 256) red[e] = 0.0;
   const int RT = (a.npairs + 15) / 16, CT = (a.nbu + 15) / 16;
-  acc_t<MODE> acc[C3_RT][C3_CT];
+  f32x4 acc[C3_RT][C3_CT];
   double acc64[C3_RT][C3_CT][4];
 #pragma unroll
   for (int i = 0; i < C3_RT; ++i)
@@ -526,22 +521,22 @@ __global__ __launch_bounds__(256) void k3_contract(Con3Args a) {
       for (int q = 0; q < 4; ++q) { acc[i][j][q] = 0; acc64[i][j][q] = 0.0; }
   const long long x_beg = (long long)blockIdx.x * a.chunk;
   const long long x_end = x_beg + a.chunk < a.vox ? x_beg + a.chunk : a.vox;
-  const T* F = (const T*)a.F;
+  const float* F = (const float*)a.F;
   int since = 0;
   __syncthreads();
   for (long long x0 = x_beg; x0 < x_end; x0 += C3_SLAB) {
     for (int e = tid; e < a.nbu * C3_SLAB; e += 256) {
       int j = e / C3_SLAB, v = e - j * C3_SLAB;
       long long x = x0 + v;
-      sF[j * C3_LDS + v] = x < x_end ? F[(size_t)j * a.vox + x] : T(0);
+      sF[j * C3_LDS + v] = x < x_end ? F[(size_t)j * a.vox + x] : 0.f;
     }
     __syncthreads();
-    con3_step<MODE, T>(sF, C3_LDS, a.nbu, wave * 32, sp, RT, CT, acc);
+    con3_step<MODE>(sF, C3_LDS, a.nbu, wave * 32, sp, RT, CT, acc);
     __syncthreads();
     since += C3_SLAB;
-    if (since >= 512) { since = 0; con3_flush<MODE>(acc, acc64); }   // FP64 flush
+    if (since >= 512) { since = 0; con3_flush(acc, acc64); }   // FP64 flush
   }
-  con3_store<MODE>(acc, acc64, red, a.partial + (size_t)blockIdx.x * 112 * 32);
+  con3_store(acc, acc64, red, a.partial + (size_t)blockIdx.x * 112 * 32);
 }
 
 // The FP64 form (FP64 data, triangle counts).  A block streams slabs of 128 voxels of all fields through
@@ -694,7 +689,7 @@ __global__ __launch_bounds__(256) void k3_fused(Fused3Args a) {
     sj[e] = j;
   }
   const int RT = (a.npairs + 15) / 16, CT = (nbu + 15) / 16;
-  acc_t<MODE> acc[C3_RT][C3_CT];
+  f32x4 acc[C3_RT][C3_CT];
   double acc64[C3_RT][C3_CT][4];
 #pragma unroll
   for (int i = 0; i < C3_RT; ++i)
@@ -760,7 +755,7 @@ __global__ __launch_bounds__(256) void k3_fused(Fused3Args a) {
     __syncthreads();
     if (nfft > 0) lds_fft<+1, float, true>(A + (size_t)nlow * ld, Bf + (size_t)nlow * ld, a.plan, nfft, tw, 2, ld);
     const float* Fl = Rf;   // row j: floats [2 j ld, 2 j ld + M)
-    for (int v0 = wave * 32; v0 < M; v0 += 128) con3_step<MODE, float>(Fl, 2 * ld, nbu, v0, sp, RT, CT, acc);
+    for (int v0 = wave * 32; v0 < M; v0 += 128) con3_step<MODE>(Fl, 2 * ld, nbu, v0, sp, RT, CT, acc);
     if (more) {
       Cx<float>* nx = stage + (cur ^ 1) * FUSED_STAGE;
       if (tid < L) nx[tid] = pf0;
@@ -769,12 +764,12 @@ __global__ __launch_bounds__(256) void k3_fused(Fused3Args a) {
     cur ^= 1;
     __syncthreads();
     since += M / 4;   // voxels per wave per line
-    if (since >= 512) { since = 0; con3_flush<MODE>(acc, acc64); }
+    if (since >= 512) { since = 0; con3_flush(acc, acc64); }
   }
   double* red = (double*)smem_raw;   // reuse the FFT buffers
   for (int e = tid; e < 112 * 32; e += 256) red[e] = 0.0;
   __syncthreads();
-  con3_store<MODE>(acc, acc64, red, a.partial + (size_t)blockIdx.x * 112 * 32);
+  con3_store(acc, acc64, red, a.partial + (size_t)blockIdx.x * 112 * 32);
 }
 
 // Split-BF16 fused kernel: the C2R along eta as MFMA GEMMs against a twiddle-fragment table, then
@@ -1232,8 +1227,8 @@ void launch_etapass3(const Pass3Args& a, int nwork, bool fp64, hipStream_t s, si
   else { set_lds<float>((const void*)k3_etapass<float>, lds); hipLaunchKernelGGL(k3_etapass<float>, dim3(nwork), dim3(256), lds, s, a); }
 }
 void launch_contract3(const Con3Args& a, int mode, int nblocks, hipStream_t s) {
-  if (mode == 1) hipLaunchKernelGGL((k3_contract<1, float>), dim3(nblocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k3_contract<2, float>), dim3(nblocks), dim3(256), 0, s, a);
+  if (mode == 1) hipLaunchKernelGGL((k3_contract<1>), dim3(nblocks), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k3_contract<2>), dim3(nblocks), dim3(256), 0, s, a);
 }
 template <int RT>
 static void launch_contract64_rt(const Con3Args& a, int nblocks, hipStream_t s) {
