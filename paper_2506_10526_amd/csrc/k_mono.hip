@@ -275,16 +275,17 @@ __device__ int cell_bin_orient(const double* __restrict__ k1e, int nk, double lo
   return j * 25 + shape_bin(mu) * 5 + shape_bin(t);
 }
 
-// acc[i] += v norm[i] Q_l^m(x) Re((px + i py)^m) for i in lm order up to the largest lmax (the caller drops l > lmax),
-// with m > 0 zero without azimuth.  The loops' bounds are constant, so that the recurrence's coefficients,
+// acc[i] += v norm[i] Q_l^m(x) Re((px + i py)^m) for i in lm order up to LMAX (the caller drops l > lmax), with
+// m > 0 zero without azimuth.  The loops' bounds are constant, so that the recurrence's coefficients,
 // 1 / (l - m) among them, are constants.  The norm goes into each weight: multiplied into the block's sums it
 // rounds those once more (error of 16 draws of 5 x 48^2 cells, l <= 2, 1.5e-16 for 0.9e-16; 2 % faster).
+template <int LMAX>
 __device__ __forceinline__ void multi_add(const double* __restrict__ norm, double v, double x, double px, double py, bool azimuth, double* acc) {
   double cr = 1.0, ci = 0.0;   // Re, Im of (px + i py)^m (without v: an infinite value gives the signs of its weights)
   double qmm = 1.0;            // Q_m^m = (-1)^m (2m - 1)!!
   if (!azimuth) px = py = 0.0;
 #pragma unroll
-  for (int m = 0; m <= MULTI_MAX_LMAX; ++m) {
+  for (int m = 0; m <= LMAX; ++m) {
     if (m > 0) {
       const double r = cr * px - ci * py;
       ci = cr * py + ci * px;
@@ -293,7 +294,7 @@ __device__ __forceinline__ void multi_add(const double* __restrict__ norm, doubl
     }
     double q2 = 0.0, q1 = qmm;   // Q_{l-2}^m, Q_{l-1}^m
 #pragma unroll
-    for (int l = m; l <= MULTI_MAX_LMAX; ++l) {
+    for (int l = m; l <= LMAX; ++l) {
       double q;
       if (l == m) q = qmm;
       else if (l == m + 1) q = x * (2.0 * m + 1.0) * qmm;
@@ -349,7 +350,7 @@ __device__ __forceinline__ void multi_merge(MultiRun& r, int nlm, int lane) {
 // registers while the bin does not change, then those of four lanes are merged in pairs, and only
 // what is left is added to the block's bins (the LDS serialises the lanes that add to one address).  133 x 768^2,
 // l <= 4, 12 k1 bins: 190 us a call without merging, 167 / 162 / 166 / 174 merging 2 / 4 / 8 / 16 lanes.
-template <int TOP>
+template <int TOP, int LMAX>
 __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1e, double lo2, double hi2,
                                             const int* qt, const unsigned* qab, const double* qv, int start,
                                             int n, double* ssum, int* scnt, int nb, int lane) {
@@ -379,7 +380,7 @@ __device__ __forceinline__ void multi_batch(const MultiArgs& a, const double* k1
 #pragma unroll
       for (int i = 0; i < MULTI_MAX_NLM; ++i) run.acc[i] = 0.0;
     }
-    multi_add(a.lm_norm, v, pz, px, py, az, run.acc);
+    multi_add<LMAX>(a.lm_norm, v, pz, px, py, az, run.acc);
     ++run.cnt;
   }
   if (n > MQ_BATCH / 2) {   // a short last batch (small calls) is not worth the merges
@@ -406,7 +407,7 @@ __device__ __forceinline__ double lane_get(double v, int l) {
 // Bound: instruction issue (some 400 a queued cell, most of them FP64: five divisions, four square roots, the
 // weights).  133 x 768^2, l <= 4, 12 k1 bins, 4.4 M cells: 250 us with the rows a fastest (few waves had the cells),
 // a row at a time and every lane's sums added to the bins; now 116.
-template <int TOP>
+template <int TOP, int LMAX>
 __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   extern __shared__ double ssum[];            // [nlm][nb] sums, then nb counts
   __shared__ double k1e[MONO_MAX_K1 + 1];
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
         }
         if (tail - head >= MQ_BATCH) {
           __builtin_amdgcn_wave_barrier();   // a wave's LDS accesses stay in program order
-          multi_batch<TOP>(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, ssum, scnt, nb, lane);
+          multi_batch<TOP, LMAX>(a, k1e, lo2, hi2, qt, qab, qv, head, MQ_BATCH, ssum, scnt, nb, lane);
           __builtin_amdgcn_wave_barrier();
           head += MQ_BATCH;
         }
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
     }
   }
   __builtin_amdgcn_wave_barrier();
-  if (tail > head) multi_batch<TOP>(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
+  if (tail > head) multi_batch<TOP, LMAX>(a, k1e, lo2, hi2, qt, qab, qv, head, tail - head, ssum, scnt, nb, lane);
   __syncthreads();
   for (int i = threadIdx.x; i < nb * nlm; i += MULTI_THREADS)
     a.m.psum[(long long)blockIdx.x * nb * nlm + i] = ssum[i];
@@ -555,7 +556,10 @@ void launch_mono_fin(const MonoArgs& a, int nblocks, double* mean, int64_t* coun
 
 void launch_multi_bin(const MultiArgs& a, int nblocks, hipStream_t s) {
   const size_t lds = (size_t)a.m.nk * 25 * (a.nlm * sizeof(double) + sizeof(int));
-  void (*k)(MultiArgs) = a.m.nk <= K1_FEW ? k_multi_bin<8> : k_multi_bin<64>;
+  // moments to l = 1 alone without the other twelve weights (133 x 768^2, all cells in 64 bins, l = 0: 1425 us with
+  // them, 1239 without)
+  void (*k)(MultiArgs) = a.lmax <= 1 ? (a.m.nk <= K1_FEW ? k_multi_bin<8, 1> : k_multi_bin<64, 1>)
+                                     : (a.m.nk <= K1_FEW ? k_multi_bin<8, MULTI_MAX_LMAX> : k_multi_bin<64, MULTI_MAX_LMAX>);
   (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(k, dim3(nblocks), dim3(MULTI_THREADS), lds, s, a);
 }
