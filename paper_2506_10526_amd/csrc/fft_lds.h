@@ -227,8 +227,8 @@ __device__ void lds_fft_ip(Cx<T>* a, const FftPlan& p, int nl, const Cx<T>* __re
 // stockham_pass_ip in the same order, so the results are the same bits; what goes is the index
 // arithmetic, which was about half of the vector instructions of the passes that run these transforms
 // (LDS addresses become one base with constant offsets, the divisions shifts or constant products).
-// Measured: ring-field passes of 192 x 256^2 402 -> 316 us, 3D passes of 256^2 x 768 256 -> 228 us
-// (delay 78 -> 72, v 70 -> 62, u 109 -> 94).
+// Measured: ring-field passes of 192 x 256^2, 10 rings, 402 -> 274 us, 3D passes of 256^2 x 768 256 -> 224 us
+// (delay 78 -> 71, v 70 -> 61, u 109 -> 93).
 constexpr int fft_ct_radix(int rem) {   // next radix when the product `rem` of radices is left
   if (rem % 3 == 0) return 3;
   int p = 0;

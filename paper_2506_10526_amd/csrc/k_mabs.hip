@@ -25,7 +25,7 @@ __device__ __forceinline__ int signed_idx(int i, int n) { return i < (n + 1) / 2
 //     holds v_b + 1 <= n / 2 of them, so the pass needs no workspace;
 //   rows (k_ring_rows): C2R along v, each row read into LDS and written over itself.
 // Bound: HBM, the rows' 4 n^2 bytes (FP32).  One block per (ring, channel, g) with the whole plane's columns in
-// LDS ran one block a CU: 10 rings x 192 channels x 256^2 FP32 1690 us, now 91 + 178 (113 + 289 with run-time FFT
+// LDS ran one block a CU: 10 rings x 192 channels x 256^2 FP32 1690 us, now 95 + 179 (113 + 289 with run-time FFT
 // plans); loading all of a thread's cells before the first is used made the column pass 127 us.
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -1056,7 +1056,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // Every entry takes the operations of split3_tile in its order (per 16 pixels A lo B hi, A hi B hi, A hi B lo;
 // FP64 every T3_FLUSH pixels), so the results are the same bits.  Two blocks a CU, one forming while the
 // other multiplies.  Bound: VALU of the formation (about as long as the MFMAs at NJ = 2).  48 channels of
-// 96^2, 6 rings, every nu1: 766 us in 256 x 192 tiles, now 386.
+// 96^2, 6 rings, every nu1: 766 us in 256 x 192 tiles, now 369.
 // ---------------------------------------------------------------------------
 constexpr int TN_I = 8, TN_J = 16;              // unit: nu1 x nu2
 constexpr int TN_F2 = 128 * 4;                  // floats before the F_b2 rows: two copy instructions of F_b1
@@ -1569,8 +1569,8 @@ __global__ void k_zero_i32(int* p, int n) {
 // per lane at the fragment read, F1 being a broadcast.  Lane group g takes pixels 4 g .. 4 g + 3 of a
 // stage, one per MFMA step, on both operands; rows of 18 doubles put 16 rows' 16-byte reads on distinct
 // banks.  Bound: FP64 issue.  Measured against 64 x 64 tiles with both A rows loaded per element: counts
-// of 96^2 x 48 channels, 6 rings 3825 -> 1487 us (55 TFLOP/s; a large FP64 matrix product reaches 73 on this
-// card); 64^2 x 16, 8 rings, whose 16 columns filled a quarter of a tile, 420 -> 71 us.
+// of 96^2 x 48 channels, 6 rings 3825 -> 1388 us (58 TFLOP/s; a large FP64 matrix product reaches 73 on this
+// card); 64^2 x 16, 8 rings, whose 16 columns filled a quarter of a tile, 420 -> 69 us.
 // ---------------------------------------------------------------------------
 typedef double f64x4m __attribute__((ext_vector_type(4)));
 constexpr int G64_K = 16, G64_LD = G64_K + 2;

@@ -45,7 +45,7 @@ __device__ __forceinline__ double window_at(const MdftArgs& a, const double* __r
 // go to Y[t][a][c] (runs of W contiguous entries per a).
 // LC: the length at compile time (four column pairs, 512 threads, all of a thread's loads in flight at once), 0:
 // any.  Bound: HBM (8 bytes in, 8 out per window entry).  133 x 768^2: 500 us with the run-time transform
-// and groups dealt to the XCDs in turn, now 330 (3.8 TB/s).  Blocks of 256
+// and groups dealt to the XCDs in turn, now 356 (3.7 TB/s).  Blocks of 256
 // threads or two column pairs, a prefetch of the next group and slices of triangles whose half spectra
 // stay in the 256 MB cache between the passes were all slower.
 template <int BM, int LC>
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(MDFT_THREADS) void k_mdft_n(MdftArgs a) {
 
 // Pass m: NL rows a < H of Y per group, transformed along m, scaled; row a of the output and its
 // Hermitian mirror, row L - a, are written whole.  LC: as in pass n (two rows, 256 threads).  Bound: HBM (16
-// bytes in, 32 out per half-spectrum entry); 133 x 768^2: 376 us before, now 356, 5.3 TB/s; shorter lengths were
+// bytes in, 32 out per half-spectrum entry); 133 x 768^2: 376 us before, now 339, 5.6 TB/s; shorter lengths were
 // bound by the index arithmetic of the run-time transform (133 x 192^2: 21 us less).
 template <int BM, int LC>
 __global__ __launch_bounds__(MDFT_THREADS) void k_mdft_m(MdftArgs a) {

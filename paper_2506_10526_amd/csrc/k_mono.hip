@@ -406,7 +406,7 @@ __device__ __forceinline__ double lane_get(double v, int l) {
 // busy (a lane per cell would leave most lanes idle through the costly part).
 // Bound: instruction issue (some 400 a queued cell, most of them FP64: five divisions, four square roots, the
 // weights).  133 x 768^2, l <= 4, 12 k1 bins, 4.4 M cells: 250 us with the rows a fastest (few waves had the cells),
-// a row at a time and every lane's sums added to the bins; now 116.
+// a row at a time and every lane's sums added to the bins; now 113.
 template <int TOP, int LMAX>
 __global__ __launch_bounds__(MULTI_THREADS) void k_multi_bin(MultiArgs a) {
   extern __shared__ double ssum[];            // [nlm][nb] sums, then nb counts
