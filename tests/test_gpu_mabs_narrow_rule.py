@@ -34,7 +34,7 @@ def test_no_slower_than_wide(monkeypatch, n, nc, rings, nu):
         monkeypatch.setenv("BS_MABS_M1", str(min(16, nu)))
         wide = us()
         print(f"[narrow rule] n={n} nc={nc} nu1={nu}: {rule:.1f} us, wide {wide:.1f} us", flush=True)
-        assert rule <= 1.12 * wide, (rule, wide)
+        assert rule <= 1.06 * wide, (rule, wide)
     finally:
         bs.bs_free_bins(h)
         c.close()
